@@ -110,9 +110,11 @@ struct apx_problem {
     long long n_live = 0;                         // floats of live-PSF stamps (3 P^2 each)
     bool has_live_cols = false;                   // some live PSF has a free parameter
     std::vector<DPair> pairs;
-    std::vector<PairItem> pitems64, pitems16;
+    std::vector<PairItem> pitems64;               // 64 x 64 tiles of two wide groups
     std::vector<PairItem> gitems;                 // 4 x 4-block Gram items, sorted by tile count
     int gram_begin[GRAM4_MAX_T + 2] = {};         // items of tile count t: [gram_begin[t], gram_begin[t + 1])
+    std::vector<PairItem> xitems;                 // 4 x 4-block items of two groups, sorted by block shape
+    int cross_begin[N_CROSS + 1] = {};            // items of block shape k: [cross_begin[k], cross_begin[k + 1])
     // reduction tables
     std::vector<int> img_seg, img_idx;            // FWD items of each image
     std::vector<int> col_seg, col_idx;            // JCOL items of each column
@@ -398,7 +400,7 @@ static int pair_slots(apx_ctx* C) {
             n_cu = v;
         else
             (void)hipGetLastError();
-        const int b = pair_blocks_per_cu(64);
+        const int b = pair_blocks_per_cu();
         if (b > 0) per_cu = b;
     }
     C->pair_slots = per_cu * n_cu;
@@ -1232,20 +1234,21 @@ static apx_status build_plan(apx_problem* P, const apx_problem_desc* d) {
         }
     }
 
-    // pairs of groups on one image whose output boxes intersect.  A pair's box is cut
-    // into K-slices of whole LDS stages (KC pixels of one row).  Narrow pairs (16-wide
-    // tiles) take slices of about 4096 pixels.  The 64-wide tile pairs share the grid in
-    // proportion to their work, so their items fill the resident workgroups of the chip
-    // about once (no second, partly empty wave of workgroups); each item still gets at
-    // least 32 stages.
+    // pairs of groups on one image whose output boxes intersect.  Pairs of two wide groups
+    // run on 64 x 64 tiles: their K-slices are whole LDS stages (KC pixels of one row), and the
+    // tile pairs share the grid in proportion to their work, so their items fill the resident
+    // workgroups of the chip about once (no second, partly empty wave of workgroups); each
+    // item still gets at least 32 stages.  All other pairs run on 4 x 4 blocks over runs of
+    // pixels (add_runs).
     {
         struct Wide { int pi, na, nb, tri, stages; };
+        struct Narrow { int pi, na, nb; };
         std::vector<Wide> wide;
-        std::vector<std::vector<PairItem>> gram_items(GRAM4_MAX_T + 1);
+        std::vector<std::vector<Narrow>> self(GRAM4_MAX_T + 1), cross(N_CROSS);
         long long outoff = 0;
         auto tile_pairs = [](int na, int nb, int tri) { return tri ? na * (na + 1) / 2 : na * nb; };
         // K-slices outermost: the tile pairs that run together read the same rows of J
-        auto add_pair_items = [&](int pi, int na, int nb, bool tri, int stages, int per, int tm) {
+        auto add_pair_items = [&](int pi, int na, int nb, bool tri, int stages, int per) {
             for (int s0 = 0; s0 < stages; s0 += per)
                 for (int ta = 0; ta < na; ++ta)
                     for (int tb = tri ? ta : 0; tb < nb; ++tb) {
@@ -1256,8 +1259,8 @@ static apx_status build_plan(apx_problem* P, const apx_problem_desc* d) {
                         it.s0 = s0;
                         it.s1 = std::min(stages, s0 + per);
                         it.out_off = outoff;
-                        outoff += (long long)tm * tm;
-                        (tm == 64 ? P->pitems64 : P->pitems16).push_back(it);
+                        outoff += 64LL * 64;
+                        P->pitems64.push_back(it);
                     }
         };
         std::vector<std::vector<int>> by_img(d->n_images);
@@ -1267,37 +1270,34 @@ static apx_status build_plan(apx_problem* P, const apx_problem_desc* d) {
             const auto& gl = by_img[k];
             for (size_t a = 0; a < gl.size(); ++a)
                 for (size_t b = a; b < gl.size(); ++b) {
-                    const DGroup& G = P->groups[gl[a]];
-                    const DGroup& H = P->groups[gl[b]];
+                    // pair.g is the group with more 4-column tiles
+                    const bool swap = ceil_div(P->groups[gl[a]].ncols, 4) < ceil_div(P->groups[gl[b]].ncols, 4);
+                    const int ig = swap ? gl[b] : gl[a], ih = swap ? gl[a] : gl[b];
+                    const DGroup& G = P->groups[ig];
+                    const DGroup& H = P->groups[ih];
                     const int y0 = std::max(G.oy0, H.oy0), x0 = std::max(G.ox0, H.ox0);
                     const int y1 = std::min(G.oy0 + G.oh, H.oy0 + H.oh), x1 = std::min(G.ox0 + G.ow, H.ox0 + H.ow);
                     if (y1 <= y0 || x1 <= x0) continue;
-                    DPair pr{gl[a], gl[b], k, G.sub, y0, x0, y1, x1};
                     const int pi = (int)P->pairs.size();
-                    P->pairs.push_back(pr);
-                    const int tm = (std::min(G.ncols, H.ncols) >= 48) ? 64 : 16;
-                    const int na = ceil_div(G.ncols, tm), nb = ceil_div(H.ncols, tm);
-                    const int stages = (y1 - y0) * ceil_div(x1 - x0, PAIR_KC);
-                    const bool tri = gl[a] == gl[b];
-                    if (tri && G.ncols <= 4 * GRAM4_MAX_T) {
-                        // a narrow group with itself: 4 x 4 blocks (k_gram4), K-slices of ~4096 px
-                        const int nt = ceil_div(G.ncols, 4);
-                        const int per = std::max(1, 4096 / PAIR_KC);
-                        for (int s0 = 0; s0 < stages; s0 += per) {
-                            PairItem it{};
-                            it.pair = pi;
-                            it.ta = nt;
-                            it.s0 = s0;
-                            it.s1 = std::min(stages, s0 + per);
-                            gram_items[nt].push_back(it);
-                        }
+                    P->pairs.push_back(DPair{ig, ih, k, G.sub, y0, x0, y1, x1});
+                    const bool tri = ig == ih;
+                    if (std::min(G.ncols, H.ncols) >= WIDE_COLS) {
+                        wide.push_back({pi, ceil_div(G.ncols, 64), ceil_div(H.ncols, 64), tri ? 1 : 0,
+                                        (y1 - y0) * ceil_div(x1 - x0, PAIR_KC)});
                         continue;
                     }
-                    if (tm == 64) {
-                        wide.push_back({pi, na, nb, tri ? 1 : 0, stages});
+                    const int na = ceil_div(G.ncols, 4), nb = ceil_div(H.ncols, 4);
+                    if (tri && na <= GRAM4_MAX_T) {
+                        self[na].push_back({pi, na, nb});
                         continue;
                     }
-                    add_pair_items(pi, na, nb, tri, stages, std::max(1, 4096 / PAIR_KC), 16);
+                    // the smallest block shape that holds min(na, 8) x min(nb, 4) tiles
+                    int shape = N_CROSS - 1;
+                    for (int q = N_CROSS - 1; q >= 0; --q)
+                        if (cross_a(q) >= std::min(na, 8) && cross_b(q) >= std::min(nb, 4) &&
+                            cross_a(q) * cross_b(q) <= cross_a(shape) * cross_b(shape))
+                            shape = q;
+                    cross[shape].push_back({pi, na, nb});
                 }
         }
         long long work = 0;
@@ -1308,18 +1308,59 @@ static apx_status build_plan(apx_problem* P, const apx_problem_desc* d) {
             const double share = (double)slots * tp * w.stages / (double)std::max(1LL, work);
             int slices = std::max(1, (int)(share / tp));
             slices = std::min(slices, std::max(1, w.stages / 32));
-            add_pair_items(w.pi, w.na, w.nb, w.tri, w.stages, ceil_div(w.stages, slices), 64);
+            add_pair_items(w.pi, w.na, w.nb, w.tri, w.stages, ceil_div(w.stages, slices));
         }
+        // The items of one launch: runs of pixels of every pair's box (bands of rows keep the
+        // pixel count of a band in 30 bits).  A run is 256 .. 4096 pixels, as short as it takes
+        // to make GRAM_ITEMS items: with few workgroups on the chip the kernel waits for its
+        // loads (three Jacobian phases of 768 cutouts, all tile counts: 1525 us with runs of
+        // 4096 pixels of padded rows, 989 us with these), and more partials cost the assembly.
+        constexpr int GRAM_ITEMS = 2048;
+        auto add_runs = [&](const std::vector<Narrow>& list, std::vector<PairItem>& items, int ba, int bb,
+                            long long entries) {
+            auto blocks = [&](const Narrow& w) { return ba ? (long long)ceil_div(w.na, ba) * ceil_div(w.nb, bb) : 1LL; };
+            double px = 0.0;
+            for (const Narrow& w : list) {
+                const DPair& pr = P->pairs[w.pi];
+                px += (double)blocks(w) * (pr.y1 - pr.y0) * (pr.x1 - pr.x0);
+            }
+            const int run = 256 * (int)std::min(16.0, std::max(1.0, std::ceil(px / GRAM_ITEMS / 256.0)));
+            for (const Narrow& w : list) {
+                const DPair& pr = P->pairs[w.pi];
+                const int bw = pr.x1 - pr.x0, bh = pr.y1 - pr.y0;
+                const int band = std::max(1, (1 << 30) / bw);
+                for (int r0 = 0; r0 < bh; r0 += band) {
+                    const int npx = std::min(band, bh - r0) * bw;
+                    for (int s0 = 0; s0 < npx; s0 += run)
+                        for (int ta = 0; ta < (ba ? w.na : 1); ta += ba ? ba : 1)
+                            for (int tb = 0; tb < (ba ? w.nb : 1); tb += ba ? bb : 1) {
+                                if (ba && pr.g == pr.h && ta > tb + bb - 1) continue;   // below the diagonal
+                                PairItem it{};
+                                it.pair = w.pi;
+                                it.ta = ba ? ta : w.na;
+                                it.tb = tb;
+                                it.s0 = s0;
+                                it.s1 = std::min(npx, s0 + run);
+                                it.row0 = r0;
+                                it.out_off = outoff;
+                                outoff += entries;
+                                items.push_back(it);
+                            }
+                }
+            }
+        };
         P->gitems.clear();
         for (int t = 0; t <= GRAM4_MAX_T; ++t) {
             P->gram_begin[t] = (int)P->gitems.size();
-            for (PairItem it : gram_items[t]) {
-                it.out_off = outoff;
-                outoff += (long long)16 * (t * (t + 1) / 2 + t);     // tile pairs, then J^T W [r 1]
-                P->gitems.push_back(it);
-            }
+            add_runs(self[t], P->gitems, 0, 0, 16LL * (t * (t + 1) / 2 + t));   // tile pairs, then J^T W [r 1]
         }
         P->gram_begin[GRAM4_MAX_T + 1] = (int)P->gitems.size();
+        P->xitems.clear();
+        for (int k = 0; k < N_CROSS; ++k) {
+            P->cross_begin[k] = (int)P->xitems.size();
+            add_runs(cross[k], P->xitems, cross_a(k), cross_b(k), 16LL * cross_a(k) * cross_b(k));
+        }
+        P->cross_begin[N_CROSS] = (int)P->xitems.size();
         P->n_pairpart = outoff;
     }
     P->asrc_col = P->n_pairpart;
@@ -1360,45 +1401,34 @@ static apx_status build_plan(apx_problem* P, const apx_problem_desc* d) {
             const long long e = ent_id(s, a, b);
             for (int m = 0; m < mult; ++m) contrib.emplace_back(e, src);
         };
-        auto add_items_tm = [&](const std::vector<PairItem>& items, int tm) {
-            for (const PairItem& it : items) {
-                const DPair& pr = P->pairs[it.pair];
-                const DGroup& G = P->groups[pr.g];
-                const DGroup& H = P->groups[pr.h];
-                for (int i = 0; i < tm; ++i) {
-                    const int ci = it.ta * tm + i;
-                    if (ci >= G.ncols) break;
-                    for (int j = 0; j < tm; ++j) {
-                        const int cj = it.tb * tm + j;
-                        if (cj >= H.ncols) break;
-                        if (pr.g == pr.h && ci > cj) continue;
-                        const int p = P->cols[G.col_begin + ci].par, q = P->cols[H.col_begin + cj].par;
-                        const bool diag_same_col = (pr.g == pr.h && ci == cj);
-                        add(p, q, it.out_off + (long long)i * tm + j, (p == q && !diag_same_col) ? 2 : 1);
-                    }
-                }
-            }
-        };
-        // keep item order: 64-tiles, 16-tiles, then 4 x 4-block Gram items, each in item order
-        add_items_tm(P->pitems64, 64);
-        add_items_tm(P->pitems16, 16);
-        for (const PairItem& it : P->gitems) {
-            const DPair& pr = P->pairs[it.pair];
+        // the rows x cols block of columns (ci0, cj0) of a pair, row-major with pitch ld at src
+        auto add_block = [&](const DPair& pr, int ci0, int cj0, int rows, int cols, long long src, int ld) {
             const DGroup& G = P->groups[pr.g];
+            const DGroup& H = P->groups[pr.h];
+            for (int i = 0; i < rows && ci0 + i < G.ncols; ++i)
+                for (int j = 0; j < cols && cj0 + j < H.ncols; ++j) {
+                    const int ci = ci0 + i, cj = cj0 + j;
+                    if (pr.g == pr.h && ci > cj) continue;
+                    const int p = P->cols[G.col_begin + ci].par, q = P->cols[H.col_begin + cj].par;
+                    const bool same_col = pr.g == pr.h && ci == cj;
+                    add(p, q, src + (long long)i * ld + j, (p == q && !same_col) ? 2 : 1);
+                }
+        };
+        // keep item order: 64-wide tiles, 4 x 4 blocks of two groups, then of one with itself
+        for (const PairItem& it : P->pitems64) add_block(P->pairs[it.pair], it.ta * 64, it.tb * 64, 64, 64, it.out_off, 64);
+        for (int k = 0; k < N_CROSS; ++k)
+            for (int i = P->cross_begin[k]; i < P->cross_begin[k + 1]; ++i) {
+                const PairItem& it = P->xitems[i];
+                for (int ta = 0; ta < cross_a(k); ++ta)
+                    for (int tb = 0; tb < cross_b(k); ++tb)
+                        add_block(P->pairs[it.pair], 4 * (it.ta + ta), 4 * (it.tb + tb), 4, 4,
+                                  it.out_off + 16LL * (ta * cross_b(k) + tb), 4);
+            }
+        for (const PairItem& it : P->gitems) {
             int q = 0;
             for (int ta = 0; ta < it.ta; ++ta)
                 for (int tb = ta; tb < it.ta; ++tb, ++q)
-                    for (int i = 0; i < 4; ++i) {
-                        const int ci = 4 * ta + i;
-                        if (ci >= G.ncols) break;
-                        for (int j = 0; j < 4; ++j) {
-                            const int cj = 4 * tb + j;
-                            if (cj >= G.ncols) break;
-                            if (ci > cj) continue;
-                            const int pp = P->cols[G.col_begin + ci].par, qq = P->cols[G.col_begin + cj].par;
-                            add(pp, qq, it.out_off + (long long)q * 16 + i * 4 + j, (pp == qq && ci != cj) ? 2 : 1);
-                        }
-                    }
+                    add_block(P->pairs[it.pair], 4 * ta, 4 * tb, 4, 4, it.out_off + 16LL * q, 4);
         }
         for (int k = 0; k < d->n_images; ++k) {
             const DImage& im = P->images[k];
@@ -1416,17 +1446,13 @@ static apx_status build_plan(apx_problem* P, const apx_problem_desc* d) {
             }
             add(im.sky_par, im.sky_par, P->asrc_img + 3LL * k + 2, 1);
         }
-        std::stable_sort(contrib.begin(), contrib.end(),
-                         [](const std::pair<long long, long long>& x, const std::pair<long long, long long>& y) {
-                             return x.first < y.first;
-                         });
+        // sources of each entry in the order they were added (a counting sort)
         P->a_off_csr.assign(n_ent + 1, 0);
         P->a_src.resize(contrib.size());
-        for (size_t i = 0; i < contrib.size(); ++i) {
-            P->a_off_csr[contrib[i].first + 1]++;
-            P->a_src[i] = contrib[i].second;
-        }
+        for (const auto& c : contrib) P->a_off_csr[c.first + 1]++;
         for (long long e = 0; e < n_ent; ++e) P->a_off_csr[e + 1] += P->a_off_csr[e];
+        std::vector<long long> next(P->a_off_csr.begin(), P->a_off_csr.end() - 1);
+        for (const auto& c : contrib) P->a_src[next[c.first]++] = c.second;
         P->a_sub.resize(n_ent);
         P->a_row.resize(n_ent);
         P->a_col.resize(n_ent);
@@ -1532,8 +1558,8 @@ static void layout(apx_problem* P) {
     ws_take<ConvItem>(P, "adj_items", P->adj_items.size());
     ws_take<DPair>(P, "pairs", P->pairs.size());
     ws_take<PairItem>(P, "pitems64", P->pitems64.size());
-    ws_take<PairItem>(P, "pitems16", P->pitems16.size());
     ws_take<PairItem>(P, "gitems", P->gitems.size());
+    ws_take<PairItem>(P, "xitems", P->xitems.size());
     ws_take<int>(P, "img_seg", P->img_seg.size());
     ws_take<int>(P, "img_idx", P->img_idx.size());
     ws_take<int>(P, "col_seg", P->col_seg.size());
@@ -1781,8 +1807,8 @@ apx_status apx_problem_bind_workspace(apx_problem* P, void* dev, uint64_t bytes)
     HIPCHK(upload(P, "adj_items", P->adj_items));
     HIPCHK(upload(P, "pairs", P->pairs));
     HIPCHK(upload(P, "pitems64", P->pitems64));
-    HIPCHK(upload(P, "pitems16", P->pitems16));
     HIPCHK(upload(P, "gitems", P->gitems));
+    HIPCHK(upload(P, "xitems", P->xitems));
     HIPCHK(upload(P, "img_seg", P->img_seg));
     HIPCHK(upload(P, "img_idx", P->img_idx));
     HIPCHK(upload(P, "col_seg", P->col_seg));
@@ -2212,11 +2238,15 @@ static apx_status normal_eq(apx_problem* P, const float* weight, double* A_out, 
     const Plan& p = P->plan;
     hipStream_t st = P->ctx->stream;
     PairLaunch L64{wsp<DPair>(P, "pairs"), wsp<PairItem>(P, "pitems64"), (int)P->pitems64.size(), 64};
-    PairLaunch L16{wsp<DPair>(P, "pairs"), wsp<PairItem>(P, "pitems16"), (int)P->pitems16.size(), 16};
     {
         TimeScope ts(P, APX_TIME_PAIRS);
         HIPCHK(launch_pairs(p, L64, weight, lm, st));
-        HIPCHK(launch_pairs(p, L16, weight, lm, st));
+        for (int k = 0; k < N_CROSS; ++k) {
+            const int b = P->cross_begin[k], n = P->cross_begin[k + 1] - b;
+            if (n <= 0) continue;
+            PairLaunch X4{wsp<DPair>(P, "pairs"), wsp<PairItem>(P, "xitems") + b, n, k};
+            HIPCHK(launch_cross4(p, X4, weight, lm, st));
+        }
         for (int t = 1; t <= GRAM4_MAX_T; ++t) {
             const int b = P->gram_begin[t], n = P->gram_begin[t + 1] - b;
             if (n <= 0) continue;

@@ -157,11 +157,21 @@ struct DPair {
 };
 // one tile pair over stages [s0, s1) of the pair's box (stage s: row y0 + s / nxs, pixels
 // x0 + (s % nxs) KC ... of that row, nxs = ceil((x1 - x0) / KC))
-struct PairItem { int pair, ta, tb, s0, s1, pad; long long out_off; };
-// The J^T W J of a narrow group with itself (at most GRAM4_MAX_T tiles of 4 columns) over one
-// K-slice, by 4 x 4 FP64 MFMA blocks: item.ta = the group's 4-column tiles; the partial is
-// every tile pair (a <= b, row-major over the upper triangle) as a 4 x 4 block.
+struct PairItem { int pair, ta, tb, s0, s1, row0; long long out_off; };
+// Narrow pairs run on 4 x 4 FP64 MFMA blocks over runs of pixels: pixels s0 .. s1 - 1, counted
+// along the rows of the pair's box from its row y0 + row0 on.  A group with itself (at most
+// GRAM4_MAX_T tiles of 4 columns): item.ta = the group's 4-column tiles; the partial is every
+// tile pair (a <= b, row-major over the upper triangle) as a 4 x 4 block.
 constexpr int GRAM4_MAX_T = 9;
+// Two groups of which one has fewer than WIDE_COLS columns (pair.g the one with more tiles), or a
+// group of 37 .. WIDE_COLS - 1 columns with itself: cross_a(k) x cross_b(k) tiles from tile ta of
+// g and tile tb of h; the partial is every tile pair, row-major, as a 4 x 4 block.
+constexpr int WIDE_COLS = 48;
+constexpr int N_CROSS = 9;
+__host__ __device__ constexpr int cross_a(int k) {
+    return k == 0 ? 1 : (k == 1 || k == 4) ? 2 : (k == 2 || k == 5 || k == 7) ? 4 : 8;
+}
+__host__ __device__ constexpr int cross_b(int k) { return k < 4 ? 1 : k < 7 ? 2 : 4; }
 
 // Adaptive integration: the Sersic windows cut into chunks of up to ADAPT_CHUNK pixels
 // (row-major window order); a pixel that needs sub-pixels is appended to the refine list.
@@ -368,14 +378,17 @@ hipError_t launch_conv_fft(const Plan& p, int kind, const ConvLaunch& L, const C
 hipError_t launch_fft_stamps(const Plan& p, int live_only, hipStream_t st);
 
 // k_jtwj.hip
-struct PairLaunch { const DPair* pairs; const PairItem* items; int n_items; int tm; };
-// Workgroups of k_pair<tm> resident per compute unit (0 if the runtime cannot say).
-int pair_blocks_per_cu(int tm);
+struct PairLaunch { const DPair* pairs; const PairItem* items; int n_items; int tm; };   // tm: see each
+// Workgroups of k_pair resident per compute unit (0 if the runtime cannot say).
+int pair_blocks_per_cu();
 hipError_t launch_pairs(const Plan& p, const PairLaunch& L, const float* weight,
                         const apx_lm_state* lm, hipStream_t st);
 // L.items: Gram items with L.tm = the number of 4-column tiles (1..GRAM4_MAX_T)
 hipError_t launch_gram4(const Plan& p, const PairLaunch& L, const float* weight,
                         const apx_lm_state* lm, hipStream_t st);
+// L.items: items of two groups with L.tm = the block shape (0..N_CROSS - 1)
+hipError_t launch_cross4(const Plan& p, const PairLaunch& L, const float* weight,
+                         const apx_lm_state* lm, hipStream_t st);
 struct SegSum {
     const double* src; int stride, comp;
     const int* seg; const int* idx; const double* wts;

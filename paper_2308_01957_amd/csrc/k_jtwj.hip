@@ -3,10 +3,10 @@
 //
 // A_pq = sum_i w_i J_ip J_iq (§2.5, the Gauss-Newton Hessian of Eq. chi2).  Columns of
 // one group share an output box; the product of two groups runs over the intersection
-// of their boxes.  FP32 Jacobian entries are promoted to FP64 (w J_p is exact in FP64),
-// staged in LDS and contracted with v_mfma_f64_16x16x4_f64; every tile of every
-// K-slice is written to its own slot and summed later in a fixed order, so the result
-// does not depend on scheduling.
+// of their boxes.  FP32 Jacobian entries are promoted to FP64 (w J_p is exact in FP64) and
+// contracted on FP64 MFMA: 64 x 64 tiles staged in LDS for two wide groups, 4 x 4 blocks
+// straight from registers for the others.  Every tile of every slice of pixels is written to
+// its own slot and summed later in a fixed order, so the result does not depend on scheduling.
 #include <type_traits>
 
 #include "apx_internal.h"
@@ -15,30 +15,27 @@ namespace apx {
 
 typedef double apx_d4 __attribute__((ext_vector_type(4)));
 
-// TM = 64: the tile's 16 x 16 blocks that hold needed entries (a block is skipped when its
-// rows or its columns lie past the group's last column, or, on a diagonal tile of a group
-// with itself, when it lies wholly below the diagonal) are dealt to the 4 waves in turn,
-// at most 4 blocks (MFMA accumulators) each.
-// TM = 16: 4 waves share one 16 x 16 tile and split each LDS stage along K.
+// Two wide groups, 64 x 64 tiles: the tile's 16 x 16 blocks that hold needed entries (a block
+// is skipped when its rows or its columns lie past the group's last column, or, on a diagonal
+// tile of a group with itself, when it lies wholly below the diagonal) are dealt to the 4 waves
+// in turn, at most 4 blocks (MFMA accumulators) each.
 // Stages of KC = PAIR_KC pixels (one row segment of the box intersection) are software
 // pipelined two deep: the global loads of stages s+1 and s+2 are in flight while the
 // MFMAs consume s.  Each thread stages the same tile columns and pixel offsets in every
 // stage, so its column offsets into J are computed once.
-template <int TM>
 __global__ __launch_bounds__(256) void k_pair(Plan p, const DPair* __restrict__ pairs,
                                               const PairItem* __restrict__ items,
                                               const float* __restrict__ weight,
                                               const apx_lm_state* lm) {
-    constexpr int KC = PAIR_KC;
+    constexpr int KC = PAIR_KC, TM = 64;
     constexpr int PER = TM * KC / 256;              // elements of A (and of B) per thread
-    constexpr int NB = TM >= 64 ? 2 : 1;            // accumulators: NB x NB per wave
+    constexpr int NB = 2;                           // accumulators: NB x NB per wave
     __shared__ double As[TM][KC + 1];
     __shared__ double Bs[TM][KC + 1];
     // the 64-wide tile pairs of one K-slice (up to 21 for a 350-column group) share its rows
     // of J in one L2 when each XCD takes a contiguous range of items (in runs of 8 they read
-    // J 3.3x over from HBM); the narrow ones, of cutouts that may skip, go in runs
-    const PairItem it = items[TM >= 64 ? xcd_item((int)blockIdx.x, (int)gridDim.x)
-                                       : xcd_chunk_item((int)blockIdx.x, (int)gridDim.x)];
+    // J 3.3x over from HBM)
+    const PairItem it = items[xcd_item((int)blockIdx.x, (int)gridDim.x)];
     const DPair pr = pairs[it.pair];
     if (lm && lm[pr.sub].need_jac == 0) return;
     // by value: the fields live in registers for the whole loop (no reloads through the
@@ -52,10 +49,10 @@ __global__ __launch_bounds__(256) void k_pair(Plan p, const DPair* __restrict__ 
     const float* __restrict__ Jh = p.J + Hh.j_off;
     const int a0 = it.ta * TM, b0 = it.tb * TM;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    // TM = 64: this wave's blocks s < nbk, row block (blk >> 4 s) & 3, column block
+    // this wave's blocks s < nbk, row block (blk >> 4 s) & 3, column block
     // (blk >> (4 s + 2)) & 3
     int blk = 0, nbk = 0;
-    if constexpr (TM >= 64) {
+    {
         const int rows = G.ncols - a0, cols = Hh.ncols - b0;
         const bool diag = pr.g == pr.h && it.ta == it.tb;
         int k = 0;
@@ -123,44 +120,35 @@ __global__ __launch_bounds__(256) void k_pair(Plan p, const DPair* __restrict__ 
         }
     };
     auto compute = [&]() {
-        if constexpr (TM >= 64) {
-            // one branch per stage on the wave's block count; inside, the LDS reads of a
-            // K step are all issued before its MFMAs
-            // a wave with fewer than 4 blocks spreads each over 4 / NS accumulators (K steps
-            // dealt in turn), so it still has 4 independent MFMA chains
-            auto run = [&](auto ns) {
-                constexpr int NS = decltype(ns)::value;
-                constexpr int R = NS == 1 ? 4 : NS == 2 ? 2 : 1;
+        // one branch per stage on the wave's block count; inside, the LDS reads of a
+        // K step are all issued before its MFMAs
+        // a wave with fewer than 4 blocks spreads each over 4 / NS accumulators (K steps
+        // dealt in turn), so it still has 4 independent MFMA chains
+        auto run = [&](auto ns) {
+            constexpr int NS = decltype(ns)::value;
+            constexpr int R = NS == 1 ? 4 : NS == 2 ? 2 : 1;
 #pragma unroll
-                for (int kk = 0; kk < KC; kk += 4) {
-                    const int rr = (kk / 4) % R;
-                    double av[NS], bv[NS];
+            for (int kk = 0; kk < KC; kk += 4) {
+                const int rr = (kk / 4) % R;
+                double av[NS], bv[NS];
 #pragma unroll
-                    for (int q = 0; q < NS; ++q) {
-                        av[q] = As[bm(q) * 16 + (lane & 15)][kk + (lane >> 4)];
-                        bv[q] = Bs[bn(q) * 16 + (lane & 15)][kk + (lane >> 4)];
-                    }
-#pragma unroll
-                    for (int q = 0; q < NS; ++q) {
-                        const int c = q * R + rr;
-                        acc[c >> 1][c & 1] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[q], bv[q], acc[c >> 1][c & 1], 0, 0, 0);
-                    }
+                for (int q = 0; q < NS; ++q) {
+                    av[q] = As[bm(q) * 16 + (lane & 15)][kk + (lane >> 4)];
+                    bv[q] = Bs[bn(q) * 16 + (lane & 15)][kk + (lane >> 4)];
                 }
-            };
-            switch (nbk) {
-                case 4: run(std::integral_constant<int, 4>{}); break;
-                case 3: run(std::integral_constant<int, 3>{}); break;
-                case 2: run(std::integral_constant<int, 2>{}); break;
-                case 1: run(std::integral_constant<int, 1>{}); break;
-                default: break;
-            }
-        } else {
 #pragma unroll
-            for (int kk = 8 * wv; kk < 8 * wv + 8; kk += 4) {
-                const double av = As[lane & 15][kk + (lane >> 4)];
-                const double bv = Bs[lane & 15][kk + (lane >> 4)];
-                acc[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, acc[0][0], 0, 0, 0);
+                for (int q = 0; q < NS; ++q) {
+                    const int c = q * R + rr;
+                    acc[c >> 1][c & 1] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[q], bv[q], acc[c >> 1][c & 1], 0, 0, 0);
+                }
             }
+        };
+        switch (nbk) {
+            case 4: run(std::integral_constant<int, 4>{}); break;
+            case 3: run(std::integral_constant<int, 3>{}); break;
+            case 2: run(std::integral_constant<int, 2>{}); break;
+            case 1: run(std::integral_constant<int, 1>{}); break;
+            default: break;
         }
     };
     if (n_stage > 0) fetch(0, ra0, rb0, rw0);
@@ -181,149 +169,258 @@ __global__ __launch_bounds__(256) void k_pair(Plan p, const DPair* __restrict__ 
     }
 
     double* out = p.pair_part + it.out_off;
-    if constexpr (TM >= 64) {
-        // blocks no wave holds are left unwritten: the assembly reads none of their entries.
-        // A block's R accumulators are added in order.
-        auto emit = [&](auto ns) {
-            constexpr int NS = decltype(ns)::value;
-            constexpr int R = NS == 1 ? 4 : NS == 2 ? 2 : 1;
+    // blocks no wave holds are left unwritten: the assembly reads none of their entries.
+    // A block's R accumulators are added in order.
+    auto emit = [&](auto ns) {
+        constexpr int NS = decltype(ns)::value;
+        constexpr int R = NS == 1 ? 4 : NS == 2 ? 2 : 1;
 #pragma unroll
-            for (int q = 0; q < NS; ++q)
+        for (int q = 0; q < NS; ++q)
 #pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    double sum = acc[(q * R) >> 1][(q * R) & 1][v];
+            for (int v = 0; v < 4; ++v) {
+                double sum = acc[(q * R) >> 1][(q * R) & 1][v];
 #pragma unroll
-                    for (int r = 1; r < R; ++r) sum += acc[(q * R + r) >> 1][(q * R + r) & 1][v];
-                    // v_mfma_f64_16x16x4: D[i][j] sits in lane j + 16 (i % 4), register i / 4
-                    const int i = bm(q) * 16 + (lane >> 4) + 4 * v;
-                    const int j = bn(q) * 16 + (lane & 15);
-                    out[i * TM + j] = sum;
-                }
-        };
-        switch (nbk) {
-            case 4: emit(std::integral_constant<int, 4>{}); break;
-            case 3: emit(std::integral_constant<int, 3>{}); break;
-            case 2: emit(std::integral_constant<int, 2>{}); break;
-            case 1: emit(std::integral_constant<int, 1>{}); break;
-            default: break;
-        }
-    } else {
-        // reduce the four K-slices in a fixed order
-        __shared__ double red[4][256];
-#pragma unroll
-        for (int v = 0; v < 4; ++v) red[wv][((lane >> 4) + 4 * v) * 16 + (lane & 15)] = acc[0][0][v];
-        __syncthreads();
-        const int t = threadIdx.x;
-        out[t] = ((red[0][t] + red[1][t]) + red[2][t]) + red[3][t];
+                for (int r = 1; r < R; ++r) sum += acc[(q * R + r) >> 1][(q * R + r) & 1][v];
+                // v_mfma_f64_16x16x4: D[i][j] sits in lane j + 16 (i % 4), register i / 4
+                const int i = bm(q) * 16 + (lane >> 4) + 4 * v;
+                const int j = bn(q) * 16 + (lane & 15);
+                out[i * TM + j] = sum;
+            }
+    };
+    switch (nbk) {
+        case 4: emit(std::integral_constant<int, 4>{}); break;
+        case 3: emit(std::integral_constant<int, 3>{}); break;
+        case 2: emit(std::integral_constant<int, 2>{}); break;
+        case 1: emit(std::integral_constant<int, 1>{}); break;
+        default: break;
     }
 }
 
-// J^T W J of a narrow group (NT tiles of 4 columns, at most 36 columns) with itself over one
-// K-slice, on v_mfma_f64_4x4x4f64: the instruction holds four independent 4 x 4 x 4 products
-// (blocks), block b of lanes 16 k + 4 b + i (A[i][k], B[k][j] at lane 16 k + 4 b + j, D[i][j] at
-// lane 16 i + 4 b + j; measured on gfx950).  Lane L takes pixel L / 4 of a 16-pixel chunk and
-// column L % 4 of a tile, so one instruction contracts 16 pixels of one 4 x 4 tile pair, and
-// the tiles are loaded straight from J into registers (each reused by every pair it is in).
-// Waves take every fourth 32-pixel stage of the slice; at the end each wave folds its four
-// blocks (lanes xor 4, xor 8) and the four waves are added in order.  Against 16 x 16 tiles
-// this pads a group of 7k columns to a multiple of 4, not 16.  Each tile is also contracted
-// with [r 1 0 0] (the pixel's residual, a one), giving the columns' J^T W r and sum w J (the
-// sky row of J^T W J) over the slice in NT more blocks, after the tile pairs.
-template <int NT>
-__global__ __launch_bounds__(256) void k_gram4(Plan p, const DPair* __restrict__ pairs,
-                                               const PairItem* __restrict__ items, int n_items,
-                                               const float* __restrict__ weight, const apx_lm_state* lm) {
-    constexpr int NP = NT * (NT + 1) / 2;
-    constexpr int KC = PAIR_KC;
-    const PairItem it = items[xcd_chunk_item((int)blockIdx.x, n_items)];
-    const DPair pr = pairs[it.pair];
-    if (lm && lm[pr.sub].need_jac == 0) return;
-    const DGroup G = p.groups[pr.g];
-    const long long pix_off = p.images[pr.image].pix_off;
-    const int imW = p.images[pr.image].Wc;
-    const long long gs = (long long)G.oh * G.ow;
-    const float* __restrict__ Jg = p.J + G.j_off;
+// J^T W J of narrow column groups on v_mfma_f64_4x4x4f64: the instruction holds four
+// independent 4 x 4 x 4 products (blocks), block b of lanes 16 k + 4 b + i (A[i][k], B[k][j] at
+// lane 16 k + 4 b + j, D[i][j] at lane 16 i + 4 b + j; measured on gfx950).  Lane L takes pixel
+// L / 4 of a 16-pixel chunk and column L % 4 of a tile of 4 columns, so one instruction
+// contracts 16 pixels of one 4 x 4 tile pair, and the tiles are loaded straight from J into
+// registers (each reused by every pair it is in).  An item is a run of pixels of the pair's
+// box counted along its rows (no padding at row ends; the row of a pixel comes from a
+// multiplication by the reciprocal of the box width, GramDiv).  Its four waves take every
+// fourth run of 16 NS pixels; all loads of a wave's next run are issued before the MFMAs of
+// the current one.  At the end each wave folds its four blocks (lanes xor 4, xor 8) and the
+// four waves are added in order.
+// What bounds it: latency of the loads while there are few waves, which is why the plan cuts
+// the boxes into enough items to fill the chip (add_runs in the plan), then for wide groups
+// the MFMAs (35 columns: 54 per 16 pixels, 98 us of MFMA issue in the 163 us that 3.9 M pixels
+// take) and for narrow ones the loads (8 columns against 8, 28 M pixels: 273 us).
+struct GramDiv {                                    // e / bw for 0 <= e < 2^31, bw >= 1
+    unsigned m, bw;                                 // m = floor((2^32 - 1) / bw)
+    __device__ __forceinline__ explicit GramDiv(int w) : m(0xffffffffu / (unsigned)w), bw((unsigned)w) {}
+    __device__ __forceinline__ void operator()(int e, int& row, int& x) const {
+        unsigned q = __umulhi((unsigned)e, m);       // the quotient or one less
+        unsigned r = (unsigned)e - q * bw;
+        if (r >= bw) { r -= bw; ++q; }
+        row = (int)q;
+        x = (int)r;
+    }
+};
+
+// The per-wave sums of NQ blocks: folded over the four blocks of the instruction, then over the
+// four waves in order, into out[NQ * 16] (block q: entry (i, j) at 16 q + 4 i + j).
+template <int NQ>
+__device__ __forceinline__ void gram_emit(const double (&acc)[NQ], double* __restrict__ out) {
+    __shared__ double red[4][NQ * 16];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int col = lane & 3, pxl = lane >> 2;       // column within a tile, pixel within a chunk
-    const long long lastA = (long long)(G.ncols - 1) * gs - G.ox0;
-    long long coff[NT];
-    bool cval[NT];
 #pragma unroll
-    for (int t = 0; t < NT; ++t) {
-        const int ca = 4 * t + col;
-        cval[t] = ca < G.ncols;
-        coff[t] = cval[t] ? (long long)ca * gs - G.ox0 : lastA;
-    }
-    double acc[NP], acx[NT];
-#pragma unroll
-    for (int q = 0; q < NP; ++q) acc[q] = 0.0;
-#pragma unroll
-    for (int t = 0; t < NT; ++t) acx[t] = 0.0;
-    const int nxs = (pr.x1 - pr.x0 + KC - 1) / KC;
-    // the wave's 16-pixel chunks, in order: chunk h of stages it.s0 + wv, + 4, + 8, ...; the
-    // loads of the next chunk are issued before the MFMAs of the current one
-    constexpr int NH = KC / 16;
-    auto fetch = [&](int st, int h, float (&bv)[NT], float& wf, float& rf, bool& in) {
-        const int row = pr.y0 + st / nxs;
-        const int x = pr.x0 + (st - (st / nxs) * nxs) * KC + 16 * h + pxl;
-        in = x < pr.x1;
-        const int xc = in ? x : pr.x1 - 1;
-        const long long grow = (long long)(row - G.oy0) * G.ow + xc;
-        const long long pix = pix_off + (long long)row * imW + xc;
-        wf = weight[pix];
-        rf = p.rbuf[pix];
-#pragma unroll
-        for (int t = 0; t < NT; ++t) bv[t] = Jg[coff[t] + grow];
-    };
-    float bc[NT], wc = 0.f, rc = 0.f;
-    bool inc = false;
-    int st = it.s0 + wv, h = 0;
-    if (st < it.s1) fetch(st, 0, bc, wc, rc, inc);
-    while (st < it.s1) {
-        int st2 = st, h2 = h + 1;
-        if (h2 == NH) {
-            h2 = 0;
-            st2 += 4;
-        }
-        float bn[NT], wn = 0.f, rn = 0.f;
-        bool inn = false;
-        if (st2 < it.s1) fetch(st2, h2, bn, wn, rn, inn);
-        const double w = inc ? (double)wc : 0.0;
-        const double vx = col == 0 ? (double)rc : (col == 1 ? 1.0 : 0.0);     // [r 1 0 0]
-        double b[NT];
-#pragma unroll
-        for (int t = 0; t < NT; ++t) b[t] = (inc && cval[t]) ? (double)bc[t] : 0.0;
-        int q = 0;
-#pragma unroll
-        for (int ta = 0; ta < NT; ++ta) {
-            const double a = b[ta] * w;
-#pragma unroll
-            for (int tb = ta; tb < NT; ++tb, ++q)
-                acc[q] = __builtin_amdgcn_mfma_f64_4x4x4f64(a, b[tb], acc[q], 0, 0, 0);
-            acx[ta] = __builtin_amdgcn_mfma_f64_4x4x4f64(a, vx, acx[ta], 0, 0, 0);
-        }
-#pragma unroll
-        for (int t = 0; t < NT; ++t) bc[t] = bn[t];
-        wc = wn;
-        rc = rn;
-        inc = inn;
-        st = st2;
-        h = h2;
-    }
-    // fold the four blocks of each wave, then the four waves in order
-    __shared__ double red[4][(NP + NT) * 16];
-#pragma unroll
-    for (int q = 0; q < NP + NT; ++q) {
-        double v = q < NP ? acc[q] : acx[q - NP];
+    for (int q = 0; q < NQ; ++q) {
+        double v = acc[q];
         v += __shfl_xor(v, 4, 64);
         v += __shfl_xor(v, 8, 64);
         // lanes with block 0 (lane % 16 < 4) hold D[i][j] at lane 16 i + j
         if ((lane & 12) == 0) red[wv][q * 16 + (lane >> 4) * 4 + (lane & 3)] = v;
     }
     __syncthreads();
-    double* out = p.pair_part + it.out_off;
-    for (int e = (int)threadIdx.x; e < (NP + NT) * 16; e += 256)
+    for (int e = (int)threadIdx.x; e < NQ * 16; e += 256)
         out[e] = ((red[0][e] + red[1][e]) + red[2][e]) + red[3][e];
+}
+
+// A group (NT tiles of 4 columns, at most 36 columns) with itself: every tile pair a <= b, and
+// each tile against [r 1 0 0] (the pixel's residual, a one), which gives the columns' J^T W r
+// and sum w J (the sky row of J^T W J) over the item in NT more blocks after the tile pairs.
+template <int NT, int NS>
+__global__ __launch_bounds__(256) void k_gram4(Plan p, const DPair* __restrict__ pairs,
+                                               const PairItem* __restrict__ items, int n_items,
+                                               const float* __restrict__ weight, const apx_lm_state* lm) {
+    constexpr int NP = NT * (NT + 1) / 2;
+    const PairItem it = items[xcd_chunk_item((int)blockIdx.x, n_items)];
+    const DPair pr = pairs[it.pair];
+    if (lm && lm[pr.sub].need_jac == 0) return;
+    const DGroup G = p.groups[pr.g];
+    const int imW = p.images[pr.image].Wc;
+    const long long gs = (long long)G.oh * G.ow;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int col = lane & 3, pxl = lane >> 2;       // column within a tile, pixel within a chunk
+    const int yb = pr.y0 + it.row0;                  // first row of the item's band
+    const float* __restrict__ Jg = p.J + G.j_off + (long long)(yb - G.oy0) * G.ow + (pr.x0 - G.ox0);
+    const long long pix0 = p.images[pr.image].pix_off + (long long)yb * imW + pr.x0;
+    const float* __restrict__ wb = weight + pix0;
+    const float* __restrict__ rb = p.rbuf + pix0;
+    const GramDiv div(pr.x1 - pr.x0);
+    const float* cb[NT];                             // this lane's column of each tile
+    bool cval[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        const int ca = 4 * t + col;
+        cval[t] = ca < G.ncols;
+        cb[t] = Jg + (long long)(cval[t] ? ca : G.ncols - 1) * gs;
+    }
+    double acc[NP + NT];
+#pragma unroll
+    for (int q = 0; q < NP + NT; ++q) acc[q] = 0.0;
+    auto fetch = [&](int e0, float (&bv)[NS][NT], float (&wf)[NS], float (&rf)[NS]) {
+#pragma unroll
+        for (int h = 0; h < NS; ++h) {
+            const int e = e0 + 16 * h + pxl;
+            const bool in = e < it.s1;
+            int row, x;
+            div(in ? e : it.s1 - 1, row, x);
+            const long long pix = (long long)row * imW + x, grow = (long long)row * G.ow + x;
+            const float wl = wb[pix];
+            rf[h] = rb[pix];
+#pragma unroll
+            for (int t = 0; t < NT; ++t) bv[h][t] = cb[t][grow];
+            wf[h] = in ? wl : 0.f;
+        }
+    };
+    float bc[NS][NT], wc[NS], rc[NS];
+    int e0 = it.s0 + 16 * NS * wv;
+    if (e0 < it.s1) fetch(e0, bc, wc, rc);
+    while (e0 < it.s1) {
+        const int e1 = e0 + 64 * NS;
+        float bn[NS][NT], wn[NS], rn[NS];
+        const bool more = e1 < it.s1;
+        if (more) fetch(e1, bn, wn, rn);
+#pragma unroll
+        for (int h = 0; h < NS; ++h) {
+            const bool in = e0 + 16 * h + pxl < it.s1;
+            const double w = (double)wc[h];
+            const double vx = col == 0 ? (double)rc[h] : (col == 1 ? 1.0 : 0.0);     // [r 1 0 0]
+            double b[NT];
+#pragma unroll
+            for (int t = 0; t < NT; ++t) b[t] = (in && cval[t]) ? (double)bc[h][t] : 0.0;
+            int q = 0;
+#pragma unroll
+            for (int ta = 0; ta < NT; ++ta) {
+                const double a = b[ta] * w;
+#pragma unroll
+                for (int tb = ta; tb < NT; ++tb, ++q)
+                    acc[q] = __builtin_amdgcn_mfma_f64_4x4x4f64(a, b[tb], acc[q], 0, 0, 0);
+                acc[NP + ta] = __builtin_amdgcn_mfma_f64_4x4x4f64(a, vx, acc[NP + ta], 0, 0, 0);
+            }
+        }
+        if (more) {
+#pragma unroll
+            for (int h = 0; h < NS; ++h) {
+#pragma unroll
+                for (int t = 0; t < NT; ++t) bc[h][t] = bn[h][t];
+                wc[h] = wn[h];
+                rc[h] = rn[h];
+            }
+        }
+        e0 = e1;
+    }
+    gram_emit<NP + NT>(acc, p.pair_part + it.out_off);
+}
+
+// Two groups of which at least one is narrow: BA tiles of 4 columns of pr.g against BB tiles
+// of pr.h over the item's pixels (tile columns past a group's last read it and count as zero).
+// (On 16 x 16 MFMA tiles two 7-column galaxies filled 49 of 256 entries: the overlaps of 60
+// galaxies on four 700 x 700 images took 562 us there, 273 us here.)
+template <int BA, int BB>
+__global__ __launch_bounds__(256) void k_cross4(Plan p, const DPair* __restrict__ pairs,
+                                                const PairItem* __restrict__ items, int n_items,
+                                                const float* __restrict__ weight, const apx_lm_state* lm) {
+    constexpr int NS = BA + BB <= 4 ? 4 : 2;
+    const PairItem it = items[xcd_chunk_item((int)blockIdx.x, n_items)];
+    const DPair pr = pairs[it.pair];
+    if (lm && lm[pr.sub].need_jac == 0) return;
+    const DGroup G = p.groups[pr.g];
+    const DGroup Hh = p.groups[pr.h];
+    const int imW = p.images[pr.image].Wc;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int col = lane & 3, pxl = lane >> 2;
+    const int yb = pr.y0 + it.row0;
+    const float* __restrict__ Jg = p.J + G.j_off + (long long)(yb - G.oy0) * G.ow + (pr.x0 - G.ox0);
+    const float* __restrict__ Jh = p.J + Hh.j_off + (long long)(yb - Hh.oy0) * Hh.ow + (pr.x0 - Hh.ox0);
+    const float* __restrict__ wb = weight + p.images[pr.image].pix_off + (long long)yb * imW + pr.x0;
+    const GramDiv div(pr.x1 - pr.x0);
+    const float *ca[BA], *cb[BB];
+    bool va[BA], vb[BB];
+#pragma unroll
+    for (int t = 0; t < BA; ++t) {
+        const int c = 4 * (it.ta + t) + col;
+        va[t] = c < G.ncols;
+        ca[t] = Jg + (long long)(va[t] ? c : G.ncols - 1) * G.oh * G.ow;
+    }
+#pragma unroll
+    for (int t = 0; t < BB; ++t) {
+        const int c = 4 * (it.tb + t) + col;
+        vb[t] = c < Hh.ncols;
+        cb[t] = Jh + (long long)(vb[t] ? c : Hh.ncols - 1) * Hh.oh * Hh.ow;
+    }
+    double acc[BA * BB];
+#pragma unroll
+    for (int q = 0; q < BA * BB; ++q) acc[q] = 0.0;
+    auto fetch = [&](int e0, float (&av)[NS][BA], float (&bv)[NS][BB], float (&wf)[NS]) {
+#pragma unroll
+        for (int h = 0; h < NS; ++h) {
+            const int e = e0 + 16 * h + pxl;
+            const bool in = e < it.s1;
+            int row, x;
+            div(in ? e : it.s1 - 1, row, x);
+            const long long grow = (long long)row * G.ow + x, hrow = (long long)row * Hh.ow + x;
+            const float wl = wb[(long long)row * imW + x];
+#pragma unroll
+            for (int t = 0; t < BA; ++t) av[h][t] = ca[t][grow];
+#pragma unroll
+            for (int t = 0; t < BB; ++t) bv[h][t] = cb[t][hrow];
+            wf[h] = in ? wl : 0.f;
+        }
+    };
+    float ac[NS][BA], bc[NS][BB], wc[NS];
+    int e0 = it.s0 + 16 * NS * wv;
+    if (e0 < it.s1) fetch(e0, ac, bc, wc);
+    while (e0 < it.s1) {
+        const int e1 = e0 + 64 * NS;
+        float an[NS][BA], bn[NS][BB], wn[NS];
+        const bool more = e1 < it.s1;
+        if (more) fetch(e1, an, bn, wn);
+#pragma unroll
+        for (int h = 0; h < NS; ++h) {
+            const bool in = e0 + 16 * h + pxl < it.s1;
+            const double w = (double)wc[h];
+            double a[BA], b[BB];
+#pragma unroll
+            for (int t = 0; t < BA; ++t) a[t] = (in && va[t]) ? (double)ac[h][t] * w : 0.0;
+#pragma unroll
+            for (int t = 0; t < BB; ++t) b[t] = (in && vb[t]) ? (double)bc[h][t] : 0.0;
+#pragma unroll
+            for (int ta = 0; ta < BA; ++ta)
+#pragma unroll
+                for (int tb = 0; tb < BB; ++tb)
+                    acc[ta * BB + tb] = __builtin_amdgcn_mfma_f64_4x4x4f64(a[ta], b[tb], acc[ta * BB + tb], 0, 0, 0);
+        }
+        if (more) {
+#pragma unroll
+            for (int h = 0; h < NS; ++h) {
+#pragma unroll
+                for (int t = 0; t < BA; ++t) ac[h][t] = an[h][t];
+#pragma unroll
+                for (int t = 0; t < BB; ++t) bc[h][t] = bn[h][t];
+                wc[h] = wn[h];
+            }
+        }
+        e0 = e1;
+    }
+    gram_emit<BA * BB>(acc, p.pair_part + it.out_off);
 }
 
 hipError_t launch_gram4(const Plan& p, const PairLaunch& L, const float* weight,
@@ -333,7 +430,7 @@ hipError_t launch_gram4(const Plan& p, const PairLaunch& L, const float* weight,
     switch (L.tm) {
 #define APX_G4(T)                                                                                       \
     case T:                                                                                             \
-        hipLaunchKernelGGL(k_gram4<T>, grid, block, 0, st, p, L.pairs, L.items, L.n_items, weight, lm); \
+        hipLaunchKernelGGL((k_gram4<T, (T) <= 5 ? 4 : 2>), grid, block, 0, st, p, L.pairs, L.items, L.n_items, weight, lm); \
         break;
         APX_G4(1) APX_G4(2) APX_G4(3) APX_G4(4) APX_G4(5) APX_G4(6) APX_G4(7) APX_G4(8) APX_G4(9)
 #undef APX_G4
@@ -343,11 +440,28 @@ hipError_t launch_gram4(const Plan& p, const PairLaunch& L, const float* weight,
     return hipGetLastError();
 }
 
-int pair_blocks_per_cu(int tm) {
+hipError_t launch_cross4(const Plan& p, const PairLaunch& L, const float* weight,
+                         const apx_lm_state* lm, hipStream_t st) {
+    if (L.n_items <= 0) return hipSuccess;
+    dim3 grid(L.n_items), block(256);
+    static_assert(N_CROSS == 9, "one case per block shape");
+    switch (L.tm) {
+#define APX_X4(K)                                                                                              \
+    case K:                                                                                                    \
+        hipLaunchKernelGGL((k_cross4<cross_a(K), cross_b(K)>), grid, block, 0, st, p, L.pairs, L.items, L.n_items, \
+                           weight, lm);                                                                        \
+        break;
+        APX_X4(0) APX_X4(1) APX_X4(2) APX_X4(3) APX_X4(4) APX_X4(5) APX_X4(6) APX_X4(7) APX_X4(8)
+#undef APX_X4
+        default:
+            return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+int pair_blocks_per_cu() {
     int nb = 0;
-    const hipError_t e = tm == 64 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_pair<64>, 256, 0)
-                                  : hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_pair<16>, 256, 0);
-    if (e != hipSuccess) {
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_pair, 256, 0) != hipSuccess) {
         (void)hipGetLastError();
         return 0;
     }
@@ -357,10 +471,7 @@ int pair_blocks_per_cu(int tm) {
 hipError_t launch_pairs(const Plan& p, const PairLaunch& L, const float* weight,
                         const apx_lm_state* lm, hipStream_t st) {
     if (L.n_items <= 0) return hipSuccess;
-    if (L.tm == 64)
-        hipLaunchKernelGGL(k_pair<64>, dim3(L.n_items), dim3(256), 0, st, p, L.pairs, L.items, weight, lm);
-    else
-        hipLaunchKernelGGL(k_pair<16>, dim3(L.n_items), dim3(256), 0, st, p, L.pairs, L.items, weight, lm);
+    hipLaunchKernelGGL(k_pair, dim3(L.n_items), dim3(256), 0, st, p, L.pairs, L.items, weight, lm);
     return hipGetLastError();
 }
 
@@ -396,13 +507,26 @@ hipError_t launch_segsum(const SegSum& a, hipStream_t st) {
 
 // J^T W J assembly: every upper entry (sub, a <= b) sums its sources in list order and
 // is written to both (a, b) and (b, a) of its sub-problem's row-major block.
+constexpr int ASM_B = 8;
 __global__ void k_assemble_A(AsmA a) {
     const long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= a.n_ent) return;
     const int s = a.ent_sub[e];
     if (a.lm && a.lm[s].need_jac == 0) return;
+    // the sources' loads in batches of ASM_B, added in list order (one at a time, an entry with
+    // 36 sources took 36 round trips to memory)
     double acc = 0.0;
-    for (long long k = a.ent_off[e]; k < a.ent_off[e + 1]; ++k) acc += a.src[a.ent_src[k]];
+    const long long k1 = a.ent_off[e + 1];
+    for (long long k = a.ent_off[e]; k < k1; k += ASM_B) {
+        long long idx[ASM_B];
+        double v[ASM_B];
+#pragma unroll
+        for (int q = 0; q < ASM_B; ++q) idx[q] = a.ent_src[k + q < k1 ? k + q : k1 - 1];
+#pragma unroll
+        for (int q = 0; q < ASM_B; ++q) v[q] = a.src[idx[q]];
+#pragma unroll
+        for (int q = 0; q < ASM_B; ++q) acc += k + q < k1 ? v[q] : 0.0;
+    }
     const DSub sb = a.subs[s];
     const int r = a.ent_row[e], c = a.ent_col[e];
     a.out[sb.a_off + (long long)r * sb.n + c] = acc;
@@ -411,7 +535,7 @@ __global__ void k_assemble_A(AsmA a) {
 
 hipError_t launch_assemble_A(const AsmA& a, hipStream_t st) {
     if (a.n_ent <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_assemble_A, dim3((unsigned)((a.n_ent + 255) / 256)), dim3(256), 0, st, a);
+    hipLaunchKernelGGL(k_assemble_A, dim3((unsigned)((a.n_ent + 63) / 64)), dim3(64), 0, st, a);
     return hipGetLastError();
 }
 
