@@ -8,6 +8,7 @@
 #include <cstring>
 #include <map>
 #include <mutex>
+#include <set>
 #include <string>
 #include <tuple>
 #include <vector>
@@ -63,7 +64,7 @@ void scratch_lookup(int device) {
 
 namespace {
 
-struct PRange { int P, shape, begin, count, pair_begin, pair_count; };
+struct PRange { int P, shape, begin, count, pair_begin, pair_count, fine; };
 
 template <class T>
 struct DevArr {
@@ -265,6 +266,7 @@ static bool tune_kernel(apx_ctx* C, int key, int P, std::array<double, 4>& us) {
     const size_t o_img = take(sizeof(DImage)), o_job = take(sizeof(ConvJob));
     const size_t o_items = take(sizeof(ConvItem) * max_items), o_psf = take(sizeof(float) * TUNE_MAXP * TUNE_MAXP);
     const size_t o_psf64 = take(sizeof(double) * TUNE_MAXP * TUNE_MAXP);
+    const size_t o_sym = take(sizeof(int));
     const size_t o_sky = take(sizeof(double)), o_r = take(sizeof(float) * npx), o_w = take(sizeof(float) * npx);
     const size_t o_d = take(sizeof(float) * npx), o_in = take(sizeof(float) * next * TUNE_CH);
     const size_t o_in64 = take(sizeof(double) * next), o_out = take(sizeof(float) * (size_t)TUNE_CH * next);
@@ -289,6 +291,9 @@ static bool tune_kernel(apx_ctx* C, int key, int P, std::array<double, 4>& us) {
     p.psf_flip = (float*)(base + o_psf);
     p.psf_live = (float*)(base + o_psf);
     p.psf64 = (double*)(base + o_psf64);
+    p.psf_sym = (int*)(base + o_sym);
+    const int sym = 1;                              // the zero stamp is symmetric
+    if (hipMemcpy(base + o_sym, &sym, sizeof sym, hipMemcpyHostToDevice) != hipSuccess) return false;
     p.sky_val = (double*)(base + o_sky);
     p.rbuf = (float*)(base + o_r);
     ConvIO io{};
@@ -430,6 +435,9 @@ static int choose_group_shape(apx_ctx* C, int key, int P, const std::vector<int>
     }
     return best;
 }
+
+// Convolution launches of fewer tiles than this (half the compute units) go fine.
+static constexpr int FINE_TILES = 128;
 
 // Regularised lower incomplete gamma P(a, x) by its power series (x < a + 1 here).
 static double gammainc_lower_series_host(double a, double x) {
@@ -1079,6 +1087,7 @@ static apx_status build_plan(apx_problem* P, const apx_problem_desc* d) {
             jobs[j].shape = fft ? SHAPE_FFT : sep ? SHAPE_SEP : 0;
         }
         // the direct jobs of each PSF size: one shape for the group (choose_group_shape)
+        std::set<int> fineP;
         {
             std::map<int, std::vector<int>> byP;
             for (size_t j = 0; j < jobs.size(); ++j)
@@ -1090,7 +1099,21 @@ static apx_status build_plan(apx_problem* P, const apx_problem_desc* d) {
                     w.push_back(jobs[j].out_w);
                     nc.push_back(nch[j]);
                 }
-                const int s = choose_group_shape(C, key, kv.first, h, w, nc);
+                int s = choose_group_shape(C, key, kv.first, h, w, nc);
+                // Too few tiles to give half the compute units one: 16 x 32 tiles with
+                // CV_R_FINE outputs per lane (a 128 x 128 image at P = 25: 8 workgroups and
+                // 18 us, against 32 and 12).  Not under a fixed policy, nor with sub-pixel
+                // grids, whose epilogue needs all CV_R outputs in a lane.
+                long long tiles = 0;
+                bool plain = C->tiles < APX_TILES_FIXED;
+                for (size_t q = 0; q < h.size(); ++q) {
+                    tiles += (long long)nc[q] * ceil_div(h[q], tile_th(s)) * ceil_div(w[q], tile_tw(s));
+                    plain = plain && P->images[jobs[kv.second[q]].image].up == 1;
+                }
+                if (plain && tiles < FINE_TILES) {
+                    s = FINE_SHAPE;
+                    fineP.insert(kv.first);
+                }
                 for (int j : kv.second) jobs[j].shape = s;
             }
         }
@@ -1119,7 +1142,8 @@ static apx_status build_plan(apx_problem* P, const apx_problem_desc* d) {
             if (same)
                 ranges.back().count += cnt;
             else
-                ranges.push_back(PRange{jb.shape == SHAPE_FFT ? 0 : jobP[j], jb.shape, b, cnt, 0, 0});
+                ranges.push_back(PRange{jb.shape == SHAPE_FFT ? 0 : jobP[j], jb.shape, b, cnt, 0, 0,
+                                        jb.shape == FINE_SHAPE && fineP.count(jobP[j]) ? 1 : 0});
         }
         if (!pairs) return;
         for (PRange& r : ranges) {
@@ -1614,6 +1638,7 @@ static void layout(apx_problem* P) {
     ws_take<double>(P, "jcol_part", 2 * (P->jcol_items.size() + P->psf_items.size()));
     ws_take<float>(P, "psf_live", P->n_live);
     ws_take<double>(P, "psf64", P->n_psf);
+    ws_take<int>(P, "psf_sym", P->n_images);
     ws_take<float2>(P, "fft_spec", P->n_fft_spec);
     ws_take<float>(P, "fft_tw", P->fft_tw.size());
     ws_take<int4>(P, "fwd_pairs", P->fwd_pairs.size());
@@ -1894,6 +1919,7 @@ apx_status apx_problem_bind_workspace(apx_problem* P, void* dev, uint64_t bytes)
     p.jcol_part = wsp<double>(P, "jcol_part");
     p.psf_live = wsp<float>(P, "psf_live");
     p.psf64 = wsp<double>(P, "psf64");
+    p.psf_sym = wsp<int>(P, "psf_sym");
     p.fft_spec = wsp<float2>(P, "fft_spec");
     p.fft_tw = reinterpret_cast<const float2*>(wsp<float>(P, "fft_tw"));
     p.grad_part = wsp<double>(P, "grad_part");
@@ -2065,7 +2091,7 @@ static apx_status run_conv(apx_problem* P, int kind, const ConvIO& io) {
     for (const PRange& r : *ranges) {
         TimeScope ts(P, r.shape == SHAPE_SEP ? APX_TIME_CONV_SEP : r.shape == SHAPE_FFT ? APX_TIME_CONV_FFT : klass);
         ConvLaunch L{wsp<ConvJob>(P, jn), wsp<ConvItem>(P, inn), r.begin, r.count, r.P, r.shape, nullptr,
-                     r.pair_begin, r.pair_count};
+                     r.pair_begin, r.pair_count, r.fine};
         if (r.shape == SHAPE_SEP) {
             hipError_t e = launch_conv_sep(p, L, io, st);
             if (e != hipSuccess) return fail(P->ctx, APX_E_HIP, std::string("separable conv launch: ") + hipGetErrorString(e));

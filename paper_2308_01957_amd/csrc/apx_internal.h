@@ -12,12 +12,14 @@ namespace apx {
 // Tile shapes --------------------------------------------------------------------
 constexpr int RT_Y = 8, RT_X = 32;            // render / derivative / gradient tiles (256 px)
 // Convolution output tiles a workgroup can own (rows x cols).  Every lane computes CV_R
-// consecutive outputs of one row, so shape s runs tile_th(s) * tile_tw(s) / CV_R threads.
+// consecutive outputs of one row, so shape s runs tile_th(s) * tile_tw(s) / CV_R threads
+// (CV_R_FINE outputs and more threads in a fine launch).
 // The tile shape of each convolution job is chosen per job (apx_ctx_set_tiles).
 constexpr int N_TILE_SHAPES = 4;
 __host__ __device__ constexpr int tile_th(int s) { return (s & 1) ? 16 : 32; }
 __host__ __device__ constexpr int tile_tw(int s) { return s < 2 ? 64 : 32; }
 constexpr int CV_R = 8;                       // consecutive outputs per lane (register window)
+constexpr int FINE_SHAPE = 3, CV_R_FINE = 2;  // launches of few tiles: this shape, this many outputs per lane
 constexpr int PAIR_KC = 32;                   // pixels per LDS stage of the J^T W J kernel
 constexpr int CHOL_NB = 64;                   // block size of the blocked Cholesky
 constexpr int SMALL_N = 64;                   // sub-problems up to this size: one-wave solver
@@ -227,6 +229,7 @@ struct Plan {
     float* psf_flip;          // flipped stamps (adjoint)
     float* psf_live;          // live-PSF stamps and their derivatives (3 P^2 per live image)
     double* psf64;            // every stamp in FP64 (objective convolution)
+    int* psf_sym;             // [n_images] 1: the stamp is the same upside down (rows U, P - 1 - U equal)
     float2* fft_spec;         // FFT mode: stamp spectra (K, flipped K) per image
     const float2* fft_tw;     // [FFT_T]: exp(-2 pi i m / FFT_T)
 
@@ -354,6 +357,7 @@ struct ConvLaunch {
     int item_begin, item_count, P, shape;
     const int4* pairs;        // FFT mode: items sharing one transform (second -1 = none), their sub-problem
     int pair_begin, pair_count;
+    int fine;                 // shape FINE_SHAPE with CV_R_FINE outputs per lane (images of up = 1 only)
 };
 struct ConvIO {
     const float* in;          // input buffer base (FWD, JCOL)

@@ -2,12 +2,16 @@
 //
 // out(y, x) = sum_{U,V} K[U][V] * in(y - U + c, x - V + c), in = 0 outside its rectangle.
 //
-// One workgroup owns a TH x TW output tile (TH * TW / CV_R threads).  The input tile with its
-// (P-1) halo is staged once into LDS; each lane then produces CV_R consecutive outputs
-// of one row: per PSF row it loads a CV_R + P - 1 register window from LDS (ds_read_b128)
-// and runs P x CV_R FMAs whose PSF operand is wave-uniform (scalar loads, then copied to
-// a VGPR), so the VALU does useful FMAs at ~CV_R*P per (CV_R+P-1)/4 LDS instructions.  Each PSF row is summed
+// One workgroup owns a TH x TW output tile (TH * TW / R threads).  The input tile with its
+// (P-1) halo is staged once into LDS; each lane then produces R consecutive outputs
+// of one row: per PSF row it loads an R + P - 1 register window from LDS (ds_read_b128)
+// and runs P x R FMAs whose PSF operand is wave-uniform (scalar loads, then copied to
+// a VGPR), so the VALU does useful FMAs at ~R*P per (R+P-1)/4 LDS instructions.  Each PSF row is summed
 // into a fresh partial before being added to the accumulator (error ~2P ulp, not P^2).
+// R = CV_R = 8 where there are tiles enough to fill the chip; launches of few tiles take
+// R = CV_R_FINE = 2 on 16 x 32 tiles (four times the lanes per output: one 128 x 128 image at
+// P = 25 takes 11.8 us instead of 18 in FP32 and in FP64, where a full chip runs the R = 2
+// kernel at 57 instead of 80 TFLOP/s).  The arithmetic of an output does not depend on R.
 //
 // On an image whose PSF has a higher resolution than its pixels the grid is of sub-pixels,
 // and the model and Jacobian epilogues first sum each pixel's sub-pixel outputs.
@@ -27,11 +31,11 @@
 
 namespace apx {
 
-// Sum of each run of UU consecutive entries into the first CV_R / UU entries.
-template <int UU, typename T>
-__device__ __forceinline__ void bin_lane(T (&acc)[CV_R]) {
+// Sum of each run of UU consecutive entries into the first R / UU entries.
+template <int UU, typename T, int R>
+__device__ __forceinline__ void bin_lane(T (&acc)[R]) {
 #pragma unroll
-    for (int q = 0; q < CV_R / UU; ++q) {
+    for (int q = 0; q < R / UU; ++q) {
         T v = acc[q * UU];
 #pragma unroll
         for (int i = 1; i < UU; ++i) v += acc[q * UU + i];
@@ -44,15 +48,98 @@ __device__ __forceinline__ double conv_wave_sum(double v) {
     return v;
 }
 
-// T is the arithmetic type of the staged input and the accumulators: float for the
-// Jacobian and adjoint passes, double for the FP64 objective.
-template <int P, int KIND, typename T, int TH, int TW>
-__global__ __launch_bounds__(TH * TW / CV_R) void k_conv(Plan p, const ConvJob* __restrict__ jobs,
-                                                         const ConvItem* __restrict__ items, int item_begin,
-                                                         ConvIO io) {
+// Sub-pixel grids (up = U > 1, a power of two <= CV_R): sum each pixel's U x U outputs, U
+// consecutive ones in a lane, then across the lanes of rows ty ^ 1 .. ty ^ (U - 1) (one wave
+// holds 64 / LPR >= 8 rows; tiles and output boxes are whole pixels).  Lane rows with
+// ty % U == 0 then hold R / U pixel values each.  Launches with R < CV_R hold no such image.
+template <int LPR, typename T, int R>
+__device__ __forceinline__ void bin_pixels(T (&acc)[R], int up) {
+    if constexpr (R == CV_R) {
+        if (up == 1) return;
+        if (up == 2) bin_lane<2>(acc);
+        else if (up == 4) bin_lane<4>(acc);
+        else bin_lane<8>(acc);
+        for (int k = 1; k < up; k <<= 1)
+#pragma unroll
+            for (int r = 0; r < R; ++r) acc[r] += __shfl_xor(acc[r], k * LPR, 64);
+    }
+}
+
+// Epilogue of the model convolution: model + sky, optional model store, FP32 residual store,
+// FP64 partials of sum w r^2, sum w r, sum w per item.
+template <typename T, int R, int NW>
+__device__ __forceinline__ void fwd_epilogue(const Plan& p, const ConvJob& jb, const DImage& im, const ConvIO& io,
+                                             int item_idx, const T (&acc)[R], int y, int xb, bool yok,
+                                             double (*red)[3]) {
+    const int up = im.up, nq = R / up;               // values per lane, render-grid step between them
+    const int xend = jb.out_x0 + jb.out_w;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const T sky = (T)p.sky_val[jb.image];
+    double c2 = 0.0, swr = 0.0, sw = 0.0;
+    if (yok) {
+        const long long rowpix = im.pix_off + (long long)(y / up) * im.Wc;
+        // the row's weights and data first: their loads overlap instead of following
+        // one another
+        float wv[R], dv[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int x = xb + r * up;
+            wv[r] = dv[r] = 0.f;
+            if (io.data && r < nq && x < xend) {
+                wv[r] = io.weight[rowpix + x / up];
+                dv[r] = io.data[rowpix + x / up];
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int x = xb + r * up;
+            if (r < nq && x < xend) {
+                const T m = acc[r] + sky;
+                const long long pix = rowpix + x / up;
+                if (io.out) io.out[pix] = (float)m;
+                if (io.data) {
+                    const double w = (double)wv[r];
+                    const double rr = (double)dv[r] - (double)m;
+                    c2 += w * rr * rr;
+                    swr += w * rr;
+                    sw += w;
+                    p.rbuf[pix] = (float)rr;
+                }
+            }
+        }
+    }
+    if (io.data) {
+        c2 = conv_wave_sum(c2);
+        swr = conv_wave_sum(swr);
+        sw = conv_wave_sum(sw);
+        if (lane == 0) { red[wv][0] = c2; red[wv][1] = swr; red[wv][2] = sw; }
+        __syncthreads();
+        if (threadIdx.x < 3) {
+            const int q = threadIdx.x;
+            double sum = red[0][q];
+#pragma unroll
+            for (int w = 1; w < NW; ++w) sum += red[w][q];
+            io.part[(long long)item_idx * 3 + q] = sum;
+        }
+    }
+}
+
+// Whether the sub-problem of an item skips this phase.
+__device__ __forceinline__ bool conv_skipped(const Plan& p, const ConvIO& io, int sub) {
+    if (io.skip_mode == 1) return p.lmf[sub].chol_done == 0 || p.lmf[sub].trial_bad != 0;
+    if (io.skip_mode == 2) return io.lm[sub].need_jac == 0;
+    return false;
+}
+
+// The FP32 kinds.
+template <int P, int KIND, int TH, int TW, int R>
+__global__ __launch_bounds__(TH * TW / R) void k_conv(Plan p, const ConvJob* __restrict__ jobs,
+                                                      const ConvItem* __restrict__ items, int item_begin,
+                                                      ConvIO io) {
+    using T = float;
     constexpr int c = (P - 1) / 2;
-    constexpr int NT = TH * TW / CV_R;              // threads
-    constexpr int LPR = TW / CV_R;                  // lanes per output row
+    constexpr int NT = TH * TW / R;                 // threads
+    constexpr int LPR = TW / R;                     // lanes per output row
     constexpr int NW = NT / 64;                     // waves
     static_assert(NW >= 1 && NT % 64 == 0, "whole waves");
     constexpr int LH = TH + P - 1;
@@ -65,11 +152,7 @@ __global__ __launch_bounds__(TH * TW / CV_R) void k_conv(Plan p, const ConvJob* 
     const ConvItem it = items[item_idx];
     const ConvJob jb = jobs[it.job];
     const DImage& im = p.images[jb.image];
-    if (io.skip_mode == 1) {
-        if (p.lmf[im.sub].chol_done == 0 || p.lmf[im.sub].trial_bad != 0) return;
-    } else if (io.skip_mode == 2) {
-        if (io.lm[im.sub].need_jac == 0) return;
-    }
+    if (conv_skipped(p, io, im.sub)) return;
     const int oy0 = jb.out_y0 + it.ty * TH;
     const int ox0 = jb.out_x0 + it.tx * TW;
     const int iy_base = oy0 - c, ix_base = ox0 - c;
@@ -93,9 +176,7 @@ __global__ __launch_bounds__(TH * TW / CV_R) void k_conv(Plan p, const ConvJob* 
             v[q] = val;
         }
     } else {
-        const T* __restrict__ in;
-        if constexpr (sizeof(T) == 8) in = io.in64 + jb.in_off + (long long)it.ch * jb.in_cs;
-        else in = (jb.in_src ? io.in_s : io.in) + jb.in_off + (long long)it.ch * jb.in_cs;
+        const T* __restrict__ in = (jb.in_src ? io.in_s : io.in) + jb.in_off + (long long)it.ch * jb.in_cs;
         const int iy1 = jb.in_y0 + jb.in_h, ix1 = jb.in_x0 + jb.in_w;
 #pragma unroll
         for (int q = 0; q < NE; ++q) {
@@ -120,114 +201,50 @@ __global__ __launch_bounds__(TH * TW / CV_R) void k_conv(Plan p, const ConvJob* 
 
     // ---- register-window convolution
     const int ty = (int)threadIdx.x / LPR, tx = (int)threadIdx.x % LPR;
-    // the stamp: FP64 copies for the FP64 objective; the flipped stamp for the adjoint;
-    // on a live-PSF image the rendered stamp, or for its PSF columns a derivative stamp
-    using KT = typename std::conditional<sizeof(T) == 8, double, float>::type;
-    const KT* __restrict__ K;
-    if constexpr (sizeof(T) == 8) K = p.psf64 + im.psf_off;
-    else if constexpr (KIND == CONV_ADJ) K = p.psf_flip + im.psf_off;
+    // the stamp: the flipped stamp for the adjoint; on a live-PSF image the rendered stamp, or
+    // for its PSF columns a derivative stamp
+    const float* __restrict__ K;
+    if constexpr (KIND == CONV_ADJ) K = p.psf_flip + im.psf_off;
     else K = im.live ? p.psf_live + im.live_off + (long long)jb.kslot[it.ch < 1 ? 0 : 1] * P * P
                      : p.psf + im.psf_off;
-    T acc[CV_R];
+    T acc[R];
 #pragma unroll
-    for (int r = 0; r < CV_R; ++r) acc[r] = 0;
+    for (int r = 0; r < R; ++r) acc[r] = 0;
     for (int U = 0; U < P; ++U) {
-        const T* row = tile + (ty + P - 1 - U) * LW + tx * CV_R;
-        T s[CV_R + P - 1];
+        const T* row = tile + (ty + P - 1 - U) * LW + tx * R;
+        T s[R + P - 1];
 #pragma unroll
-        for (int k = 0; k < CV_R + P - 1; ++k) s[k] = row[k];
-        T part[CV_R];
+        for (int k = 0; k < R + P - 1; ++k) s[k] = row[k];
+        T part[R];
 #pragma unroll
-        for (int r = 0; r < CV_R; ++r) part[r] = 0;
+        for (int r = 0; r < R; ++r) part[r] = 0;
 #pragma unroll
         for (int V = 0; V < P; ++V) {
-            T kv = (T)K[U * P + V];
-            // FP32: the PSF value (scalar load) moves from its SGPR into a VGPR, one v_mov
-            // per CV_R FMAs: gfx950 issues FMAs of VGPR operands from two waves at once,
-            // FMAs that read an SGPR one at a time (measured 124 vs 76 TFLOP/s)
-            if constexpr (sizeof(T) == 4) {
-                T kvv;
-                asm("v_mov_b32 %0, %1" : "=v"(kvv) : "s"(kv));
-                kv = kvv;
-            }
+            // the PSF value (scalar load) moves from its SGPR into a VGPR, one v_mov per R FMAs:
+            // gfx950 issues FMAs of VGPR operands from two waves at once, FMAs that read an
+            // SGPR one at a time (measured 124 vs 76 TFLOP/s)
+            T kv;
+            asm("v_mov_b32 %0, %1" : "=v"(kv) : "s"(K[U * P + V]));
 #pragma unroll
-            for (int r = 0; r < CV_R; ++r) part[r] = fma(kv, s[r + P - 1 - V], part[r]);
+            for (int r = 0; r < R; ++r) part[r] = fma(kv, s[r + P - 1 - V], part[r]);
         }
 #pragma unroll
-        for (int r = 0; r < CV_R; ++r) acc[r] += part[r];
+        for (int r = 0; r < R; ++r) acc[r] += part[r];
     }
 
     // ---- epilogue
     const int y = oy0 + ty;
-    const int xb = ox0 + tx * CV_R;
+    const int xb = ox0 + tx * R;
     const int xend = jb.out_x0 + jb.out_w;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    // Sub-pixel grids (up = U > 1, a power of two <= CV_R): sum each pixel's U x U outputs,
-    // U consecutive ones in a lane, then across the lanes of rows ty ^ 1 .. ty ^ (U - 1)
-    // (one wave holds 64 / LPR >= 8 rows; tiles and output boxes are whole pixels).  Lane
-    // rows with ty % U == 0 then hold CV_R / U pixel values each.
     const int up = im.up;
-    if (KIND != CONV_ADJ && up > 1) {
-        if (up == 2) bin_lane<2>(acc);
-        else if (up == 4) bin_lane<4>(acc);
-        else bin_lane<8>(acc);
-        for (int k = 1; k < up; k <<= 1)
-#pragma unroll
-            for (int r = 0; r < CV_R; ++r) acc[r] += __shfl_xor(acc[r], k * LPR, 64);
-    }
-    const int nq = KIND == CONV_ADJ ? CV_R : CV_R / up;         // values per lane
+    if constexpr (KIND != CONV_ADJ) bin_pixels<LPR>(acc, up);
+    const int nq = KIND == CONV_ADJ ? R : R / up;               // values per lane
     const int sx = KIND == CONV_ADJ ? 1 : up;                   // render-grid step between them
     const bool yok = y < jb.out_y0 + jb.out_h && (KIND == CONV_ADJ || (ty & (up - 1)) == 0);
     const int yc = KIND == CONV_ADJ ? y : y / up;               // image pixel row
     if constexpr (KIND == CONV_FWD) {
-        const T sky = (T)p.sky_val[jb.image];
-        double c2 = 0.0, swr = 0.0, sw = 0.0;
-        if (yok) {
-            const long long rowpix = im.pix_off + (long long)yc * im.Wc;
-            // the row's weights and data first: their loads overlap instead of following
-            // one another
-            float wv[CV_R], dv[CV_R];
-#pragma unroll
-            for (int r = 0; r < CV_R; ++r) {
-                const int x = xb + r * sx;
-                wv[r] = dv[r] = 0.f;
-                if (io.data && r < nq && x < xend) {
-                    wv[r] = io.weight[rowpix + x / up];
-                    dv[r] = io.data[rowpix + x / up];
-                }
-            }
-#pragma unroll
-            for (int r = 0; r < CV_R; ++r) {
-                const int x = xb + r * sx;
-                if (r < nq && x < xend) {
-                    const T m = acc[r] + sky;
-                    const long long pix = rowpix + x / up;
-                    if (io.out) io.out[pix] = (float)m;
-                    if (io.data) {
-                        const double w = (double)wv[r];
-                        const double rr = (double)dv[r] - (double)m;
-                        c2 += w * rr * rr;
-                        swr += w * rr;
-                        sw += w;
-                        p.rbuf[pix] = (float)rr;
-                    }
-                }
-            }
-        }
-        if (io.data) {
-            c2 = conv_wave_sum(c2);
-            swr = conv_wave_sum(swr);
-            sw = conv_wave_sum(sw);
-            if (lane == 0) { red[wv][0] = c2; red[wv][1] = swr; red[wv][2] = sw; }
-            __syncthreads();
-            if (threadIdx.x < 3) {
-                const int q = threadIdx.x;
-                double sum = red[0][q];
-#pragma unroll
-                for (int w = 1; w < NW; ++w) sum += red[w][q];
-                io.part[(long long)item_idx * 3 + q] = sum;
-            }
-        }
+        fwd_epilogue<T, R, NW>(p, jb, im, io, item_idx, acc, y, xb, yok, red);
     } else if constexpr (KIND == CONV_JCOL) {
         float* __restrict__ out = io.out + jb.out_off + (long long)it.ch * jb.out_cs;
         double s1 = 0.0, s2 = 0.0;
@@ -237,9 +254,9 @@ __global__ __launch_bounds__(TH * TW / CV_R) void k_conv(Plan p, const ConvJob* 
             const int ow = jb.out_w / up;
             const long long orow = (long long)(yc - jb.out_y0 / up) * ow - jb.out_x0 / up;
             const long long rowpix = im.pix_off + (long long)yc * im.Wc;
-            float wv[CV_R], rv[CV_R];                   // loads first, as above
+            float wv[R], rv[R];                   // loads first, as above
 #pragma unroll
-            for (int r = 0; r < CV_R; ++r) {
+            for (int r = 0; r < R; ++r) {
                 const int x = xb + r * sx;
                 wv[r] = rv[r] = 0.f;
                 if (epart && r < nq && x < xend) {
@@ -248,7 +265,7 @@ __global__ __launch_bounds__(TH * TW / CV_R) void k_conv(Plan p, const ConvJob* 
                 }
             }
 #pragma unroll
-            for (int r = 0; r < CV_R; ++r) {
+            for (int r = 0; r < R; ++r) {
                 const int x = xb + r * sx;
                 if (r < nq && x < xend) {
                     const int xc = x / up;
@@ -279,12 +296,181 @@ __global__ __launch_bounds__(TH * TW / CV_R) void k_conv(Plan p, const ConvJob* 
         if (yok) {
             const long long orow = (long long)(y - jb.out_y0) * jb.out_w - jb.out_x0;
 #pragma unroll
-            for (int r = 0; r < CV_R; ++r) {
+            for (int r = 0; r < R; ++r) {
                 const int x = xb + r;
                 if (x < xend) out[orow + x] = acc[r];
             }
         }
     }
+}
+
+// Row pitch (in doubles) of the FP64 kernel's LDS tile: an odd number of 16-byte chunks.  The
+// lanes of one output row read windows 64 bytes apart (every fourth bank group); with an even
+// number of chunks the rows of a wave fall on the same groups (P = 25, 2048 x 2048: 109 us at
+// a pitch of 88 doubles, 70 us at 90; P = 15: 51 us at 80, 34 us at 78).
+constexpr int pitch64(int w) {
+    const int e = (w + 1) & ~1;
+    return (e / 2) % 2 ? e : e + 2;
+}
+
+// The FP64 objective's model convolution.  Where the stamp is the same upside down (any stamp
+// sampled from a round profile; psf_sym, found per call by k_psf_prep), rows U and P - 1 - U
+// of the stamp multiply the sum of two input rows: R + P - 1 additions replace P R FMAs.
+// Each window goes through registers in pieces of CH64 taps, the next piece's LDS reads in
+// flight while the current one is multiplied.  Above P = 41 the pieces are pinned in that order
+// (the compiler otherwise reads whole windows of both rows first, 256 registers and spills at
+// P = 51: 411 us for 2048 x 2048 against 297 pinned); below, its own order is as fast on a
+// full chip and better with one workgroup per CU (P = 31: 35 against 43 us).
+// Bound by FP64 issue and LDS reads alike: by 2 P^2 per output, on one 2048 x 2048 image,
+// 34 -> 55 TFLOP/s at P = 15 without and with the fold, 44 -> 74 at P = 25, 49 -> 80 at P = 41,
+// 53 -> 78 at P = 51, 41 -> 63 at P = 63.
+constexpr int CH64 = 8;
+__device__ __forceinline__ void pin(double (&a)[CV_R], int& o1, int& o2) {
+    asm volatile("" : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(a[4]), "+v"(a[5]), "+v"(a[6]), "+v"(a[7]),
+                      "+v"(o1), "+v"(o2));
+}
+__device__ __forceinline__ void pin(double (&a)[CV_R_FINE], int& o1, int& o2) {
+    asm volatile("" : "+v"(a[0]), "+v"(a[1]), "+v"(o1), "+v"(o2));
+}
+template <int P, int TH, int TW, int R>
+__global__ __launch_bounds__(TH * TW / R) void k_conv64(Plan p, const ConvJob* __restrict__ jobs,
+                                                        const ConvItem* __restrict__ items, int item_begin,
+                                                        ConvIO io) {
+    constexpr int c = (P - 1) / 2;
+    constexpr int NT = TH * TW / R;
+    constexpr int LPR = TW / R;
+    constexpr int NW = NT / 64;
+    static_assert(NW >= 1 && NT % 64 == 0, "whole waves");
+    constexpr int LH = TH + P - 1;
+    constexpr int LW0 = TW + P - 1;
+    constexpr int LW = pitch64(LW0);
+    __shared__ __attribute__((aligned(16))) double tile[LH * LW];
+    __shared__ double red[NW][3];
+
+    const int item_idx = item_begin + xcd_chunk_item((int)blockIdx.x, (int)gridDim.x);
+    const ConvItem it = items[item_idx];
+    const ConvJob jb = jobs[it.job];
+    const DImage& im = p.images[jb.image];
+    if (conv_skipped(p, io, im.sub)) return;
+    const int oy0 = jb.out_y0 + it.ty * TH;
+    const int ox0 = jb.out_x0 + it.tx * TW;
+    const int iy_base = oy0 - c, ix_base = ox0 - c;
+
+    // ---- stage the input tile (zero outside the input rectangle), NB loads of a thread at a
+    // time before their LDS stores
+    constexpr int NE = (LH * LW0 + NT - 1) / NT, NB = NE < 24 ? NE : 24;
+    {
+        const double* __restrict__ in = io.in64 + jb.in_off + (long long)it.ch * jb.in_cs;
+        const int iy1 = jb.in_y0 + jb.in_h, ix1 = jb.in_x0 + jb.in_w;
+        for (int q0 = 0; q0 < NE; q0 += NB) {
+            double v[NB];
+#pragma unroll
+            for (int q = 0; q < NB; ++q) {
+                const int e = (int)threadIdx.x + NT * (q0 + q);
+                const int ly = e / LW0, lx = e - ly * LW0;
+                const int y = iy_base + ly, x = ix_base + lx;
+                v[q] = 0.0;
+                if (e < LH * LW0 && y >= jb.in_y0 && y < iy1 && x >= jb.in_x0 && x < ix1)
+                    v[q] = in[(long long)(y - jb.in_y0) * jb.in_w + (x - jb.in_x0)];
+            }
+#pragma unroll
+            for (int q = 0; q < NB; ++q) {
+                const int e = (int)threadIdx.x + NT * (q0 + q);
+                if (e < LH * LW0) {
+                    const int ly = e / LW0, lx = e - ly * LW0;
+                    tile[ly * LW + lx] = v[q];
+                }
+            }
+        }
+    }
+    __syncthreads();
+
+    // ---- register-window convolution
+    const int ty = (int)threadIdx.x / LPR, tx = (int)threadIdx.x % LPR;
+    // the stamp does not change during the launch: scalar loads, which the barriers below would
+    // otherwise turn into vector loads
+    using Const = const __attribute__((address_space(4))) double*;
+    const Const K = (Const)(p.psf64 + im.psf_off);
+    double acc[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) acc[r] = 0.0;
+    constexpr int N = R + P - 1, NC = (P + CH64 - 1) / CH64;
+    constexpr bool PINNED = P > (R == CV_R ? 41 : 51);
+    // acc[r] += sum_j kk[P - 1 - j] s[r + j], s the window that starts at pair o1 of the tile
+    // (with TWO: plus the one at pair o2), read as pairs (ds_read_b128).  pin() keeps the
+    // pieces apart: a piece's FMAs come before it, the reads that follow (whose offsets pass
+    // through it) after.
+    static_assert(N % 2 == 0 && R % 2 == 0 && LW % 2 == 0 && CH64 % 2 == 0, "windows are whole pairs");
+    const double2* tile2 = reinterpret_cast<const double2*>(tile);
+    auto row = [&](auto two, int o1, int o2, Const kk) {
+        constexpr bool TWO = decltype(two)::value;
+        double s[N], part[R];
+        double2 a[CH64 / 2], b[CH64 / 2];
+#pragma unroll
+        for (int r = 0; r < R; ++r) part[r] = 0.0;
+#pragma unroll
+        for (int k = 0; k < R; k += 2) {
+            double2 v = tile2[o1 + k / 2];
+            if constexpr (TWO) {
+                const double2 w = tile2[o2 + k / 2];
+                v.x += w.x;
+                v.y += w.y;
+            }
+            s[k] = v.x;
+            s[k + 1] = v.y;
+        }
+#pragma unroll
+        for (int q = 0; q < CH64; q += 2)
+            if (R + q < N) {
+                a[q / 2] = tile2[o1 + (R + q) / 2];
+                if constexpr (TWO) b[q / 2] = tile2[o2 + (R + q) / 2];
+            }
+#pragma unroll
+        for (int ch = 0; ch < NC; ++ch) {
+#pragma unroll
+            for (int q = 0; q < CH64; q += 2) {
+                const int k = R + ch * CH64 + q;
+                if (k < N) {
+                    s[k] = a[q / 2].x;
+                    s[k + 1] = a[q / 2].y;
+                    if constexpr (TWO) {
+                        s[k] += b[q / 2].x;
+                        s[k + 1] += b[q / 2].y;
+                    }
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < CH64; q += 2) {
+                const int k = R + (ch + 1) * CH64 + q;
+                if (k < N) {
+                    a[q / 2] = tile2[o1 + k / 2];
+                    if constexpr (TWO) b[q / 2] = tile2[o2 + k / 2];
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < CH64; ++q) {
+                const int j = ch * CH64 + q;
+                if (j < P) {
+                    const double kv = kk[P - 1 - j];
+#pragma unroll
+                    for (int r = 0; r < R; ++r) part[r] = fma(kv, s[r + j], part[r]);
+                }
+            }
+            if constexpr (PINNED) pin(part, o1, o2);
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) acc[r] += part[r];
+    };
+    const int o0 = (ty * LW + tx * R) / 2;
+    const int npair = p.psf_sym[jb.image] ? c : 0;   // block-uniform
+    for (int U = 0; U < npair; ++U) row(std::true_type{}, o0 + (P - 1 - U) * (LW / 2), o0 + U * (LW / 2), K + U * P);
+    for (int U = npair; U < P - npair; ++U) row(std::false_type{}, o0 + (P - 1 - U) * (LW / 2), o0, K + U * P);
+
+    // ---- epilogue
+    const int y = oy0 + ty;
+    bin_pixels<LPR>(acc, im.up);
+    const bool yok = y < jb.out_y0 + jb.out_h && (ty & (im.up - 1)) == 0;
+    fwd_epilogue<double, R, NW>(p, jb, im, io, item_idx, acc, y, ox0 + tx * R, yok, red);
 }
 
 // Jacobian-column convolution with a rank-one stamp K_UV = a_U b_V (jobs of shape
@@ -315,11 +501,7 @@ __global__ __launch_bounds__(256) void k_conv_sep(Plan p, const ConvJob* __restr
     const ConvItem it = items[item_idx];
     const ConvJob jb = jobs[it.job];
     const DImage& im = p.images[jb.image];
-    if (io.skip_mode == 1) {
-        if (p.lmf[im.sub].chol_done == 0 || p.lmf[im.sub].trial_bad != 0) return;
-    } else if (io.skip_mode == 2) {
-        if (io.lm[im.sub].need_jac == 0) return;
-    }
+    if (conv_skipped(p, io, im.sub)) return;
     const int oy0 = jb.out_y0 + it.ty * TH;
     const int ox0 = jb.out_x0 + it.tx * TW;
     const int iy_base = oy0 - c, ix_base = ox0 - c;
@@ -450,14 +632,18 @@ __global__ __launch_bounds__(256) void k_conv_sep(Plan p, const ConvJob* __restr
     X(31) X(33) X(35) X(37) X(39) X(41) X(43) X(45) X(47) X(49) X(51) X(53) X(55) X(57)      \
     X(59) X(61) X(63)
 
-template <int KIND, typename T, int TH, int TW>
+template <int KIND, typename T, int TH, int TW, int R>
 hipError_t launch_conv_shape(const Plan& p, const ConvLaunch& L, const ConvIO& io, hipStream_t st) {
-    dim3 grid(L.item_count), block(TH * TW / CV_R);
+    dim3 grid(L.item_count), block(TH * TW / R);
     switch (L.P) {
-#define APX_CASE(PP)                                                                         \
-    case PP:                                                                                 \
-        hipLaunchKernelGGL((k_conv<PP, KIND, T, TH, TW>), grid, block, 0, st, p, L.jobs,     \
-                           L.items, L.item_begin, io);                                      \
+#define APX_CASE(PP)                                                                                     \
+    case PP:                                                                                             \
+        if constexpr (sizeof(T) == 8)                                                                    \
+            hipLaunchKernelGGL((k_conv64<PP, TH, TW, R>), grid, block, 0, st, p, L.jobs, L.items,        \
+                               L.item_begin, io);                                                        \
+        else                                                                                             \
+            hipLaunchKernelGGL((k_conv<PP, KIND, TH, TW, R>), grid, block, 0, st, p, L.jobs, L.items,    \
+                               L.item_begin, io);                                                        \
         break;
         APX_FOR_EACH_P(APX_CASE)
 #undef APX_CASE
@@ -488,10 +674,12 @@ hipError_t launch_conv_kind(const Plan& p, const ConvLaunch& L, const ConvIO& io
     if (L.item_count <= 0) return hipSuccess;
     static_assert(N_TILE_SHAPES == 4, "one case per tile shape");
     switch (L.shape) {
-        case 0: return launch_conv_shape<KIND, T, tile_th(0), tile_tw(0)>(p, L, io, st);
-        case 1: return launch_conv_shape<KIND, T, tile_th(1), tile_tw(1)>(p, L, io, st);
-        case 2: return launch_conv_shape<KIND, T, tile_th(2), tile_tw(2)>(p, L, io, st);
-        case 3: return launch_conv_shape<KIND, T, tile_th(3), tile_tw(3)>(p, L, io, st);
+        case 0: return launch_conv_shape<KIND, T, tile_th(0), tile_tw(0), CV_R>(p, L, io, st);
+        case 1: return launch_conv_shape<KIND, T, tile_th(1), tile_tw(1), CV_R>(p, L, io, st);
+        case 2: return launch_conv_shape<KIND, T, tile_th(2), tile_tw(2), CV_R>(p, L, io, st);
+        case FINE_SHAPE:
+            if (L.fine) return launch_conv_shape<KIND, T, tile_th(FINE_SHAPE), tile_tw(FINE_SHAPE), CV_R_FINE>(p, L, io, st);
+            return launch_conv_shape<KIND, T, tile_th(FINE_SHAPE), tile_tw(FINE_SHAPE), CV_R>(p, L, io, st);
         default: return hipErrorInvalidValue;
     }
 }

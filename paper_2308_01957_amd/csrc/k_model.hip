@@ -165,9 +165,18 @@ __global__ __launch_bounds__(256) void k_psf_prep(Plan p, const double* __restri
     const int P = im.P, c = im.c, P2 = P * P;
     double* K64 = p.psf64 + im.psf_off;
     if (!im.live) {
-        for (int e = threadIdx.x; e < P2; e += blockDim.x) K64[e] = (double)p.psf[im.psf_off + e];
+        const float* K = p.psf + im.psf_off;
+        int sym = 1;
+        for (int e = threadIdx.x; e < P2; e += blockDim.x) {
+            const int u = e / P;
+            K64[e] = (double)K[e];
+            sym &= K[e] == K[e + (P - 1 - 2 * u) * P];   // false for a NaN: then no rows are paired
+        }
+        sym = __syncthreads_and(sym);
+        if (threadIdx.x == 0) p.psf_sym[k] = sym;
         return;
     }
+    if (threadIdx.x == 0) p.psf_sym[k] = 1;          // a function of u^2 + v^2
     double n = im.live_par[0] >= 0 ? theta[im.live_par[0]] : im.live_fixed[0];
     double rd = im.live_par[1] >= 0 ? theta[im.live_par[1]] : im.live_fixed[1];
     const bool valid = isfinite(n) && isfinite(rd) && n >= PSF_N_MIN && n <= PSF_N_MAX &&
