@@ -1892,6 +1892,7 @@ apx_status apx_problem_bind_workspace(apx_problem* P, void* dev, uint64_t bytes)
         p.node_w[k] = k < (int)P->node_w.size() ? P->node_w[k] : 0.f;
         p.node_od[k] = k < (int)P->node_od.size() ? P->node_od[k] : 0.0;
         p.node_wd[k] = k < (int)P->node_wd.size() ? P->node_wd[k] : 0.0;
+        p.node_max = std::max(p.node_max, std::fabs(p.node_od[k]));
     }
     p.images = wsp<DImage>(P, "images");
     p.comps = wsp<DComp>(P, "comps");

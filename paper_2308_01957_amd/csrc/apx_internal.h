@@ -106,6 +106,9 @@ struct DComp {
     double fixed[7];
 };
 
+// Terms of the binomial series the FP64 render uses away from a component's centre
+constexpr int BIN_DEG = 11;
+
 // Per-call component constants (written by k_prep from theta)
 struct CompConst {
     double x0, y0;            // Sersic centre (sky frame); point: pixel position
@@ -115,6 +118,12 @@ struct CompConst {
     double h_d, A_d, B_d;     // t = exp2(g log2 R^2 - h), I = exp2(A - B t)
     double g_d;               // 0.5 / n
     double F64;               // point-source flux (FP64)
+    // The pixel axes in the component's frame (FP64 render): (ax, ay) and (bx, by) are the
+    // images of (1, 0) and (0, 1), rotated and the second entry scaled by 1/q; qxx, qxy, qyy
+    // the quadratic form of a pixel offset, R^2(offset) = qxx ox^2 + qxy ox oy + qyy oy^2, and
+    // qmax its bound over the nodes
+    double ax, ay, bx, by, qxx, qxy, qyy, qmax;
+    double bin[BIN_DEG];      // (1 + d)^g = 1 + bin[0] d + bin[1] d^2 + ... (binomial series)
     float cs, sn, iq;         // cos PA, sin PA, 1/q
     float g;                  // 0.5 / n
     float b, bp, n, re, q;    // b_n, db_n/dn and raw parameters (derivatives)
@@ -218,6 +227,7 @@ struct Plan {
     double k_re;
     float node_o[MAX_NODES_1D], node_w[MAX_NODES_1D];
     double node_od[MAX_NODES_1D], node_wd[MAX_NODES_1D];
+    double node_max;          // largest |node offset|
 
     const DImage* images;
     const DComp* comps;

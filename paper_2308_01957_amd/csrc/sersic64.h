@@ -140,6 +140,29 @@ __device__ __forceinline__ double log2_t(double x, const double* __restrict__ ta
     return fma(q * u, 1.4426950408889634074, tab[128 + j] + (double)e);
 }
 
+// 2^(y / 64) by the same table and series, for |y| < 2^23 (the argument comes scaled, which
+// saves the scaling and makes the remainder a difference): n = rint(y), f = y - n exact.
+// (Rounding by adding 1.5 2^52 and building the power of two in the exponent field, without
+// rint, conversion and ldexp, measured 5 % slower over the whole render.)
+constexpr double exp2s_coef(int k) {                 // (ln 2 / 64)^k / k!
+    double v = 1.0;
+    for (int i = 1; i <= k; ++i) v *= 0.6931471805599453094 / 64.0 / i;
+    return v;
+}
+constexpr double EXP2S_C4 = exp2s_coef(4);
+__device__ __forceinline__ double exp2_64th(double y, const double* __restrict__ tab, double e4) {
+    constexpr double C1 = exp2s_coef(1), C2 = exp2s_coef(2), C3 = exp2s_coef(3), C5 = exp2s_coef(5);
+    const double nd = rint(y);
+    const double f = y - nd;
+    const int n = (int)nd;
+    double p = fma_svv(C5, f, e4);
+    p = fma_vvs(p, f, C3);
+    p = fma_vvs(p, f, C2);
+    p = fma_vvs(p, f, C1);
+    p = fma(p, f, 1.0);
+    return ldexp(tab[n & 63] * p, n >> 6);
+}
+
 // I at a point given in the component's frame (xp along the major axis, yq = yp / q).
 __device__ __forceinline__ double sersic_I64_r(const CompConst& c, double xp, double yq,
                                                const double* __restrict__ tab, const Poly64Regs& rg) {
