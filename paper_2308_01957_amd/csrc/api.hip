@@ -117,10 +117,10 @@ struct apx_problem {
     std::vector<PairItem> xitems;                 // 4 x 4-block items of two groups, sorted by block shape
     int cross_begin[N_CROSS + 1] = {};            // items of block shape k: [cross_begin[k], cross_begin[k + 1])
     // reduction tables
-    std::vector<int> img_seg, img_idx;            // FWD items of each image
+    std::vector<int2> img_items;                  // FWD items of each image: first, end
     std::vector<int> col_seg, col_idx;            // JCOL items of each column
     std::vector<int> gcol_seg;                    // grad partials of each column (contiguous)
-    std::vector<int> chi_seg, chi_idx;            // img_sum entries of each sub
+    std::vector<int> chi_seg, sub_img;            // images of each sub
     std::vector<int> g_seg, g_idx, g_sub;         // J^T W r sources per theta index
     std::vector<double> g_w;
     std::vector<int> gr_seg, gr_idx;              // gradient sources per theta index
@@ -154,7 +154,7 @@ struct apx_problem {
     Layout L;
     std::map<std::string, size_t> off;
     Plan plan{};
-    double* asrc = nullptr;          // [pair_part | col_sum | grad_col | img_sum]
+    double* asrc = nullptr;          // [pair_part | col_sum | (column numbers of the gradient) | img_sum]
     long long asrc_col = 0, asrc_gcol = 0, asrc_img = 0;
     double* chi2_sub = nullptr;      // [n_sub]
     double* chi2_trial = nullptr;    // [n_sub]
@@ -1231,13 +1231,9 @@ static apx_status build_plan(apx_problem* P, const apx_problem_desc* d) {
 
     // reduction tables: FWD items per image, JCOL items per column, grad partials per column
     {
-        P->img_seg.assign(1, 0);
         for (int k = 0; k < d->n_images; ++k) {
-            const DImage& im = P->images[k];
-            (void)im;
-            const int n = job_tiles(P->fwd_jobs[k]);
-            for (int q = 0; q < n; ++q) P->img_idx.push_back(fwd_item_begin[k] + q);
-            P->img_seg.push_back((int)P->img_idx.size());
+            const int b = fwd_item_begin[k];
+            P->img_items.push_back(make_int2(b, b + job_tiles(P->fwd_jobs[k])));
         }
         P->col_seg.assign(1, 0);
         P->gcol_seg.assign(1, 0);
@@ -1538,12 +1534,12 @@ static apx_status build_plan(apx_problem* P, const apx_problem_desc* d) {
             P->par_sky_off.push_back((int)P->par_sky.size());
             P->g_sub.push_back(std::max(0, P->par_sub[p]));
         }
-        P->chi_seg.assign(1, 0);
-        for (int s = 0; s < d->n_sub; ++s) {
-            for (int k = 0; k < d->n_images; ++k)
-                if (P->images[k].sub == s) P->chi_idx.push_back((int)(P->asrc_img + 3LL * k));
-            P->chi_seg.push_back((int)P->chi_idx.size());
-        }
+        P->chi_seg.assign(d->n_sub + 1, 0);
+        P->sub_img.resize(d->n_images);
+        for (const DImage& im : P->images) P->chi_seg[im.sub + 1]++;
+        for (int s = 0; s < d->n_sub; ++s) P->chi_seg[s + 1] += P->chi_seg[s];
+        std::vector<int> next(P->chi_seg.begin(), P->chi_seg.end() - 1);
+        for (int k = 0; k < d->n_images; ++k) P->sub_img[next[P->images[k].sub]++] = k;
     }
     if ((long long)P->asrc_img + 3LL * d->n_images >= (1LL << 31))
         return fail(C, APX_E_UNSUPPORTED, "problem too large for 32-bit reduction indices");
@@ -1584,13 +1580,12 @@ static void layout(apx_problem* P) {
     ws_take<PairItem>(P, "pitems64", P->pitems64.size());
     ws_take<PairItem>(P, "gitems", P->gitems.size());
     ws_take<PairItem>(P, "xitems", P->xitems.size());
-    ws_take<int>(P, "img_seg", P->img_seg.size());
-    ws_take<int>(P, "img_idx", P->img_idx.size());
+    ws_take<int2>(P, "img_items", P->img_items.size());
     ws_take<int>(P, "col_seg", P->col_seg.size());
     ws_take<int>(P, "col_idx", P->col_idx.size());
     ws_take<int>(P, "gcol_seg", P->gcol_seg.size());
     ws_take<int>(P, "chi_seg", P->chi_seg.size());
-    ws_take<int>(P, "chi_idx", P->chi_idx.size());
+    ws_take<int>(P, "sub_img", P->sub_img.size());
     ws_take<int>(P, "g_seg", P->g_seg.size());
     ws_take<int>(P, "g_idx", P->g_idx.size());
     ws_take<double>(P, "g_w", P->g_w.size());
@@ -1834,13 +1829,12 @@ apx_status apx_problem_bind_workspace(apx_problem* P, void* dev, uint64_t bytes)
     HIPCHK(upload(P, "pitems64", P->pitems64));
     HIPCHK(upload(P, "gitems", P->gitems));
     HIPCHK(upload(P, "xitems", P->xitems));
-    HIPCHK(upload(P, "img_seg", P->img_seg));
-    HIPCHK(upload(P, "img_idx", P->img_idx));
+    HIPCHK(upload(P, "img_items", P->img_items));
     HIPCHK(upload(P, "col_seg", P->col_seg));
     HIPCHK(upload(P, "col_idx", P->col_idx));
     HIPCHK(upload(P, "gcol_seg", P->gcol_seg));
     HIPCHK(upload(P, "chi_seg", P->chi_seg));
-    HIPCHK(upload(P, "chi_idx", P->chi_idx));
+    HIPCHK(upload(P, "sub_img", P->sub_img));
     HIPCHK(upload(P, "g_seg", P->g_seg));
     HIPCHK(upload(P, "g_idx", P->g_idx));
     HIPCHK(upload(P, "g_w", P->g_w));
@@ -1927,7 +1921,6 @@ apx_status apx_problem_bind_workspace(apx_problem* P, void* dev, uint64_t bytes)
     P->asrc = wsp<double>(P, "asrc");
     p.pair_part = P->asrc;
     p.col_sum = P->asrc + P->asrc_col;
-    p.grad_col = P->asrc + P->asrc_gcol;
     p.img_sum = P->asrc + P->asrc_img;
     p.A = wsp<double>(P, "A");
     p.M = wsp<double>(P, "M");
@@ -2119,23 +2112,14 @@ static apx_status run_conv(apx_problem* P, int kind, const ConvIO& io) {
         if (_s != APX_OK) return _s;          \
     } while (0)
 
-static SegSum segsum_base() {
-    SegSum a{};
-    a.stride = 1;
-    a.ostride = 1;
-    a.scale = 1.0;
-    return a;
-}
-
 // Per-theta constants (component constants, stamps) and, in adaptive mode, the
 // integration choices and values; want_grad: the refined pixels' derivatives too.
-static apx_status prep(apx_problem* P, const double* theta, int lm_trial, int skip_mode,
-                       const apx_lm_state* lm, int want_grad) {
+static apx_status prep(apx_problem* P, const PrepIO& pio, int skip_mode, const apx_lm_state* lm, int want_grad) {
     const Plan& p = P->plan;
     hipStream_t st = P->ctx->stream;
     {
         TimeScope ts(P, APX_TIME_PREP);
-        HIPCHK(launch_prep(p, theta, lm_trial, st));
+        HIPCHK(launch_prep(p, pio, st));
         if (P->fft_live < 0) {
             P->fft_live = 0;
             for (const DImage& im : P->images) P->fft_live += im.fft_off >= 0 && im.live ? 1 : 0;
@@ -2153,13 +2137,19 @@ static apx_status prep(apx_problem* P, const double* theta, int lm_trial, int sk
     return APX_OK;
 }
 
-// Forward model + residual partials, reduced to img_sum (3 per image) and chi2[n_sub].
-static apx_status fwd_chi2(apx_problem* P, const double* theta, const float* data, const float* weight,
-                           float* model, double* chi2_out, int lm_trial, int skip_mode,
-                           const apx_lm_state* lm, int want_grad) {
+static PrepIO prep_at(const double* theta) {
+    PrepIO io{};
+    io.theta = theta;
+    return io;
+}
+
+// Forward model + residual partials, reduced to img_sum (3 per image) and, by tail, chi2[n_sub]
+// and what its kind asks for (tail.chi2 may be null).
+static apx_status fwd_chi2(apx_problem* P, const PrepIO& pio, const float* data, const float* weight,
+                           float* model, TailIO tail, int skip_mode, const apx_lm_state* lm, int want_grad) {
     const Plan& p = P->plan;
     hipStream_t st = P->ctx->stream;
-    APXCHK(prep(P, theta, lm_trial, skip_mode, lm, want_grad));
+    APXCHK(prep(P, pio, skip_mode, lm, want_grad));
     {
         TimeScope ts(P, APX_TIME_RENDER);
         if (P->objective == APX_OBJECTIVE_FP64) HIPCHK(launch_render64(p, skip_mode, lm, st));
@@ -2176,30 +2166,20 @@ static apx_status fwd_chi2(apx_problem* P, const double* theta, const float* dat
     io.lm = lm;
     APXCHK(run_conv(P, CONV_FWD, io));
     if (data) {
-        TimeScope ts(P, APX_TIME_REDUCE);
-        {
-            SegSum a = segsum_base();               // sum w r^2, sum w r, sum w per image
-            a.src = p.fwd_part;
-            a.stride = 3;
-            a.ncomp = 3;
-            a.seg = wsp<int>(P, "img_seg");
-            a.idx = wsp<int>(P, "img_idx");
-            a.n_seg = P->n_images;
-            a.out = p.img_sum;
-            a.ostride = 3;
-            HIPCHK(launch_segsum(a, st));
-        }
-        if (chi2_out) {
-            SegSum a = segsum_base();
-            a.src = P->asrc;
-            a.seg = wsp<int>(P, "chi_seg");
-            a.idx = wsp<int>(P, "chi_idx");
-            a.n_seg = P->n_sub;
-            a.out = chi2_out;
-            HIPCHK(launch_segsum(a, st));
-        }
+        TimeScope ts(P, tail.kind >= TAIL_INIT ? APX_TIME_LM : APX_TIME_REDUCE);
+        tail.img_items = wsp<int2>(P, "img_items");
+        tail.chi_seg = wsp<int>(P, "chi_seg");
+        tail.sub_img = wsp<int>(P, "sub_img");
+        HIPCHK(launch_tail(p, tail, st));
     }
     return APX_OK;
+}
+
+static TailIO tail_of(int kind, double* chi2) {
+    TailIO t{};
+    t.kind = kind;
+    t.chi2 = chi2;
+    return t;
 }
 
 // Derivative images and Jacobian blocks (with sum w r J, sum w J partials if weight).
@@ -2224,18 +2204,9 @@ static apx_status psf_columns(apx_problem* P, const float* weight, int skip_mode
 }
 
 static apx_status col_sums(apx_problem* P) {
-    const Plan& p = P->plan;
+    if (P->col_idx.empty()) return APX_OK;          // every column's sums come from its Gram items
     TimeScope ts(P, APX_TIME_REDUCE);
-    SegSum a = segsum_base();                       // sum w r J, sum w J per column
-    a.src = p.jcol_part;
-    a.stride = 2;
-    a.ncomp = 2;
-    a.seg = wsp<int>(P, "col_seg");
-    a.idx = wsp<int>(P, "col_idx");
-    a.n_seg = (int)P->cols.size();
-    a.out = p.col_sum;
-    a.ostride = 2;
-    HIPCHK(launch_segsum(a, P->ctx->stream));
+    HIPCHK(launch_col_sums(P->plan, wsp<int>(P, "col_seg"), wsp<int>(P, "col_idx"), P->ctx->stream));
     return APX_OK;
 }
 
@@ -2293,17 +2264,30 @@ static apx_status normal_eq(apx_problem* P, const float* weight, double* A_out, 
     a.subs = p.subs;
     a.out = A_out;
     a.lm = lm;
-    HIPCHK(launch_assemble_A(a, st));
-    SegSum g = segsum_base();
-    g.src = P->asrc;
-    g.seg = wsp<int>(P, "g_seg");
-    g.idx = wsp<int>(P, "g_idx");
-    g.wts = wsp<double>(P, "g_w");
-    g.n_seg = P->n_par;
-    g.out = g_out;
-    g.seg_sub = wsp<int>(P, "g_sub");
-    g.lm = lm;
-    HIPCHK(launch_segsum(g, st));
+    a.g_seg = wsp<int>(P, "g_seg");
+    a.g_idx = wsp<int>(P, "g_idx");
+    a.g_w = wsp<double>(P, "g_w");
+    a.g_sub = wsp<int>(P, "g_sub");
+    a.n_par = P->n_par;
+    a.g = g_out;
+    HIPCHK(launch_assemble(a, st));
+    return APX_OK;
+}
+
+// The gradient from the tile partials and the image (and live-PSF column) sums.
+static apx_status grad_sum(apx_problem* P, double* out) {
+    GradSum a{};
+    a.src = P->asrc;
+    a.grad_part = P->plan.grad_part;
+    a.gr_seg = wsp<int>(P, "gr_seg");
+    a.gr_idx = wsp<int>(P, "gr_idx");
+    a.gr_w = wsp<double>(P, "gr_w");
+    a.gcol_seg = wsp<int>(P, "gcol_seg");
+    a.col0 = (int)P->asrc_gcol;
+    a.n_cols = (int)P->cols.size();
+    a.n_par = P->n_par;
+    a.out = out;
+    HIPCHK(launch_grad_sum(a, P->ctx->stream));
     return APX_OK;
 }
 
@@ -2326,16 +2310,14 @@ static bool par_ok(const apx_problem* P, const void* ptr) { return ptr != nullpt
 apx_status apx_render(apx_problem* P, const double* theta, float* model) {
     APXCHK(ready(P));
     if (!par_ok(P, theta) || !model) return fail(P->ctx, APX_E_INVALID, "null pointer");
-    return fwd_chi2(P, theta, nullptr, nullptr, model, nullptr, 0, 0, nullptr, 0);
+    return fwd_chi2(P, prep_at(theta), nullptr, nullptr, model, TailIO{}, 0, nullptr, 0);
 }
 
 apx_status apx_chi2(apx_problem* P, const double* theta, const float* data, const float* weight,
                     double* chi2) {
     APXCHK(ready(P));
     if (!par_ok(P, theta) || !data || !weight || !chi2) return fail(P->ctx, APX_E_INVALID, "null pointer");
-    APXCHK(fwd_chi2(P, theta, data, weight, nullptr, chi2, 0, 0, nullptr, 0));
-    HIPCHK(launch_chi2_check(chi2, P->n_sub, P->plan.sticky, P->ctx->stream));
-    return APX_OK;
+    return fwd_chi2(P, prep_at(theta), data, weight, nullptr, tail_of(TAIL_CHECK, chi2), 0, nullptr, 0);
 }
 
 apx_status apx_jacobian(apx_problem* P, const double* theta, float* J, int64_t ldJ) {
@@ -2343,7 +2325,7 @@ apx_status apx_jacobian(apx_problem* P, const double* theta, float* J, int64_t l
     if (!par_ok(P, theta) || !par_ok(P, J)) return fail(P->ctx, APX_E_INVALID, "null pointer");
     if (ldJ < P->n_pix) return fail(P->ctx, APX_E_INVALID, "ldJ < n_pix");
     hipStream_t st = P->ctx->stream;
-    APXCHK(prep(P, theta, 0, 0, nullptr, 1));
+    APXCHK(prep(P, prep_at(theta), 0, nullptr, 1));
     APXCHK(jac_blocks(P, nullptr, nullptr));
     HIPCHK(launch_jscatter(P->plan, wsp<int>(P, "par_off"), wsp<int>(P, "par_cols"), wsp<int>(P, "par_sky_off"),
                            wsp<int>(P, "par_sky"), J, ldJ, st));
@@ -2355,11 +2337,9 @@ apx_status apx_jtwj(apx_problem* P, const double* theta, const float* data, cons
     APXCHK(ready(P));
     if (!par_ok(P, theta) || !data || !weight || !par_ok(P, JtWJ) || !par_ok(P, JtWr) || !chi2)
         return fail(P->ctx, APX_E_INVALID, "null pointer");
-    APXCHK(fwd_chi2(P, theta, data, weight, nullptr, chi2, 0, 0, nullptr, 1));
+    APXCHK(fwd_chi2(P, prep_at(theta), data, weight, nullptr, tail_of(TAIL_CHECK, chi2), 0, nullptr, 1));
     APXCHK(jac_blocks(P, weight, nullptr));
-    APXCHK(normal_eq(P, weight, JtWJ, JtWr, nullptr));
-    HIPCHK(launch_chi2_check(chi2, P->n_sub, P->plan.sticky, P->ctx->stream));
-    return APX_OK;
+    return normal_eq(P, weight, JtWJ, JtWr, nullptr);
 }
 
 }  // extern "C"
@@ -2373,7 +2353,7 @@ static apx_status cov_core(apx_problem* P, const double* theta, const float* dat
         return fail(P->ctx, APX_E_INVALID, "null pointer");
     const Plan& p = P->plan;
     hipStream_t st = P->ctx->stream;
-    APXCHK(fwd_chi2(P, theta, data, weight, nullptr, chi2, 0, 0, nullptr, 1));
+    APXCHK(fwd_chi2(P, prep_at(theta), data, weight, nullptr, tail_of(TAIL_CHECK, chi2), 0, nullptr, 1));
     APXCHK(jac_blocks(P, weight, nullptr));
     APXCHK(normal_eq(P, weight, p.A, p.gvec, nullptr));
     {
@@ -2389,7 +2369,6 @@ static apx_status cov_core(apx_problem* P, const double* theta, const float* dat
             if (factor) HIPCHK(launch_cov_transpose(p, s, n, out, st));
         }
     }
-    HIPCHK(launch_chi2_check(chi2, P->n_sub, p.sticky, st));
     return APX_OK;
 }
 
@@ -2408,13 +2387,16 @@ apx_status apx_covariance_factor(apx_problem* P, const double* theta, const floa
 }  // extern "C"
 
 // chi2 and d chi2 / d theta at theta; lm_trial = 1 marks out-of-domain sub-problems in their
-// trial flags instead of the sticky error flags (sampler trajectories).
+// trial flags instead of the sticky error flags (sampler trajectories).  kind: TAIL_CHI2 or
+// TAIL_CHECK.
 static apx_status grad_core(apx_problem* P, const double* theta, const float* data, const float* weight,
-                            double* grad, double* chi2, int lm_trial) {
+                            double* grad, double* chi2, int lm_trial, int kind) {
     const Plan& p = P->plan;
     hipStream_t st = P->ctx->stream;
-    APXCHK(fwd_chi2(P, theta, data, weight, nullptr, chi2, lm_trial, 0, nullptr, 1));
-    HIPCHK(launch_flip_psf(p, st));
+    PrepIO pio = prep_at(theta);
+    pio.mark = lm_trial;
+    pio.flip = 1;
+    APXCHK(fwd_chi2(P, pio, data, weight, nullptr, tail_of(kind, chi2), 0, nullptr, 1));
     ConvIO io{};
     io.out = p.Abar;
     io.weight = weight;
@@ -2423,25 +2405,11 @@ static apx_status grad_core(apx_problem* P, const double* theta, const float* da
         TimeScope ts(P, APX_TIME_GRAD);
         HIPCHK(launch_grad_tiles(p, st));
     }
-    SegSum a = segsum_base();
-    a.src = p.grad_part;
-    a.seg = wsp<int>(P, "gcol_seg");
-    a.n_seg = (int)P->cols.size();
-    a.out = p.grad_col;
-    HIPCHK(launch_segsum(a, st));
     if (P->has_live_cols) {                 // live-PSF columns: -2 sum w r J from their convolutions
         APXCHK(psf_columns(P, weight, 0, nullptr));
         APXCHK(col_sums(P));
     }
-    SegSum g = segsum_base();
-    g.src = P->asrc;
-    g.seg = wsp<int>(P, "gr_seg");
-    g.idx = wsp<int>(P, "gr_idx");
-    g.wts = wsp<double>(P, "gr_w");
-    g.n_seg = P->n_par;
-    g.out = grad;
-    HIPCHK(launch_segsum(g, st));
-    return APX_OK;
+    return grad_sum(P, grad);
 }
 
 extern "C" {
@@ -2451,9 +2419,7 @@ apx_status apx_chi2_grad(apx_problem* P, const double* theta, const float* data,
     APXCHK(ready(P));
     if (!par_ok(P, theta) || !data || !weight || !par_ok(P, grad) || !chi2)
         return fail(P->ctx, APX_E_INVALID, "null pointer");
-    APXCHK(grad_core(P, theta, data, weight, grad, chi2, 0));
-    HIPCHK(launch_chi2_check(chi2, P->n_sub, P->plan.sticky, P->ctx->stream));
-    return APX_OK;
+    return grad_core(P, theta, data, weight, grad, chi2, 0, TAIL_CHECK);
 }
 
 }  // extern "C"
@@ -2503,7 +2469,7 @@ struct Nuts {
         HIPCHK(launch_nuts_copy(stop, 0, copy3(dst, src), n, st));
         HIPCHK(launch_hmc_matvec(p, F, dst.g, dst.r, -0.25 * v * step, st, stop));
         HIPCHK(launch_hmc_matvec(p, Ft, dst.r, dst.t, v * step, st, stop));
-        APXCHK(grad_core(P, dst.t, data, weight, dst.g, chi2, 1));
+        APXCHK(grad_core(P, dst.t, data, weight, dst.g, chi2, 1, TAIL_CHI2));
         HIPCHK(launch_hmc_matvec(p, F, dst.g, dst.r, -0.25 * v * step, st, stop));
         HIPCHK(launch_nuts_leaf(p, dev, chi2, dst.r, st));
         return APX_OK;
@@ -2590,7 +2556,7 @@ static apx_status nuts_transition(Nuts& N, const NPoint& em, const NPoint& ep, d
         HIPCHK(hipMemcpyAsync(em.t, theta, n * sizeof(double), hipMemcpyDeviceToDevice, s));
         HIPCHK(hipMemcpyAsync(em.r, z, n * sizeof(double), hipMemcpyDeviceToDevice, s));
     }
-    APXCHK(grad_core(P, em.t, N.data, N.weight, em.g, N.chi2, first ? 0 : 1));
+    APXCHK(grad_core(P, em.t, N.data, N.weight, em.g, N.chi2, first ? 0 : 1, TAIL_CHI2));
     HIPCHK(launch_nuts_start(p, N.dev, N.chi2, em.r, u, s));
     HIPCHK(launch_nuts_copy(nullptr, 0, copy3(ep, em), n, s));
     int k = 1, depth = 0;
@@ -2726,13 +2692,13 @@ apx_status apx_hmc_run(apx_problem* P, const float* data, const float* weight, d
     double* Ft = p.M;                              // F^T (the Cholesky scratch is free here)
     HIPCHK(launch_hmc_transpose(p, F, Ft, st));
     // gradient at the start (an out-of-domain start raises the sticky flag)
-    APXCHK(grad_core(P, theta, data, weight, h.grad_cur, h.chi2_cur, 0));
+    APXCHK(grad_core(P, theta, data, weight, h.grad_cur, h.chi2_cur, 0, TAIL_CHI2));
     for (long long i = 0; i < n_samples; ++i) {
         HIPCHK(launch_hmc_begin(p, h, i, st));
         for (int l = 0; l < n_leapfrog; ++l) {
             HIPCHK(launch_hmc_matvec(p, F, l == 0 ? h.grad_cur : h.grad_new, h.r, -0.25 * step, st));
             HIPCHK(launch_hmc_matvec(p, Ft, h.r, h.theta, step, st));
-            APXCHK(grad_core(P, theta, data, weight, h.grad_new, h.chi2_new, 1));
+            APXCHK(grad_core(P, theta, data, weight, h.grad_new, h.chi2_new, 1, TAIL_CHI2));
             HIPCHK(launch_hmc_matvec(p, F, h.grad_new, h.r, -0.25 * step, st));
         }
         HIPCHK(launch_hmc_accept(p, h, i, st));
@@ -2745,8 +2711,9 @@ apx_status apx_render_vjp(apx_problem* P, const double* theta, const float* grad
     if (!par_ok(P, theta) || !grad_model || !par_ok(P, grad_theta)) return fail(P->ctx, APX_E_INVALID, "null pointer");
     const Plan& p = P->plan;
     hipStream_t st = P->ctx->stream;
-    APXCHK(prep(P, theta, 0, 0, nullptr, 1));
-    HIPCHK(launch_flip_psf(p, st));
+    PrepIO pio = prep_at(theta);
+    pio.flip = 1;
+    APXCHK(prep(P, pio, 0, nullptr, 1));
     ConvIO io{};
     io.out = p.Abar;
     io.seed = grad_model;
@@ -2756,12 +2723,6 @@ apx_status apx_render_vjp(apx_problem* P, const double* theta, const float* grad
         HIPCHK(launch_grad_tiles(p, st));
         HIPCHK(launch_seed_sums(p, grad_model, wsp<double>(P, "seed_part"), st));
     }
-    SegSum a = segsum_base();
-    a.src = p.grad_part;
-    a.seg = wsp<int>(P, "gcol_seg");
-    a.n_seg = (int)P->cols.size();
-    a.out = p.grad_col;
-    HIPCHK(launch_segsum(a, st));
     if (P->has_live_cols) {
         // live-PSF columns: sum seed J from their convolutions, with the residual buffer set
         // to -1/2 so that the gradient tables' weight -2 on sum w r J gives sum seed J
@@ -2769,37 +2730,28 @@ apx_status apx_render_vjp(apx_problem* P, const double* theta, const float* grad
         APXCHK(psf_columns(P, grad_model, 0, nullptr));
         APXCHK(col_sums(P));
     }
-    SegSum g = segsum_base();
-    g.src = P->asrc;
-    g.seg = wsp<int>(P, "gr_seg");
-    g.idx = wsp<int>(P, "gr_idx");
-    g.wts = wsp<double>(P, "gr_w");
-    g.n_seg = P->n_par;
-    g.out = grad_theta;
-    HIPCHK(launch_segsum(g, st));
-    return APX_OK;
+    return grad_sum(P, grad_theta);
 }
 
 apx_status apx_lm_init(apx_problem* P, const double* theta, const float* data, const float* weight,
                        apx_lm_state* state) {
     APXCHK(ready(P));
     if (!par_ok(P, theta) || !data || !weight || !state) return fail(P->ctx, APX_E_INVALID, "null pointer");
-    APXCHK(fwd_chi2(P, theta, data, weight, nullptr, P->chi2_sub, 0, 0, nullptr, 0));
-    HIPCHK(launch_lm_init(P->plan, P->chi2_sub, state, P->ctx->stream));
-    return APX_OK;
+    TailIO tail = tail_of(TAIL_INIT, P->chi2_sub);
+    tail.lm = state;
+    return fwd_chi2(P, prep_at(theta), data, weight, nullptr, tail, 0, nullptr, 0);
 }
 
 static apx_status lm_step_enqueue(apx_problem* P, const float* data, const float* weight, double* theta,
                                   apx_lm_state* state) {
     const Plan& p = P->plan;
     hipStream_t st = P->ctx->stream;
-    {
-        TimeScope ts(P, APX_TIME_LM);
-        if (P->large_subs.empty()) HIPCHK(launch_lm_begin(p, state, st));
-        else HIPCHK(launch_lm_begin_adopt(p, state, st));
-    }
-    // normal equations at theta for sub-problems whose last step was accepted
-    APXCHK(prep(P, theta, 0, 2, state, 1));
+    // the iteration's flags (and adopted steps), and the normal equations at theta for
+    // sub-problems whose last step was accepted
+    PrepIO pio = prep_at(theta);
+    pio.lm = state;
+    pio.adopt = P->large_subs.empty() ? 0 : 1;
+    APXCHK(prep(P, pio, 2, state, 1));
     APXCHK(jac_blocks(P, weight, state));
     APXCHK(normal_eq(P, weight, p.A, p.gvec, state));
     // damped solves
@@ -2808,17 +2760,14 @@ static apx_status lm_step_enqueue(apx_problem* P, const float* data, const float
         HIPCHK(launch_chol_small(p, wsp<int>(P, "small_subs"), (int)P->small_subs.size(), P->nmax_small, state, st));
         for (int s : P->large_subs) HIPCHK(launch_chol_large(p, s, P->subs[s].n, state, st));
     }
-    // trial
-    {
-        TimeScope ts(P, APX_TIME_LM);
-        HIPCHK(launch_lm_trial(p, theta, state, st));
-    }
-    APXCHK(fwd_chi2(P, p.theta_trial, data, weight, nullptr, P->chi2_trial, 1, 1, state, 0));
-    {
-        TimeScope ts(P, APX_TIME_LM);
-        HIPCHK(launch_lm_accept(p, P->chi2_trial, theta, state, st));
-    }
-    return APX_OK;
+    // the trial at theta + h, and its gain ratio
+    PrepIO trial = prep_at(theta);
+    trial.step = p.hvec;
+    trial.mark = 1;
+    TailIO tail = tail_of(TAIL_ACCEPT, P->chi2_trial);
+    tail.lm = state;
+    tail.theta = theta;
+    return fwd_chi2(P, trial, data, weight, nullptr, tail, 1, state, 0);
 }
 
 apx_status apx_lm_step(apx_problem* P, const float* data, const float* weight, double* theta,

@@ -264,7 +264,6 @@ struct Plan {
     double* col_sum;          // 2 per column
     double* pair_part;        // pair tiles
     double* grad_part;        // gradient partials (per group: ncols x ntiles)
-    double* grad_col;         // per column
     double* A;                // internal J^T W J blocks (per sub)
     double* gvec;             // internal J^T W r [n_par]
     double* M;                // Cholesky factor (per sub)
@@ -344,13 +343,20 @@ __device__ __forceinline__ bool sub_skipped(const Plan& p, int sub, int mode, co
 
 // Launchers (each returns hipGetLastError()) ----------------------------------------
 // k_model.hip
-hipError_t launch_prep(const Plan& p, const double* theta, int lm_trial, hipStream_t st);
+struct PrepIO {
+    const double* theta;      // [n_par]
+    const double* step;       // LM trial: evaluate at theta + step (also written to theta_trial); null otherwise
+    int mark;                 // 1: out-of-domain parameters mark their sub-problem's trial, 0: the sticky flag
+    int flip;                 // also the flipped stamps (adjoint)
+    apx_lm_state* lm;         // start of an LM iteration: clear its flags; null otherwise
+    int adopt;                // ... and let large sub-problems take a step solved ahead (step, pred, lambda, retries)
+};
+hipError_t launch_prep(const Plan& p, const PrepIO& io, hipStream_t st);
 // skip_mode: 0 none, 1 skip sub-problems without a valid trial, 2 skip those that keep J
 hipError_t launch_render_mode(const Plan& p, int skip_mode, const apx_lm_state* lm, hipStream_t st);
 hipError_t launch_render64(const Plan& p, int skip_mode, const apx_lm_state* lm, hipStream_t st);
 hipError_t launch_deriv(const Plan& p, const apx_lm_state* lm, hipStream_t st);
 hipError_t launch_grad_tiles(const Plan& p, hipStream_t st);
-hipError_t launch_flip_psf(const Plan& p, hipStream_t st);
 
 // k_adapt.hip: error budgets, choices and values of the adaptive integration at the
 // current theta (after launch_prep); want_grad also forms the refined pixels' derivatives
@@ -403,16 +409,25 @@ hipError_t launch_gram4(const Plan& p, const PairLaunch& L, const float* weight,
 // L.items: items of two groups with L.tm = the block shape (0..N_CROSS - 1)
 hipError_t launch_cross4(const Plan& p, const PairLaunch& L, const float* weight,
                          const apx_lm_state* lm, hipStream_t st);
-struct SegSum {
-    const double* src; int stride, comp;
-    const int* seg; const int* idx; const double* wts;
-    int n_seg;
-    double* out; int ostride, ocomp;
-    double scale;
-    const int* seg_sub; const apx_lm_state* lm;
-    int ncomp;                                // components comp .. comp + ncomp - 1 (0: one)
+// Sums of the convolution partials.  Per column, sum w r J and sum w J over its items.
+hipError_t launch_col_sums(const Plan& p, const int* col_seg, const int* col_idx, hipStream_t st);
+// After the model convolution: per image, sum w r^2, sum w r, sum w over its items
+// (img_items[k] = first, end) into img_sum, chi^2 of each sub-problem over its
+// images (sub_img[chi_seg[s]] ...), and what follows it.
+enum TailKind { TAIL_CHI2 = 0, TAIL_CHECK = 1, TAIL_INIT = 2, TAIL_ACCEPT = 3 };
+struct TailIO {
+    const int2* img_items;    // [n_images]
+    const int* chi_seg;       // [n_sub + 1]
+    const int* sub_img;
+    double* chi2;             // [n_sub]
+    int kind;                 // CHECK: raise the sticky flag on a non-finite chi^2; INIT: fresh LM states;
+                              // ACCEPT: gain ratio, accept or reject, lambda, theta update
+    apx_lm_state* lm;
+    double* theta;
 };
-hipError_t launch_segsum(const SegSum& a, hipStream_t st);
+hipError_t launch_tail(const Plan& p, const TailIO& io, hipStream_t st);
+// J^T W J and J^T W r from their partials: entry e of A sums src[ent_src[k]], k in
+// [ent_off[e], ent_off[e + 1]), in order; g[q] sums g_w[k] src[g_idx[k]] over g_seg.
 struct AsmA {
     const long long* ent_off; const int* ent_sub; const int* ent_row; const int* ent_col;
     const long long* ent_src;
@@ -420,29 +435,33 @@ struct AsmA {
     const double* src;
     const DSub* subs;
     double* out;
+    const int* g_seg; const int* g_idx; const double* g_w; const int* g_sub;
+    int n_par;
+    double* g;
     const apx_lm_state* lm;
 };
-hipError_t launch_assemble_A(const AsmA& a, hipStream_t st);
+hipError_t launch_assemble(const AsmA& a, hipStream_t st);
+// Gradient per theta index: the sources gr_idx of gr_seg, weighted; a source in [col0, col0 +
+// n_cols) stands for the sum of that column's tile partials (gcol_seg), others are entries of src.
+struct GradSum {
+    const double* src; const double* grad_part;
+    const int* gr_seg; const int* gr_idx; const double* gr_w; const int* gcol_seg;
+    int col0, n_cols, n_par;
+    double* out;
+};
+hipError_t launch_grad_sum(const GradSum& a, hipStream_t st);
 hipError_t launch_fill(double* x, long long n, double v, hipStream_t st);
 hipError_t launch_fill_f(float* x, long long n, float v, hipStream_t st);
 hipError_t launch_jscatter(const Plan& p, const int* par_off, const int* par_cols,
                            const int* par_sky_off, const int* par_sky, float* Jd, long long ldJ,
                            hipStream_t st);
-hipError_t launch_chi2_check(const double* chi2, int n, int* sticky, hipStream_t st);
 
 // k_lm.hip
-hipError_t launch_lm_begin(const Plan& p, apx_lm_state* lm, hipStream_t st);
-// large sub-problems whose step was solved ahead take it (step, pred, lambda, retries)
-hipError_t launch_lm_begin_adopt(const Plan& p, apx_lm_state* lm, hipStream_t st);
-hipError_t launch_lm_init(const Plan& p, const double* chi2_sub, apx_lm_state* lm, hipStream_t st);
 hipError_t launch_chol_small(const Plan& p, const int* small_subs, int n_small, int nmax,
                              apx_lm_state* lm, hipStream_t st);
 hipError_t launch_chol_large(const Plan& p, int sub, int n, apx_lm_state* lm, hipStream_t st);
 hipError_t launch_chol_reset(const Plan& p, int sub, hipStream_t st);
 hipError_t launch_chol_blocks(const Plan& p, int sub, int n, hipStream_t st);
-hipError_t launch_lm_trial(const Plan& p, const double* theta, apx_lm_state* lm, hipStream_t st);
-hipError_t launch_lm_accept(const Plan& p, const double* chi2_trial, double* theta,
-                            apx_lm_state* lm, hipStream_t st);
 
 // k_cov.hip
 // factor / forward_only: F = L^{-T} (A = L L^T) instead of A^{-1}, so that F F^T = A^{-1}

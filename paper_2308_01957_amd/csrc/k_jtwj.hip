@@ -10,6 +10,7 @@
 #include <type_traits>
 
 #include "apx_internal.h"
+#include "lm_state.h"
 
 namespace apx {
 
@@ -475,41 +476,138 @@ hipError_t launch_pairs(const Plan& p, const PairLaunch& L, const float* weight,
     return hipGetLastError();
 }
 
-// out[s*ostride + ocomp] = scale * sum_k wts[k] * src[(idx ? idx[k] : k) * stride + comp],
-// k in [seg[s], seg[s+1]).  One wave per segment: lane l sums entries l, l+64, ... in
-// order, then a fixed butterfly combines the lanes -- the same order on every run.
-// Segments of sub-problems that keep their Jacobian are skipped when lm is given.  With
-// ncomp > 1 one launch sums components comp + q into ocomp + q (q < ncomp), one wave per
-// (segment, component), each in the same order as a launch of its own.
-__global__ __launch_bounds__(256) void k_segsum(SegSum a) {
-    const int nc = a.ncomp > 1 ? a.ncomp : 1;
-    const int sf = blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int lane = threadIdx.x & 63;
-    if (sf >= a.n_seg * nc) return;
-    const int s = sf / nc, q = sf - s * nc;
-    if (a.lm && a.seg_sub && a.lm[a.seg_sub[s]].need_jac == 0) return;
+// Sum over entries b + lane, b + lane + 64, ... < e of load(k), four loads of a lane in flight:
+// the same order on every run.
+template <class F>
+__device__ __forceinline__ double lane_sum(int b, int e, F&& load) {
     double acc = 0.0;
-    for (int k = a.seg[s] + lane; k < a.seg[s + 1]; k += 64) {
-        const long long j = a.idx ? (long long)a.idx[k] : (long long)k;
-        const double v = a.src[j * a.stride + a.comp + q];
-        acc += a.wts ? a.wts[k] * v : v;
+    for (int k = b + (int)(threadIdx.x & 63); k < e; k += 256) {
+        double v[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[q] = k + 64 * q < e ? load(k + 64 * q) : 0.0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc += v[q];
     }
-    for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
-    if (lane == 0) a.out[(long long)s * a.ostride + a.ocomp + q] = acc * a.scale;
+    return acc;
+}
+__device__ __forceinline__ double butterfly(double v) {
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    return v;
 }
 
-hipError_t launch_segsum(const SegSum& a, hipStream_t st) {
-    const long long n = (long long)a.n_seg * (a.ncomp > 1 ? a.ncomp : 1);
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_segsum, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, st, a);
+// One wave per (column, component).
+__global__ __launch_bounds__(256) void k_col_sums(Plan p, const int* __restrict__ col_seg,
+                                                  const int* __restrict__ col_idx) {
+    const int sf = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (sf >= 2 * p.n_cols) return;
+    const int c = sf >> 1, q = sf & 1;
+    const double v = butterfly(lane_sum(col_seg[c], col_seg[c + 1], [&](int k) { return p.jcol_part[2LL * col_idx[k] + q]; }));
+    if ((threadIdx.x & 63) == 0) p.col_sum[2 * c + q] = v;
+}
+
+hipError_t launch_col_sums(const Plan& p, const int* col_seg, const int* col_idx, hipStream_t st) {
+    if (p.n_cols <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_col_sums, dim3((2 * p.n_cols + 3) / 4), dim3(256), 0, st, p, col_seg, col_idx);
+    return hipGetLastError();
+}
+
+// One workgroup per sub-problem: for each of its images, every thread takes items tid, tid +
+// 256, ... (all three components), then a fixed butterfly per wave and the four waves in order;
+// thread 0 adds the images' chi^2 in order.  One launch instead of four (image sums, chi^2,
+// check or accept): at 64 x 64 they were 1.8 us of work and 5 us of launch each.
+__global__ __launch_bounds__(256) void k_tail(Plan p, TailIO io) {
+    __shared__ double red[4][3];
+    __shared__ int acc_flag;
+    const int s = blockIdx.x, lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    double chi = 0.0;                                    // thread 0's
+    for (int q = io.chi_seg[s]; q < io.chi_seg[s + 1]; ++q) {
+        const int k = io.sub_img[q];
+        const int2 it = io.img_items[k];
+        double v0 = 0.0, v1 = 0.0, v2 = 0.0;
+        for (int i = it.x + (int)threadIdx.x; i < it.y; i += 512) {
+            const double* a = p.fwd_part + 3LL * i;
+            const bool two = i + 256 < it.y;
+            const double a0 = a[0], a1 = a[1], a2 = a[2];
+            const double b0 = two ? a[768] : 0.0, b1 = two ? a[769] : 0.0, b2 = two ? a[770] : 0.0;
+            v0 += a0;
+            v1 += a1;
+            v2 += a2;
+            v0 += b0;
+            v1 += b1;
+            v2 += b2;
+        }
+        v0 = butterfly(v0);
+        v1 = butterfly(v1);
+        v2 = butterfly(v2);
+        if (lane == 0) {
+            red[wv][0] = v0;
+            red[wv][1] = v1;
+            red[wv][2] = v2;
+        }
+        __syncthreads();
+        if (threadIdx.x < 3) {
+            const int c = threadIdx.x;
+            const double v = ((red[0][c] + red[1][c]) + red[2][c]) + red[3][c];
+            p.img_sum[3 * k + c] = v;
+            chi += v;
+        }
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) {
+        if (io.chi2) io.chi2[s] = chi;
+        if (io.kind == TAIL_CHECK && !isfinite(chi)) atomicOr(p.sticky, FLAG_NONFINITE);
+        if (io.kind == TAIL_INIT) lm_init_state(p, s, chi, io.lm);
+        acc_flag = io.kind == TAIL_ACCEPT ? lm_accept_state(p, s, chi, io.lm) : 0;
+    }
+    if (io.kind != TAIL_ACCEPT) return;
+    __syncthreads();
+    if (acc_flag) {
+        const DSub sb = p.subs[s];
+        for (int k = threadIdx.x; k < sb.n; k += 256) io.theta[sb.p0 + k] = p.theta_trial[sb.p0 + k];
+    }
+}
+
+hipError_t launch_tail(const Plan& p, const TailIO& io, hipStream_t st) {
+    hipLaunchKernelGGL(k_tail, dim3(p.n_sub), dim3(256), 0, st, p, io);
+    return hipGetLastError();
+}
+
+// One wave per theta index.
+__global__ __launch_bounds__(256) void k_grad_sum(GradSum a) {
+    const int k = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (k >= a.n_par) return;
+    const int lane = threadIdx.x & 63;
+    double acc = 0.0;
+    for (int q = a.gr_seg[k]; q < a.gr_seg[k + 1]; ++q) {
+        const int j = a.gr_idx[q], c = j - a.col0;
+        const double w = a.gr_w[q];
+        if (c >= 0 && c < a.n_cols) acc += w * lane_sum(a.gcol_seg[c], a.gcol_seg[c + 1], [&](int i) { return a.grad_part[i]; });
+        else if (lane == 0) acc += w * a.src[j];
+    }
+    acc = butterfly(acc);
+    if (lane == 0) a.out[k] = acc;
+}
+
+hipError_t launch_grad_sum(const GradSum& a, hipStream_t st) {
+    if (a.n_par <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_grad_sum, dim3((a.n_par + 3) / 4), dim3(256), 0, st, a);
     return hipGetLastError();
 }
 
 // J^T W J assembly: every upper entry (sub, a <= b) sums its sources in list order and
-// is written to both (a, b) and (b, a) of its sub-problem's row-major block.
+// is written to both (a, b) and (b, a) of its sub-problem's row-major block.  The blocks after
+// the entries' take one theta index each: J^T W r (one wave, lanes strided, fixed butterfly).
+// Sub-problems that keep their Jacobian are skipped when lm is given.
 constexpr int ASM_B = 8;
-__global__ void k_assemble_A(AsmA a) {
-    const long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+__global__ __launch_bounds__(64) void k_assemble(AsmA a, int ent_blocks) {
+    if ((int)blockIdx.x >= ent_blocks) {
+        const int k = (int)blockIdx.x - ent_blocks;
+        if (a.lm && a.lm[a.g_sub[k]].need_jac == 0) return;
+        const double v = butterfly(lane_sum(a.g_seg[k], a.g_seg[k + 1], [&](int i) { return a.g_w[i] * a.src[a.g_idx[i]]; }));
+        if (threadIdx.x == 0) a.g[k] = v;
+        return;
+    }
+    const long long e = (long long)blockIdx.x * 64 + threadIdx.x;
     if (e >= a.n_ent) return;
     const int s = a.ent_sub[e];
     if (a.lm && a.lm[s].need_jac == 0) return;
@@ -533,9 +631,10 @@ __global__ void k_assemble_A(AsmA a) {
     a.out[sb.a_off + (long long)c * sb.n + r] = acc;
 }
 
-hipError_t launch_assemble_A(const AsmA& a, hipStream_t st) {
-    if (a.n_ent <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_assemble_A, dim3((unsigned)((a.n_ent + 63) / 64)), dim3(64), 0, st, a);
+hipError_t launch_assemble(const AsmA& a, hipStream_t st) {
+    const long long eb = (a.n_ent + 63) / 64;
+    if (eb + a.n_par <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_assemble, dim3((unsigned)(eb + a.n_par)), dim3(64), 0, st, a, (int)eb);
     return hipGetLastError();
 }
 
@@ -606,18 +705,6 @@ hipError_t launch_fill(double* x, long long n, double v, hipStream_t st) {
     long long b = (n + 255) / 256;
     if (b > 65536) b = 65536;
     hipLaunchKernelGGL(k_fill_d, dim3((unsigned)b), dim3(256), 0, st, x, n, v);
-    return hipGetLastError();
-}
-
-// Sticky non-finite flag from per-sub chi^2 values.
-__global__ void k_chi2_check(const double* chi2, int n, int* sticky) {
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s < n && !isfinite(chi2[s])) atomicOr(sticky, FLAG_NONFINITE);
-}
-
-hipError_t launch_chi2_check(const double* chi2, int n, int* sticky, hipStream_t st) {
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_chi2_check, dim3((n + 255) / 256), dim3(256), 0, st, chi2, n, sticky);
     return hipGetLastError();
 }
 

@@ -1,8 +1,9 @@
 // Levenberg-Marquardt kernels (§2.5): Marquardt-damped normal equations solved by FP64
 // Cholesky on the device, with the damping raised and the factorisation retried when a
-// pivot is not positive (the step never meets a singular matrix), the trial step, and
-// the gain-ratio accept/reject with lambda update.  All control stays on the device so
-// an iteration can be captured in a HIP graph; every sub-problem carries its own state.
+// pivot is not positive (the step never meets a singular matrix).  The trial step starts the
+// next evaluation (k_prep); the gain ratio, accept or reject and the lambda update end it
+// (k_tail, lm_state.h).  All control stays on the device so an iteration can be captured in
+// a HIP graph; every sub-problem carries its own state.
 #include "apx_internal.h"
 
 namespace apx {
@@ -15,189 +16,6 @@ __device__ __forceinline__ double lm_wave_max(double v) {
     for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
     return v;
 }
-
-// Start of an iteration: clear the per-iteration flags of both solve copies and decide
-// whether a large sub-problem takes the step solved ahead: the same A (its last trial was
-// rejected, so no new normal equations) and the lambda that solve started from.
-__global__ void k_lm_begin(Plan p, const apx_lm_state* lm) {
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= p.n_sub) return;
-    LMFlags f;
-    f.chol_done = 0;
-    f.chol_fail = 0;
-    f.trial_bad = 0;
-    f.skip = 0;
-    f.subst_fail = 0;
-    f.rhs_folded = 0;
-    f.adopted = 0;
-    p.lmf[p.n_sub + s] = f;
-    const LMSpec sp = p.spec[s];
-    f.adopted = p.subs[s].large && sp.valid && lm[s].need_jac == 0 && lm[s].lambda == sp.lam_start;
-    p.lmf[s] = f;
-}
-
-hipError_t launch_lm_begin(const Plan& p, apx_lm_state* lm, hipStream_t st) {
-    hipLaunchKernelGGL(k_lm_begin, dim3((p.n_sub + 255) / 256), dim3(256), 0, st, p, lm);
-    return hipGetLastError();
-}
-
-// k_lm_begin, then adoption, in one launch with one wave per sub-problem (for problems with
-// a large sub-problem, whose solves are made ahead): lane 0 sets the flags as k_lm_begin does;
-// an adopting sub-problem then takes the step, its predicted decrease, lambda and retry
-// count from the solve made ahead (exactly what solving now would give: same A, D, g and
-// starting lambda, same kernels), and the record is used up.
-__global__ __launch_bounds__(64) void k_lm_begin_adopt(Plan p, apx_lm_state* lm) {
-    const int s = blockIdx.x;
-    int adopted = 0;
-    if (threadIdx.x == 0) {
-        LMFlags f;
-        f.chol_done = 0;
-        f.chol_fail = 0;
-        f.trial_bad = 0;
-        f.skip = 0;
-        f.subst_fail = 0;
-        f.rhs_folded = 0;
-        f.adopted = 0;
-        p.lmf[p.n_sub + s] = f;
-        const LMSpec sp = p.spec[s];
-        f.adopted = p.subs[s].large && sp.valid && lm[s].need_jac == 0 && lm[s].lambda == sp.lam_start;
-        p.lmf[s] = f;
-        adopted = f.adopted;
-    }
-    adopted = __shfl(adopted, 0, 64);
-    if (!adopted) return;
-    const DSub sb = p.subs[s];
-    for (int i = (int)threadIdx.x; i < sb.n; i += 64) p.hvec[sb.p0 + i] = p.hvec[p.n_par + sb.p0 + i];
-    if (threadIdx.x == 0) {
-        const LMSpec sp = p.spec[s];
-        lm[s].pred = sp.pred;
-        lm[s].lambda = sp.lam_final;
-        lm[s].n_chol_retry += sp.retries;
-        p.lmf[s].chol_done = sp.done;
-        p.spec[s].valid = 0;
-    }
-}
-
-hipError_t launch_lm_begin_adopt(const Plan& p, apx_lm_state* lm, hipStream_t st) {
-    hipLaunchKernelGGL(k_lm_begin_adopt, dim3(p.n_sub), dim3(64), 0, st, p, lm);
-    return hipGetLastError();
-}
-
-__global__ void k_lm_init(Plan p, const double* chi2_sub, apx_lm_state* lm) {
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= p.n_sub) return;
-    apx_lm_state st;
-    st.lambda = APX_LM_LAMBDA0;
-    st.chi2 = chi2_sub[s];
-    st.chi2_trial = 0.0;
-    st.pred = 0.0;
-    st.rho = 0.0;
-    st.need_jac = 1;
-    st.accepted = 0;
-    st.n_accept = 0;
-    st.n_reject = 0;
-    st.n_chol_retry = 0;
-    st.status = isfinite(st.chi2) ? APX_OK : APX_E_NONFINITE;
-    lm[s] = st;
-    p.spec[s].valid = 0;
-}
-
-hipError_t launch_lm_init(const Plan& p, const double* chi2_sub, apx_lm_state* lm, hipStream_t st) {
-    hipLaunchKernelGGL(k_lm_init, dim3((p.n_sub + 255) / 256), dim3(256), 0, st, p, chi2_sub, lm);
-    return hipGetLastError();
-}
-
-// -------------------------------------------------------------- small sub-problems
-// One wave64 per sub-problem (n <= 64): the damped matrix, its factor and the step
-// live in LDS; the retries happen inside the kernel.
-__global__ __launch_bounds__(64) void k_chol_small(Plan p, const int* __restrict__ small_subs,
-                                                   int nmax, apx_lm_state* lm) {
-    extern __shared__ double sm[];
-    const int s = small_subs[blockIdx.x];
-    const DSub sb = p.subs[s];
-    const int n = sb.n, ld = nmax + 1;
-    double* M = sm;
-    double* y = sm + (long long)nmax * ld;
-    const int i = threadIdx.x;
-    const double* A = p.A + sb.a_off;
-    const double* g = p.gvec + sb.p0;
-    if (n == 0) {
-        if (i == 0) { p.lmf[s].chol_done = 1; lm[s].pred = 0.0; }
-        return;
-    }
-    const double di = i < n ? A[(long long)i * n + i] : 0.0;
-    const double dmax = lm_wave_max(i < n ? di : -1e308);
-    const double Di = fmax(di, APX_LM_DAMP_FLOOR * dmax);
-    double lam = lm[s].lambda;
-    int done = 0, retries = 0;
-    for (int att = 0; att < APX_LM_ATTEMPTS; ++att) {
-        if (i < n)
-            for (int j = 0; j <= i; ++j) M[i * ld + j] = A[(long long)i * n + j] + (i == j ? lam * Di : 0.0);
-        __syncthreads();
-        bool ok = true;
-        for (int k = 0; k < n; ++k) {
-            const double piv = M[k * ld + k];
-            if (!(piv > 0.0) || !isfinite(piv)) { ok = false; break; }
-            const double lkk = sqrt(piv);
-            __syncthreads();
-            if (i == k) M[k * ld + k] = lkk;
-            if (i > k && i < n) M[i * ld + k] = M[i * ld + k] / lkk;
-            __syncthreads();
-            if (i > k && i < n) {
-                const double lik = M[i * ld + k];
-                for (int j = k + 1; j <= i; ++j) M[i * ld + j] -= lik * M[j * ld + k];
-            }
-            __syncthreads();
-        }
-        __syncthreads();
-        if (ok) { done = 1; break; }
-        lam = fmin(lam * APX_LM_UP, APX_LM_LAMBDA_MAX);
-        ++retries;
-    }
-    double h = 0.0;
-    if (done) {
-        if (i < n) y[i] = g[i];
-        __syncthreads();
-        for (int k = 0; k < n; ++k) {
-            if (i == k) y[k] = y[k] / M[k * ld + k];
-            __syncthreads();
-            if (i > k && i < n) y[i] -= M[i * ld + k] * y[k];
-            __syncthreads();
-        }
-        for (int k = n - 1; k >= 0; --k) {
-            if (i == k) y[k] = y[k] / M[k * ld + k];
-            __syncthreads();
-            if (i < k) y[i] -= M[k * ld + i] * y[k];
-            __syncthreads();
-        }
-        if (i < n) h = y[i];
-    }
-    const double pr = lm_wave_sum(i < n ? h * (lam * Di * h + g[i]) : 0.0);
-    if (i < n) {
-        p.hvec[sb.p0 + i] = h;
-        p.Ddiag[sb.p0 + i] = Di;
-    }
-    if (i == 0) {
-        lm[s].lambda = lam;
-        lm[s].pred = pr;
-        lm[s].n_chol_retry += retries;
-        p.lmf[s].chol_done = done;
-    }
-}
-
-hipError_t launch_chol_small(const Plan& p, const int* small_subs, int n_small, int nmax,
-                             apx_lm_state* lm, hipStream_t st) {
-    if (n_small <= 0) return hipSuccess;
-    const size_t lds = (size_t)nmax * (nmax + 1) * sizeof(double) + (size_t)nmax * sizeof(double);
-    hipLaunchKernelGGL(k_chol_small, dim3(n_small), dim3(64), lds, st, p, small_subs, nmax, lm);
-    return hipGetLastError();
-}
-
-// -------------------------------------------------------------- large sub-problems
-// Right-looking blocked Cholesky (block CHOL_NB).  The first attempt runs as a sequence
-// of launches (panel, trailing update) so the update spreads over the chip; a failed
-// attempt is retried (lambda *= UP) by one fallback workgroup that factors the whole
-// matrix itself -- the rare path costs one launch that exits at once when unused.
 
 // 1/sqrt(x) for positive normal x: the hardware estimate refined by two Newton steps
 // y <- y (3 - x y^2) / 2 (each roughly doubles the correct bits), a short dependent chain
@@ -216,6 +34,131 @@ __device__ __forceinline__ double lane_bcast(double v, int src) {
     const int hi = __builtin_amdgcn_readlane(__double2hiint(v), src);
     return __hiloint2double(hi, lo);
 }
+
+// -------------------------------------------------------------- small sub-problems
+// One wave64 per sub-problem (n <= 64), one row of the damped matrix per lane in registers (N
+// columns, N the next of a few sizes >= n, padded with identity rows): a right-looking Cholesky
+// whose pivot and column entries come by readlane, so no column step waits for LDS or a
+// barrier.  The factor goes through LDS once, for the back substitution's columns.  Latency
+// of its serial chain bounds it: with the rows in LDS and each step behind three barriers the
+// largest of 768 cutouts (36 parameters) took 64 us and one 8-parameter system 10 us.  The
+// retries happen inside the kernel.
+template <int N>
+__device__ __forceinline__ bool chol_rows(const double* __restrict__ A, int n, double lamD, double (&a)[N], double& rinv) {
+    const int i = threadIdx.x;
+#pragma unroll
+    for (int j = 0; j < N; ++j) a[j] = (i < n && j < n) ? A[(long long)i * n + j] : (i == j ? 1.0 : 0.0);
+#pragma unroll
+    for (int j = 0; j < N; ++j)
+        if (i == j && j < n) a[j] += lamD;
+    bool ok = true;
+    rinv = 1.0;
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        double piv = lane_bcast(a[k], k);
+        // a failed pivot is recorded and replaced by 1 so the (discarded) factor stays finite
+        if (!(piv > 0.0) || !isfinite(piv)) { ok = false; piv = 1.0; }
+        const double r = rsqrt_f64(piv);
+        const double l = i > k ? a[k] * r : 0.0;
+        a[k] = i > k ? l : (i == k ? piv * r : a[k]);
+        if (i == k) rinv = r;
+#pragma unroll
+        for (int j = k + 1; j < N; ++j) a[j] = fma(-l, lane_bcast(l, j), a[j]);
+    }
+    return ok;
+}
+
+template <int N>
+__device__ __forceinline__ void chol_small_n(const Plan& p, int s, const DSub& sb, apx_lm_state* lm, double* sm) {
+    const int n = sb.n, i = threadIdx.x;
+    const double* A = p.A + sb.a_off;
+    const double gi = i < n ? p.gvec[sb.p0 + i] : 0.0;
+    const double di = i < n ? A[(long long)i * n + i] : 0.0;
+    double lam = lm[s].lambda;
+    const double dmax = lm_wave_max(i < n ? di : -1e308);
+    const double Di = fmax(di, APX_LM_DAMP_FLOOR * dmax);
+    double a[N], rinv = 1.0;
+    int done = 0, retries = 0;
+    for (int att = 0; att < APX_LM_ATTEMPTS; ++att) {
+        if (chol_rows<N>(A, n, lam * Di, a, rinv)) { done = 1; break; }
+        lam = fmin(lam * APX_LM_UP, APX_LM_LAMBDA_MAX);
+        ++retries;
+    }
+    double h = 0.0;
+    if (done) {
+        double y = gi;
+#pragma unroll
+        for (int k = 0; k < N; ++k) {                    // L y = g
+            const double yk = lane_bcast(y, k) * lane_bcast(rinv, k);
+            y = i == k ? yk : (i > k ? fma(-a[k], yk, y) : y);
+        }
+        if (i < N) {
+#pragma unroll
+            for (int j = 0; j < N; ++j) sm[i * (N + 1) + j] = a[j];
+        }
+        __syncthreads();
+        const double* col = sm + (i < N ? i : 0);        // column i of L
+#pragma unroll
+        for (int k = N - 1; k >= 0; --k) {               // L^T h = y
+            const double hk = lane_bcast(y, k) * lane_bcast(rinv, k);
+            y = i == k ? hk : (i < k ? fma(-col[k * (N + 1)], hk, y) : y);
+        }
+        if (i < n) h = y;
+    }
+    const double pr = lm_wave_sum(i < n ? h * (lam * Di * h + gi) : 0.0);
+    if (i < n) {
+        p.hvec[sb.p0 + i] = h;
+        p.Ddiag[sb.p0 + i] = Di;
+    }
+    if (i == 0) {
+        lm[s].lambda = lam;
+        lm[s].pred = pr;
+        lm[s].n_chol_retry += retries;
+        p.lmf[s].chol_done = done;
+    }
+}
+
+// NMAX: the largest size of the launch (the 64-column rows would cost every sub-problem of a
+// batch their registers).
+template <int NMAX>
+__global__ __launch_bounds__(64) void k_chol_small(Plan p, const int* __restrict__ small_subs, apx_lm_state* lm) {
+    extern __shared__ double sm[];
+    const int s = small_subs[blockIdx.x];
+    const DSub sb = p.subs[s];
+    if (sb.n == 0) {
+        if (threadIdx.x == 0) { p.lmf[s].chol_done = 1; lm[s].pred = 0.0; }
+        return;
+    }
+    if (sb.n <= 8) return chol_small_n<8>(p, s, sb, lm, sm);
+    if constexpr (NMAX > 8)
+        if (sb.n <= 16) return chol_small_n<16>(p, s, sb, lm, sm);
+    if constexpr (NMAX > 16)
+        if (sb.n <= 24) return chol_small_n<24>(p, s, sb, lm, sm);
+    if constexpr (NMAX > 24)
+        if (sb.n <= 40) return chol_small_n<40>(p, s, sb, lm, sm);
+    if constexpr (NMAX > 40) chol_small_n<64>(p, s, sb, lm, sm);
+}
+
+hipError_t launch_chol_small(const Plan& p, const int* small_subs, int n_small, int nmax,
+                             apx_lm_state* lm, hipStream_t st) {
+    if (n_small <= 0) return hipSuccess;
+#define APX_CS(N)                                                                                             \
+    hipLaunchKernelGGL(k_chol_small<N>, dim3(n_small), dim3(64), (size_t)(N) * ((N) + 1) * sizeof(double), st, p, \
+                       small_subs, lm)
+    if (nmax <= 8) APX_CS(8);
+    else if (nmax <= 16) APX_CS(16);
+    else if (nmax <= 24) APX_CS(24);
+    else if (nmax <= 40) APX_CS(40);
+    else APX_CS(64);
+#undef APX_CS
+    return hipGetLastError();
+}
+
+// -------------------------------------------------------------- large sub-problems
+// Right-looking blocked Cholesky (block CHOL_NB).  The first attempt runs as a sequence
+// of launches (panel, trailing update) so the update spreads over the chip; a failed
+// attempt is retried (lambda *= UP) by one fallback workgroup that factors the whole
+// matrix itself -- the rare path costs one launch that exits at once when unused.
 
 // Blocked factorisation of one CHOL_NB x CHOL_NB diagonal block in LDS, by the whole
 // 256-thread workgroup (every thread must call it).  The block is taken in four 16-column
@@ -966,72 +909,6 @@ hipError_t launch_chol_large(const Plan& p, int s, int n, apx_lm_state* lm, hipS
     hipLaunchKernelGGL(k_subst_fwd, dim3(nblk, 2), dim3(256), 0, st, p, s);
     hipLaunchKernelGGL(k_subst_bwd, dim3(nblk, 2), dim3(256), 0, st, p, s);
     hipLaunchKernelGGL(k_subst_finish, dim3(1, 2), dim3(256), 0, st, p, s, lm);
-    return hipGetLastError();
-}
-
-// -------------------------------------------------------------------- trial/accept
-__global__ void k_lm_trial(Plan p, const double* __restrict__ theta) {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= p.n_par) return;
-    const int s = p.par_sub[k];
-    double v = theta[k];
-    if (s >= 0 && p.lmf[s].chol_done) v += p.hvec[k];
-    p.theta_trial[k] = v;
-}
-
-hipError_t launch_lm_trial(const Plan& p, const double* theta, apx_lm_state* lm, hipStream_t st) {
-    (void)lm;
-    if (p.n_par == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_lm_trial, dim3((p.n_par + 255) / 256), dim3(256), 0, st, p, theta);
-    return hipGetLastError();
-}
-
-__global__ void k_lm_accept(Plan p, const double* __restrict__ chi2_trial, double* theta,
-                            apx_lm_state* lm) {
-    __shared__ int acc_flag;
-    const int s = blockIdx.x;
-    const DSub sb = p.subs[s];
-    if (threadIdx.x == 0) {
-        apx_lm_state st = lm[s];
-        const LMFlags f = p.lmf[s];
-        int accept = 0;
-        if (!f.chol_done) {
-            st.chi2_trial = __builtin_nan("");
-            st.rho = __builtin_nan("");
-        } else if (f.trial_bad) {
-            st.chi2_trial = __builtin_inf();
-            st.rho = -__builtin_inf();
-            st.lambda = fmin(st.lambda * APX_LM_UP, APX_LM_LAMBDA_MAX);
-        } else {
-            const double c2t = chi2_trial[s];
-            const double rho = st.pred != 0.0 ? (st.chi2 - c2t) / st.pred : __builtin_nan("");
-            st.chi2_trial = c2t;
-            st.rho = rho;
-            if (rho > APX_LM_EPS4) {
-                accept = 1;
-                st.chi2 = c2t;
-                st.lambda = fmax(st.lambda / APX_LM_DOWN, APX_LM_LAMBDA_MIN);
-            } else {
-                st.lambda = fmin(st.lambda * APX_LM_UP, APX_LM_LAMBDA_MAX);
-            }
-        }
-        st.accepted = accept;
-        st.need_jac = accept;
-        if (accept) st.n_accept += 1; else st.n_reject += 1;
-        lm[s] = st;
-        // a step solved ahead stays usable only after a rejection of a solved trial (same A,
-        // lambda raised exactly once)
-        if (accept || !f.chol_done) p.spec[s].valid = 0;
-        acc_flag = accept;
-    }
-    __syncthreads();
-    if (acc_flag)
-        for (int k = threadIdx.x; k < sb.n; k += blockDim.x) theta[sb.p0 + k] = p.theta_trial[sb.p0 + k];
-}
-
-hipError_t launch_lm_accept(const Plan& p, const double* chi2_trial, double* theta,
-                            apx_lm_state* lm, hipStream_t st) {
-    hipLaunchKernelGGL(k_lm_accept, dim3(p.n_sub), dim3(64), 0, st, p, chi2_trial, theta, lm);
     return hipGetLastError();
 }
 

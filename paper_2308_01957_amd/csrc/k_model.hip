@@ -68,11 +68,70 @@ __device__ void shift_taps(int method, int a, double delta, double* w, double* d
 }
 
 // ------------------------------------------------------------------------- prep
-__global__ __launch_bounds__(128) void k_prep(Plan p, const double* __restrict__ theta, int lm_trial) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+// The start of every evaluation in one launch: component constants and skies, stamps, and, in
+// an LM iteration, what precedes them (the iteration's flags and adopted steps, or the trial
+// parameters theta + h).  These are a handful of microseconds of work each, and as launches
+// of their own they cost a small fit more than the work (a 64 x 64 fit spent 20 launches an
+// iteration, 98 us of which 65 were kernels).  Block ranges, in order: components and images;
+// one block per image's stamp; the begin blocks; the trial parameters.
+struct PrepBlocks { int comps, psf, begin, trial; };
+
+// theta[k] of the evaluation: the caller's, or with a step theta + h where the solve succeeded
+__device__ __forceinline__ double prep_theta(const Plan& p, const PrepIO& io, int k) {
+    double v = io.theta[k];
+    if (io.step) {
+        const int s = p.par_sub[k];
+        if (s >= 0 && p.lmf[s].chol_done) v += io.step[k];
+    }
+    return v;
+}
+
+// Start of an iteration: clear the per-iteration flags of both solve copies and decide
+// whether a large sub-problem takes the step solved ahead: the same A (its last trial was
+// rejected, so no new normal equations) and the lambda that solve started from.
+__device__ __forceinline__ int lm_begin_sub(const Plan& p, const apx_lm_state* lm, int s) {
+    LMFlags f;
+    f.chol_done = 0;
+    f.chol_fail = 0;
+    f.trial_bad = 0;
+    f.skip = 0;
+    f.subst_fail = 0;
+    f.rhs_folded = 0;
+    f.adopted = 0;
+    p.lmf[p.n_sub + s] = f;
+    const LMSpec sp = p.spec[s];
+    f.adopted = p.subs[s].large && sp.valid && lm[s].need_jac == 0 && lm[s].lambda == sp.lam_start;
+    p.lmf[s] = f;
+    return f.adopted;
+}
+
+// One wave per sub-problem (problems with a large sub-problem, whose solves are made ahead):
+// an adopting sub-problem takes the step, its predicted decrease, lambda and retry count from
+// the solve made ahead (exactly what solving now would give: same A, D, g and starting
+// lambda, same kernels), and the record is used up.
+__device__ __forceinline__ void lm_adopt_sub(const Plan& p, apx_lm_state* lm, int s) {
+    if (threadIdx.x >= 64) return;
+    int adopted = 0;
+    if (threadIdx.x == 0) adopted = lm_begin_sub(p, lm, s);
+    adopted = __shfl(adopted, 0, 64);
+    if (!adopted) return;
+    const DSub sb = p.subs[s];
+    for (int i = (int)threadIdx.x; i < sb.n; i += 64) p.hvec[sb.p0 + i] = p.hvec[p.n_par + sb.p0 + i];
+    if (threadIdx.x == 0) {
+        const LMSpec sp = p.spec[s];
+        lm[s].pred = sp.pred;
+        lm[s].lambda = sp.lam_final;
+        lm[s].n_chol_retry += sp.retries;
+        p.lmf[s].chol_done = sp.done;
+        p.spec[s].valid = 0;
+    }
+}
+
+__device__ void prep_comp(const Plan& p, const PrepIO& io, int i) {
+    const int lm_trial = io.mark;
     if (i < p.n_images) {
         const DImage& im = p.images[i];
-        const double sky = im.sky_par >= 0 ? theta[im.sky_par] : im.sky_fixed;
+        const double sky = im.sky_par >= 0 ? prep_theta(p, io, im.sky_par) : im.sky_fixed;
         p.sky_val[i] = sky;
         if (!isfinite(sky)) {
             if (lm_trial) atomicOr(&p.lmf[im.sub].trial_bad, 1);
@@ -85,7 +144,7 @@ __global__ __launch_bounds__(128) void k_prep(Plan p, const double* __restrict__
     double v[7];
     bool finite = true;
     for (int k = 0; k < 7; ++k) {
-        v[k] = cp.par[k] >= 0 ? theta[cp.par[k]] : cp.fixed[k];
+        v[k] = cp.par[k] >= 0 ? prep_theta(p, io, cp.par[k]) : cp.fixed[k];
         finite = finite && isfinite(v[k]);
     }
     CompConst c;
@@ -170,10 +229,11 @@ __global__ __launch_bounds__(128) void k_prep(Plan p, const double* __restrict__
 // Stamps of every image for this theta: fixed stamps promoted to FP64 (objective
 // convolution); live Moffat stamps (§2.1.3, §3.4) rendered at the integer offsets,
 // normalised, with d/dn and d/dR_d of the normalised stamp (quotient rule), in FP64 and
-// as FP32 copies for the FP32 kernels.  One workgroup per image; the sums are ordered.
-__global__ __launch_bounds__(256) void k_psf_prep(Plan p, const double* __restrict__ theta, int lm_trial) {
+// as FP32 copies for the FP32 kernels; with io.flip, the flipped stamps of the adjoint.  One
+// workgroup per image; the sums are ordered.
+__device__ void prep_psf(const Plan& p, const PrepIO& io, int k) {
     __shared__ double red[4][3];
-    const int k = blockIdx.x;
+    const int lm_trial = io.mark;
     const DImage& im = p.images[k];
     const int P = im.P, c = im.c, P2 = P * P;
     double* K64 = p.psf64 + im.psf_off;
@@ -184,14 +244,15 @@ __global__ __launch_bounds__(256) void k_psf_prep(Plan p, const double* __restri
             const int u = e / P;
             K64[e] = (double)K[e];
             sym &= K[e] == K[e + (P - 1 - 2 * u) * P];   // false for a NaN: then no rows are paired
+            if (io.flip) p.psf_flip[im.psf_off + P2 - 1 - e] = K[e];
         }
         sym = __syncthreads_and(sym);
         if (threadIdx.x == 0) p.psf_sym[k] = sym;
         return;
     }
     if (threadIdx.x == 0) p.psf_sym[k] = 1;          // a function of u^2 + v^2
-    double n = im.live_par[0] >= 0 ? theta[im.live_par[0]] : im.live_fixed[0];
-    double rd = im.live_par[1] >= 0 ? theta[im.live_par[1]] : im.live_fixed[1];
+    double n = im.live_par[0] >= 0 ? prep_theta(p, io, im.live_par[0]) : im.live_fixed[0];
+    double rd = im.live_par[1] >= 0 ? prep_theta(p, io, im.live_par[1]) : im.live_fixed[1];
     const bool valid = isfinite(n) && isfinite(rd) && n >= PSF_N_MIN && n <= PSF_N_MAX &&
                        rd >= PSF_RD_MIN && rd <= PSF_RD_MAX;
     if (!valid) {
@@ -239,16 +300,46 @@ __global__ __launch_bounds__(256) void k_psf_prep(Plan p, const double* __restri
         const double dr = (f * (-n) / x * (-2.0 * r2 * ird2 / rd) - Kv * Sdr) * iS;
         K64[e] = Kv;
         K32[e] = (float)Kv;
+        if (io.flip) p.psf_flip[im.psf_off + P2 - 1 - e] = (float)Kv;
         K32[P2 + e] = (float)dn;
         K32[2 * P2 + e] = (float)dr;
     }
 }
 
-hipError_t launch_prep(const Plan& p, const double* theta, int lm_trial, hipStream_t st) {
+__global__ __launch_bounds__(256) void k_prep(Plan p, PrepIO io, PrepBlocks nb) {
+    int b = (int)blockIdx.x;
+    if (b < nb.comps) {
+        prep_comp(p, io, b * 256 + (int)threadIdx.x);
+        return;
+    }
+    b -= nb.comps;
+    if (b < nb.psf) {
+        prep_psf(p, io, b);
+        return;
+    }
+    b -= nb.psf;
+    if (b < nb.begin) {
+        if (io.adopt) {
+            lm_adopt_sub(p, io.lm, b);
+        } else {
+            const int s = b * 256 + (int)threadIdx.x;
+            if (s < p.n_sub) lm_begin_sub(p, io.lm, s);
+        }
+        return;
+    }
+    b -= nb.begin;
+    const int k = b * 256 + (int)threadIdx.x;
+    if (k < p.n_par) p.theta_trial[k] = prep_theta(p, io, k);
+}
+
+hipError_t launch_prep(const Plan& p, const PrepIO& io, hipStream_t st) {
     const int n = p.n_comps > p.n_images ? p.n_comps : p.n_images;
-    if (n == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_prep, dim3((n + 127) / 128), dim3(128), 0, st, p, theta, lm_trial);
-    if (p.n_images > 0) hipLaunchKernelGGL(k_psf_prep, dim3(p.n_images), dim3(256), 0, st, p, theta, lm_trial);
+    PrepBlocks nb;
+    nb.comps = (n + 255) / 256;
+    nb.psf = p.n_images;
+    nb.begin = !io.lm ? 0 : io.adopt ? p.n_sub : (p.n_sub + 255) / 256;
+    nb.trial = io.step ? (p.n_par + 255) / 256 : 0;
+    hipLaunchKernelGGL(k_prep, dim3(nb.comps + nb.psf + nb.begin + nb.trial), dim3(256), 0, st, p, io, nb);
     return hipGetLastError();
 }
 
@@ -833,18 +924,6 @@ hipError_t launch_grad_tiles(const Plan& p, hipStream_t st) {
     return hipGetLastError();
 }
 
-// -------------------------------------------------------------- flipped PSF
-__global__ void k_flip_psf(Plan p) {
-    const int k = blockIdx.y;
-    const DImage& im = p.images[k];
-    const int P = im.P;
-    for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < P * P; e += gridDim.x * blockDim.x) {
-        const int u = e / P, v = e % P;
-        const float* K = im.live ? p.psf_live + im.live_off : p.psf + im.psf_off;
-        p.psf_flip[im.psf_off + e] = K[(P - 1 - u) * P + (P - 1 - v)];
-    }
-}
-
 // -------------------------------------------------------------- seed sums (VJP sky column)
 // Block c of image k sums pixels c*256 + t + SEED_BLOCKS*256*m in FP64 (fixed order per
 // thread, then waves in order); one wave per image folds the SEED_BLOCKS partials.
@@ -875,12 +954,6 @@ hipError_t launch_seed_sums(const Plan& p, const float* seed, double* part, hipS
     if (p.n_images == 0) return hipSuccess;
     hipLaunchKernelGGL(k_seed_part, dim3(SEED_BLOCKS, p.n_images), dim3(256), 0, st, p, seed, part);
     hipLaunchKernelGGL(k_seed_fold, dim3(p.n_images), dim3(64), 0, st, p, part);
-    return hipGetLastError();
-}
-
-hipError_t launch_flip_psf(const Plan& p, hipStream_t st) {
-    if (p.n_images == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_flip_psf, dim3(4, p.n_images), dim3(256), 0, st, p);
     return hipGetLastError();
 }
 
