@@ -266,7 +266,7 @@ static bool tune_kernel(apx_ctx* C, int key, int P, std::array<double, 4>& us) {
     const size_t o_img = take(sizeof(DImage)), o_job = take(sizeof(ConvJob));
     const size_t o_items = take(sizeof(ConvItem) * max_items), o_psf = take(sizeof(float) * TUNE_MAXP * TUNE_MAXP);
     const size_t o_psf64 = take(sizeof(double) * TUNE_MAXP * TUNE_MAXP);
-    const size_t o_sym = take(sizeof(int));
+    const size_t o_sym = take(sizeof(int)), o_plan = take(sizeof(Plan));
     const size_t o_sky = take(sizeof(double)), o_r = take(sizeof(float) * npx), o_w = take(sizeof(float) * npx);
     const size_t o_d = take(sizeof(float) * npx), o_in = take(sizeof(float) * next * TUNE_CH);
     const size_t o_in64 = take(sizeof(double) * next), o_out = take(sizeof(float) * (size_t)TUNE_CH * next);
@@ -296,6 +296,8 @@ static bool tune_kernel(apx_ctx* C, int key, int P, std::array<double, 4>& us) {
     if (hipMemcpy(base + o_sym, &sym, sizeof sym, hipMemcpyHostToDevice) != hipSuccess) return false;
     p.sky_val = (double*)(base + o_sky);
     p.rbuf = (float*)(base + o_r);
+    p.dev = (PlanPtr)(base + o_plan);
+    if (hipMemcpy(base + o_plan, &p, sizeof p, hipMemcpyHostToDevice) != hipSuccess) return false;
     ConvIO io{};
     io.in = (const float*)(base + o_in);
     io.in64 = (const double*)(base + o_in64);
@@ -1653,6 +1655,7 @@ static void layout(apx_problem* P) {
     ws_take<double>(P, "chol_diag", 2 * (size_t)CHOL_NB * CHOL_NB * P->large_subs.size());
     ws_take<LMSpec>(P, "spec", P->n_sub);
     ws_take<int>(P, "sticky", 1);
+    ws_take<Plan>(P, "plan", 1);
     ws_take<double>(P, "sky_val", P->n_images);
     ws_take<double>(P, "seed_part", 64LL * P->n_images);
     ws_take<double>(P, "chi2_sub", P->n_sub);
@@ -1960,6 +1963,8 @@ apx_status apx_problem_bind_workspace(apx_problem* P, void* dev, uint64_t bytes)
     p.n_ext = P->n_ext;
     P->chi2_sub = wsp<double>(P, "chi2_sub");
     P->chi2_trial = wsp<double>(P, "chi2_trial");
+    p.dev = (PlanPtr)wsp<Plan>(P, "plan");
+    HIPCHK(hipMemcpyAsync(wsp<Plan>(P, "plan"), &p, sizeof(Plan), hipMemcpyHostToDevice, P->ctx->stream));
     HIPCHK(hipMemsetAsync(p.sticky, 0, sizeof(int), P->ctx->stream));
     HIPCHK(hipMemsetAsync(p.lmf, 0, sizeof(LMFlags) * 2 * P->n_sub, P->ctx->stream));
     HIPCHK(hipMemsetAsync(p.spec, 0, sizeof(LMSpec) * P->n_sub, P->ctx->stream));
@@ -2054,6 +2059,7 @@ apx_status apx_problem_set_wait_limit(apx_problem* P, int32_t polls) {
     if (P->capturing) return fail(P->ctx, APX_E_INVALID, "the wait limit cannot change during capture");
     HIPCHK(hipStreamSynchronize(P->ctx->stream));
     P->plan.wait_spin_max = polls == 0 ? SUBST_SPIN_MAX : polls;
+    HIPCHK(hipMemcpy(wsp<Plan>(P, "plan"), &P->plan, sizeof(Plan), hipMemcpyHostToDevice));
     drop_graph(P);                      // a captured iteration holds the old plan
     return APX_OK;
 }

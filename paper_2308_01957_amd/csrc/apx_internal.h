@@ -220,6 +220,14 @@ struct LMSpec {
 };
 
 // Launch-time views of the workspace ----------------------------------------------
+// Most kernels take the plan by the address of its copy in the workspace: a launch with the
+// record itself (over 1 KB of arguments) costs the host 4.7 us, one with a pointer 2.7 us, and
+// small fits are bound by that.  The copy does not change while kernels run, so it is read
+// through the constant address space (scalar loads, as kernel arguments are).
+struct Plan;
+using PlanPtr = const __attribute__((address_space(4))) Plan*;
+using PlanRef = const __attribute__((address_space(4))) Plan&;
+
 struct Plan {
     int n_images, n_comps, n_par, n_sub, n_groups, n_cols;
     int s, rule, mode, objective;
@@ -300,6 +308,7 @@ struct Plan {
     long long n_apix;
 
     long long n_pix, n_ext;
+    PlanPtr dev;              // this record's copy in the workspace
     // bound of a substitution hand-off wait in polls; < 0: every wait takes its flag as never
     // raised and gives up after -wait_spin_max polls (forces the give-up path from the host)
     int wait_spin_max;
@@ -335,7 +344,7 @@ __device__ __forceinline__ Plan solve_view(const Plan& p, int which) {
 
 // skip_mode of the launchers: 0 none, 1 sub-problems without a valid trial (the trial
 // render), 2 sub-problems that keep their Jacobian (lm[sub].need_jac == 0)
-__device__ __forceinline__ bool sub_skipped(const Plan& p, int sub, int mode, const apx_lm_state* lm) {
+__device__ __forceinline__ bool sub_skipped(PlanRef p, int sub, int mode, const apx_lm_state* lm) {
     if (mode == 1) return p.lmf[sub].chol_done == 0 || p.lmf[sub].trial_bad != 0;
     if (mode == 2) return lm[sub].need_jac == 0;
     return false;

@@ -68,7 +68,7 @@ __device__ __forceinline__ void bin_pixels(T (&acc)[R], int up) {
 // Epilogue of the model convolution: model + sky, optional model store, FP32 residual store,
 // FP64 partials of sum w r^2, sum w r, sum w per item.
 template <typename T, int R, int NW>
-__device__ __forceinline__ void fwd_epilogue(const Plan& p, const ConvJob& jb, const DImage& im, const ConvIO& io,
+__device__ __forceinline__ void fwd_epilogue(PlanRef p, const ConvJob& jb, const DImage& im, const ConvIO& io,
                                              int item_idx, const T (&acc)[R], int y, int xb, bool yok,
                                              double (*red)[3]) {
     const int up = im.up, nq = R / up;               // values per lane, render-grid step between them
@@ -125,7 +125,7 @@ __device__ __forceinline__ void fwd_epilogue(const Plan& p, const ConvJob& jb, c
 }
 
 // Whether the sub-problem of an item skips this phase.
-__device__ __forceinline__ bool conv_skipped(const Plan& p, const ConvIO& io, int sub) {
+__device__ __forceinline__ bool conv_skipped(PlanRef p, const ConvIO& io, int sub) {
     if (io.skip_mode == 1) return p.lmf[sub].chol_done == 0 || p.lmf[sub].trial_bad != 0;
     if (io.skip_mode == 2) return io.lm[sub].need_jac == 0;
     return false;
@@ -133,9 +133,10 @@ __device__ __forceinline__ bool conv_skipped(const Plan& p, const ConvIO& io, in
 
 // The FP32 kinds.
 template <int P, int KIND, int TH, int TW, int R>
-__global__ __launch_bounds__(TH * TW / R) void k_conv(Plan p, const ConvJob* __restrict__ jobs,
+__global__ __launch_bounds__(TH * TW / R) void k_conv(PlanPtr pp, const ConvJob* __restrict__ jobs,
                                                       const ConvItem* __restrict__ items, int item_begin,
                                                       ConvIO io) {
+    PlanRef p = *pp;
     using T = float;
     constexpr int c = (P - 1) / 2;
     constexpr int NT = TH * TW / R;                 // threads
@@ -333,9 +334,10 @@ __device__ __forceinline__ void pin(double (&a)[CV_R_FINE], int& o1, int& o2) {
     asm volatile("" : "+v"(a[0]), "+v"(a[1]), "+v"(o1), "+v"(o2));
 }
 template <int P, int TH, int TW, int R>
-__global__ __launch_bounds__(TH * TW / R) void k_conv64(Plan p, const ConvJob* __restrict__ jobs,
+__global__ __launch_bounds__(TH * TW / R) void k_conv64(PlanPtr pp, const ConvJob* __restrict__ jobs,
                                                         const ConvItem* __restrict__ items, int item_begin,
                                                         ConvIO io) {
+    PlanRef p = *pp;
     constexpr int c = (P - 1) / 2;
     constexpr int NT = TH * TW / R;
     constexpr int LPR = TW / R;
@@ -482,9 +484,10 @@ __global__ __launch_bounds__(TH * TW / R) void k_conv64(Plan p, const ConvJob* _
 // partials of sum w r J and sum w J per item unless the job's gram_part is set).  2 (P + P (TH + P - 1) / TH) multiply-adds per output
 // instead of 2 P^2.
 template <int P>
-__global__ __launch_bounds__(256) void k_conv_sep(Plan p, const ConvJob* __restrict__ jobs,
+__global__ __launch_bounds__(256) void k_conv_sep(PlanPtr pp, const ConvJob* __restrict__ jobs,
                                                   const ConvItem* __restrict__ items, int item_begin,
                                                   ConvIO io) {
+    PlanRef p = *pp;
     constexpr int TH = SEP_TH, TW = SEP_TW, NT = 256;
     constexpr int c = (P - 1) / 2;
     constexpr int LPR = TW / CV_R;                  // lanes per output row
@@ -639,10 +642,10 @@ hipError_t launch_conv_shape(const Plan& p, const ConvLaunch& L, const ConvIO& i
 #define APX_CASE(PP)                                                                                     \
     case PP:                                                                                             \
         if constexpr (sizeof(T) == 8)                                                                    \
-            hipLaunchKernelGGL((k_conv64<PP, TH, TW, R>), grid, block, 0, st, p, L.jobs, L.items,        \
+            hipLaunchKernelGGL((k_conv64<PP, TH, TW, R>), grid, block, 0, st, p.dev, L.jobs, L.items,        \
                                L.item_begin, io);                                                        \
         else                                                                                             \
-            hipLaunchKernelGGL((k_conv<PP, KIND, TH, TW, R>), grid, block, 0, st, p, L.jobs, L.items,    \
+            hipLaunchKernelGGL((k_conv<PP, KIND, TH, TW, R>), grid, block, 0, st, p.dev, L.jobs, L.items,    \
                                L.item_begin, io);                                                        \
         break;
         APX_FOR_EACH_P(APX_CASE)
@@ -659,7 +662,7 @@ inline hipError_t launch_conv_sep_impl(const Plan& p, const ConvLaunch& L, const
     switch (L.P) {
 #define APX_CASE(PP)                                                                                   \
     case PP:                                                                                           \
-        hipLaunchKernelGGL((k_conv_sep<PP>), grid, block, 0, st, p, L.jobs, L.items, L.item_begin, io); \
+        hipLaunchKernelGGL((k_conv_sep<PP>), grid, block, 0, st, p.dev, L.jobs, L.items, L.item_begin, io); \
         break;
         APX_FOR_EACH_P(APX_CASE)
 #undef APX_CASE

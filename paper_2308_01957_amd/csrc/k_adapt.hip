@@ -47,17 +47,19 @@ __device__ __forceinline__ double prof_at(const CompConst& c, const DImage& im, 
 // centre offset of sub-pixel i (0..4) along one axis of a unit square
 __device__ __forceinline__ double sub_off(int i) { return (i + 0.5) * 0.2 - 0.5; }
 
-__global__ void k_adapt_reset(Plan p) {
+__global__ void k_adapt_reset(PlanPtr pp) {
+    PlanRef p = *pp;
     if (threadIdx.x == 0) p.acount[0] = 0;
 }
 
-__device__ __forceinline__ bool chunk_active(const Plan& p, const AChunk& ch, int skip_mode, const apx_lm_state* lm) {
+__device__ __forceinline__ bool chunk_active(PlanRef p, const AChunk& ch, int skip_mode, const apx_lm_state* lm) {
     const DComp& cp = p.comps[ch.comp];
     return !sub_skipped(p, cp.sub, skip_mode, lm) && p.cc[ch.comp].valid;
 }
 
 // apart[chunk] = sum of the centre values of the chunk's pixels (fixed order).
-__global__ __launch_bounds__(ADAPT_CHUNK) void k_adapt_flux(Plan p, int skip_mode, const apx_lm_state* lm) {
+__global__ __launch_bounds__(ADAPT_CHUNK) void k_adapt_flux(PlanPtr pp, int skip_mode, const apx_lm_state* lm) {
+    PlanRef p = *pp;
     __shared__ double red[ADAPT_CHUNK / 64];
     const AChunk ch = p.achunks[blockIdx.x];
     if (!chunk_active(p, ch, skip_mode, lm)) return;
@@ -83,7 +85,8 @@ __global__ __launch_bounds__(ADAPT_CHUNK) void k_adapt_flux(Plan p, int skip_mod
 }
 
 // One wave per component: ae[comp] = tol * area * (sum of its chunk partials) / N.
-__global__ __launch_bounds__(64) void k_adapt_fold(Plan p, int skip_mode, const apx_lm_state* lm) {
+__global__ __launch_bounds__(64) void k_adapt_fold(PlanPtr pp, int skip_mode, const apx_lm_state* lm) {
+    PlanRef p = *pp;
     const int ci = blockIdx.x;
     const int cb = p.acomp_chunk[ci], ce = p.acomp_chunk[ci + 1];
     if (cb == ce) return;
@@ -100,7 +103,8 @@ __global__ __launch_bounds__(64) void k_adapt_fold(Plan p, int skip_mode, const 
 }
 
 // One thread per window pixel: centre or 3 x 3 value and its choice, or a refine entry.
-__global__ __launch_bounds__(ADAPT_CHUNK) void k_adapt_pix(Plan p, int skip_mode, const apx_lm_state* lm) {
+__global__ __launch_bounds__(ADAPT_CHUNK) void k_adapt_pix(PlanPtr pp, int skip_mode, const apx_lm_state* lm) {
+    PlanRef p = *pp;
     const AChunk ch = p.achunks[blockIdx.x];
     const DComp& cp = p.comps[ch.comp];
     if (sub_skipped(p, cp.sub, skip_mode, lm)) return;
@@ -159,7 +163,7 @@ __device__ __forceinline__ double block_sum(double v, double* red) {
 
 // Position (pixel coordinates) of node q of the refined sub-pixels: nq = index into the
 // list of 7x7-refined sub-pixels, then sub-sub-pixel m and node (kx, ky).
-__device__ __forceinline__ void node7(const Plan& p, const int* need_list, double x, double y, int q,
+__device__ __forceinline__ void node7(PlanRef p, const int* need_list, double x, double y, int q,
                                       double& px, double& py, double& wgt) {
     const int j = need_list[q / N_G7], rem = q % N_G7, m = rem / 49, k = rem % 49;
     const double* o7 = p.agl + 16;
@@ -169,7 +173,8 @@ __device__ __forceinline__ void node7(const Plan& p, const int* need_list, doubl
     wgt = (w7[k % 7] * w7[k / 7]) * 0.04;              // sub-sub-pixel mean over 25
 }
 
-__global__ __launch_bounds__(REFINE_THREADS) void k_adapt_refine(Plan p) {
+__global__ __launch_bounds__(REFINE_THREADS) void k_adapt_refine(PlanPtr pp) {
+    PlanRef p = *pp;
     __shared__ double nv[N_G3 + N_G5];
     __shared__ double g5s[25];
     __shared__ int need_list[25];
@@ -244,7 +249,8 @@ __global__ __launch_bounds__(REFINE_THREADS) void k_adapt_refine(Plan p) {
 
 // The derivatives of the rule each listed pixel took: 7 x 7 nodes of its refined
 // sub-pixels, 5 x 5 nodes of the others, all in one strided node range.
-__global__ __launch_bounds__(REFINE_THREADS) void k_adapt_refine_grad(Plan p) {
+__global__ __launch_bounds__(REFINE_THREADS) void k_adapt_refine_grad(PlanPtr pp) {
+    PlanRef p = *pp;
     __shared__ int need_list[25], keep_list[25];
     __shared__ int n_need;
     __shared__ double red[REFINE_THREADS / 64][7];
@@ -301,13 +307,13 @@ __global__ __launch_bounds__(REFINE_THREADS) void k_adapt_refine_grad(Plan p) {
 
 hipError_t launch_adapt(const Plan& p, int skip_mode, const apx_lm_state* lm, int want_grad, hipStream_t st) {
     if (p.n_achunks == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_adapt_reset, dim3(1), dim3(64), 0, st, p);
-    hipLaunchKernelGGL(k_adapt_flux, dim3(p.n_achunks), dim3(ADAPT_CHUNK), 0, st, p, skip_mode, lm);
-    hipLaunchKernelGGL(k_adapt_fold, dim3(p.n_comps), dim3(64), 0, st, p, skip_mode, lm);
-    hipLaunchKernelGGL(k_adapt_pix, dim3(p.n_achunks), dim3(ADAPT_CHUNK), 0, st, p, skip_mode, lm);
+    hipLaunchKernelGGL(k_adapt_reset, dim3(1), dim3(64), 0, st, p.dev);
+    hipLaunchKernelGGL(k_adapt_flux, dim3(p.n_achunks), dim3(ADAPT_CHUNK), 0, st, p.dev, skip_mode, lm);
+    hipLaunchKernelGGL(k_adapt_fold, dim3(p.n_comps), dim3(64), 0, st, p.dev, skip_mode, lm);
+    hipLaunchKernelGGL(k_adapt_pix, dim3(p.n_achunks), dim3(ADAPT_CHUNK), 0, st, p.dev, skip_mode, lm);
     const long long g = p.n_apix < 4096 ? p.n_apix : 4096;
-    hipLaunchKernelGGL(k_adapt_refine, dim3((unsigned)g), dim3(REFINE_THREADS), 0, st, p);
-    if (want_grad) hipLaunchKernelGGL(k_adapt_refine_grad, dim3((unsigned)g), dim3(REFINE_THREADS), 0, st, p);
+    hipLaunchKernelGGL(k_adapt_refine, dim3((unsigned)g), dim3(REFINE_THREADS), 0, st, p.dev);
+    if (want_grad) hipLaunchKernelGGL(k_adapt_refine_grad, dim3((unsigned)g), dim3(REFINE_THREADS), 0, st, p.dev);
     return hipGetLastError();
 }
 

@@ -140,7 +140,7 @@ __device__ __forceinline__ void fft2d(cf* sm, const cf* tw) {
     fft_lines(sm, tw, 1);
 }
 
-__device__ __forceinline__ void load_twiddles(const Plan& p, cf* tw) {
+__device__ __forceinline__ void load_twiddles(PlanRef p, cf* tw) {
     if (threadIdx.x < FT) {
         const float2 v = p.fft_tw[threadIdx.x];
         tw[threadIdx.x] = {v.x, v.y};
@@ -150,7 +150,8 @@ __device__ __forceinline__ void load_twiddles(const Plan& p, cf* tw) {
 // Spectrum of one stamp slot of one image, zero-padded to 128 x 128 at the origin: K
 // (slot 0, the model and Jacobian convolutions) and K flipped (slot 1, the adjoint).  On a
 // live-PSF image K is the stamp rendered for the current theta.
-__global__ __launch_bounds__(FFT_THREADS) void k_fft_stamp(Plan p, int live_only) {
+__global__ __launch_bounds__(FFT_THREADS) void k_fft_stamp(PlanPtr pp, int live_only) {
+    PlanRef p = *pp;
     __shared__ cf sm[FT * FTP];
     __shared__ cf tw[FT];
     const int k = blockIdx.y, slot = blockIdx.x;
@@ -177,7 +178,7 @@ __global__ __launch_bounds__(FFT_THREADS) void k_fft_stamp(Plan p, int live_only
 
 hipError_t launch_fft_stamps(const Plan& p, int live_only, hipStream_t st) {
     if (p.n_images == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_fft_stamp, dim3(2, p.n_images), dim3(FFT_THREADS), 0, st, p, live_only);
+    hipLaunchKernelGGL(k_fft_stamp, dim3(2, p.n_images), dim3(FFT_THREADS), 0, st, p.dev, live_only);
     return hipGetLastError();
 }
 
@@ -195,10 +196,11 @@ __device__ __forceinline__ double fft_block_sum(double v, double* red) {
 }
 
 template <int KIND>
-__global__ __launch_bounds__(FFT_THREADS) void k_conv_fft(Plan p, const ConvJob* __restrict__ jobs,
+__global__ __launch_bounds__(FFT_THREADS) void k_conv_fft(PlanPtr pp, const ConvJob* __restrict__ jobs,
                                                           const ConvItem* __restrict__ items,
                                                           const int4* __restrict__ pairs, int pair_begin,
                                                           ConvIO io) {
+    PlanRef p = *pp;
     __shared__ cf sm[FT * FTP];
     __shared__ cf tw[FT];
     __shared__ double red[FFT_THREADS / 64];
@@ -450,7 +452,7 @@ __global__ __launch_bounds__(FFT_THREADS) void k_conv_fft(Plan p, const ConvJob*
 template <int KIND>
 static hipError_t launch_fft_kind(const Plan& p, const ConvLaunch& L, const ConvIO& io, hipStream_t st) {
     if (L.pair_count <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_conv_fft<KIND>, dim3(L.pair_count), dim3(FFT_THREADS), 0, st, p, L.jobs, L.items,
+    hipLaunchKernelGGL(k_conv_fft<KIND>, dim3(L.pair_count), dim3(FFT_THREADS), 0, st, p.dev, L.jobs, L.items,
                        L.pairs, L.pair_begin, io);
     return hipGetLastError();
 }

@@ -14,7 +14,8 @@
 namespace apx {
 
 // Ft = F^T block by block (so that both products below read their matrix by columns).
-__global__ void k_hmc_transpose(Plan p, const double* __restrict__ F, double* __restrict__ Ft) {
+__global__ void k_hmc_transpose(PlanPtr pp, const double* __restrict__ F, double* __restrict__ Ft) {
+    PlanRef p = *pp;
     const DSub sb = p.subs[blockIdx.y];
     const long long n = sb.n, nn = n * n;
     for (long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x; e < nn;
@@ -26,8 +27,9 @@ __global__ void k_hmc_transpose(Plan p, const double* __restrict__ F, double* __
 
 // One thread per theta index j of a sub-problem (local index i): out[j] += coef * sum_k M[k][i] v[k].
 // With M = F this is F^T v (the kick), with M = F^T it is F v (the drift).
-__global__ void k_hmc_matvec(Plan p, const double* __restrict__ M, const double* __restrict__ v,
+__global__ void k_hmc_matvec(PlanPtr pp, const double* __restrict__ M, const double* __restrict__ v,
                              double* __restrict__ out, double coef, const int* skip) {
+    PlanRef p = *pp;
     const int j = blockIdx.x * blockDim.x + threadIdx.x;
     if (j >= p.n_par || (skip && *skip)) return;
     const int s = p.par_sub[j];
@@ -50,7 +52,8 @@ __device__ __forceinline__ double sub_sq(const double* r, const DSub& sb) {
 
 // One wave per sub-problem: r = z_i, theta0 = theta, H0 = chi2 / 2 + |r|^2 / 2, clear the
 // domain flag of the trajectory.
-__global__ __launch_bounds__(64) void k_hmc_begin(Plan p, HmcIO h, long long i) {
+__global__ __launch_bounds__(64) void k_hmc_begin(PlanPtr pp, HmcIO h, long long i) {
+    PlanRef p = *pp;
     const int s = blockIdx.x;
     const DSub sb = p.subs[s];
     const double* z = h.z + i * p.n_par;
@@ -68,7 +71,8 @@ __global__ __launch_bounds__(64) void k_hmc_begin(Plan p, HmcIO h, long long i) 
 // One wave per sub-problem: Metropolis test on H1 - H0; accepted -> keep theta and the end
 // point's gradient and chi^2, rejected -> restore theta0.  Block n_sub copies the entries of
 // theta that belong to no sub-problem.
-__global__ __launch_bounds__(64) void k_hmc_accept(Plan p, HmcIO h, long long i) {
+__global__ __launch_bounds__(64) void k_hmc_accept(PlanPtr pp, HmcIO h, long long i) {
+    PlanRef p = *pp;
     const int s = blockIdx.x;
     double* out = h.samples + i * p.n_par;
     if (s == p.n_sub) {
@@ -98,24 +102,24 @@ __global__ __launch_bounds__(64) void k_hmc_accept(Plan p, HmcIO h, long long i)
 
 hipError_t launch_hmc_transpose(const Plan& p, const double* F, double* Ft, hipStream_t st) {
     if (p.n_sub == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_hmc_transpose, dim3(16, p.n_sub), dim3(256), 0, st, p, F, Ft);
+    hipLaunchKernelGGL(k_hmc_transpose, dim3(16, p.n_sub), dim3(256), 0, st, p.dev, F, Ft);
     return hipGetLastError();
 }
 
 hipError_t launch_hmc_matvec(const Plan& p, const double* M, const double* v, double* out, double coef,
                              hipStream_t st, const int* skip) {
     if (p.n_par == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_hmc_matvec, dim3((p.n_par + 255) / 256), dim3(256), 0, st, p, M, v, out, coef, skip);
+    hipLaunchKernelGGL(k_hmc_matvec, dim3((p.n_par + 255) / 256), dim3(256), 0, st, p.dev, M, v, out, coef, skip);
     return hipGetLastError();
 }
 
 hipError_t launch_hmc_begin(const Plan& p, const HmcIO& h, long long i, hipStream_t st) {
-    hipLaunchKernelGGL(k_hmc_begin, dim3(p.n_sub), dim3(64), 0, st, p, h, i);
+    hipLaunchKernelGGL(k_hmc_begin, dim3(p.n_sub), dim3(64), 0, st, p.dev, h, i);
     return hipGetLastError();
 }
 
 hipError_t launch_hmc_accept(const Plan& p, const HmcIO& h, long long i, hipStream_t st) {
-    hipLaunchKernelGGL(k_hmc_accept, dim3(p.n_sub + 1), dim3(64), 0, st, p, h, i);
+    hipLaunchKernelGGL(k_hmc_accept, dim3(p.n_sub + 1), dim3(64), 0, st, p.dev, h, i);
     return hipGetLastError();
 }
 
@@ -123,7 +127,7 @@ hipError_t launch_hmc_accept(const Plan& p, const HmcIO& h, long long i, hipStre
 // every sub-problem, +inf when any sub-problem's point left the domain (whose flags it then
 // clears).  Called by all 256 threads of one workgroup; fixed-order sums; the result is
 // valid in thread 0.
-__device__ double nuts_energy(const Plan& p, const double* __restrict__ chi2, const double* __restrict__ r) {
+__device__ double nuts_energy(PlanRef p, const double* __restrict__ chi2, const double* __restrict__ r) {
     __shared__ double red[4];
     __shared__ int bad;
     if (threadIdx.x == 0) bad = 0;
@@ -148,8 +152,9 @@ __device__ double nuts_energy(const Plan& p, const double* __restrict__ chi2, co
     return h;
 }
 
-__global__ __launch_bounds__(256) void k_nuts_start(Plan p, NutsDev* d, const double* __restrict__ chi2,
+__global__ __launch_bounds__(256) void k_nuts_start(PlanPtr pp, NutsDev* d, const double* __restrict__ chi2,
                                                     const double* __restrict__ r, const double* __restrict__ u) {
+    PlanRef p = *pp;
     const double h = nuts_energy(p, chi2, r);
     if (threadIdx.x == 0) {
         d->H0 = h;
@@ -188,8 +193,9 @@ __global__ __launch_bounds__(256) void k_nuts_copy(const int* flag, int want, Nu
 
 // A leaf: point in the slice when log_slice <= -H; the doubling stops (divergent) when
 // log_slice >= -H + APX_NUTS_DELTA_MAX.
-__global__ __launch_bounds__(256) void k_nuts_leaf(Plan p, NutsDev* d, const double* __restrict__ chi2,
+__global__ __launch_bounds__(256) void k_nuts_leaf(PlanPtr pp, NutsDev* d, const double* __restrict__ chi2,
                                                    const double* __restrict__ r) {
+    PlanRef p = *pp;
     const double h = nuts_energy(p, chi2, r);
     if (threadIdx.x == 0 && !d->stop) {
         d->alpha += isfinite(h) ? fmin(1.0, exp(d->H0 - h)) : 0.0;
@@ -248,10 +254,11 @@ __global__ __launch_bounds__(256) void k_nuts_top(NutsDev* d, int depth, const d
     if (acc) nuts_copy_all(sample, n);
 }
 
-__global__ __launch_bounds__(256) void k_nuts_uturn(Plan p, const double* __restrict__ tm,
+__global__ __launch_bounds__(256) void k_nuts_uturn(PlanPtr pp, const double* __restrict__ tm,
                                                     const double* __restrict__ tp, const double* __restrict__ vm,
                                                     const double* __restrict__ vp, NutsDev* d, const int* flag,
                                                     int want) {
+    PlanRef p = *pp;
     __shared__ double red[4][2];
     if (*flag != want) return;                // uniform across the workgroup
     double a = 0.0, b = 0.0;
@@ -277,18 +284,19 @@ __global__ __launch_bounds__(256) void k_nuts_uturn(Plan p, const double* __rest
     }
 }
 
-__global__ void k_clear_trial_flags(Plan p) {
+__global__ void k_clear_trial_flags(PlanPtr pp) {
+    PlanRef p = *pp;
     for (int s = (int)threadIdx.x; s < p.n_sub; s += blockDim.x) p.lmf[s].trial_bad = 0;
 }
 
 hipError_t launch_clear_trial_flags(const Plan& p, hipStream_t st) {
-    hipLaunchKernelGGL(k_clear_trial_flags, dim3(1), dim3(256), 0, st, p);
+    hipLaunchKernelGGL(k_clear_trial_flags, dim3(1), dim3(256), 0, st, p.dev);
     return hipGetLastError();
 }
 
 hipError_t launch_nuts_start(const Plan& p, NutsDev* d, const double* chi2, const double* r, const double* u,
                              hipStream_t st) {
-    hipLaunchKernelGGL(k_nuts_start, dim3(1), dim3(256), 0, st, p, d, chi2, r, u);
+    hipLaunchKernelGGL(k_nuts_start, dim3(1), dim3(256), 0, st, p.dev, d, chi2, r, u);
     return hipGetLastError();
 }
 
@@ -303,7 +311,7 @@ hipError_t launch_nuts_copy(const int* flag, int want, const NutsCopy& c, long l
 }
 
 hipError_t launch_nuts_leaf(const Plan& p, NutsDev* d, const double* chi2, const double* r, hipStream_t st) {
-    hipLaunchKernelGGL(k_nuts_leaf, dim3(1), dim3(256), 0, st, p, d, chi2, r);
+    hipLaunchKernelGGL(k_nuts_leaf, dim3(1), dim3(256), 0, st, p.dev, d, chi2, r);
     return hipGetLastError();
 }
 
@@ -326,7 +334,7 @@ hipError_t launch_nuts_top(NutsDev* d, int depth, const double* u, const NutsCop
 
 hipError_t launch_nuts_uturn(const Plan& p, const double* tm, const double* tp, const double* vm,
                              const double* vp, NutsDev* d, const int* flag, int want, hipStream_t st) {
-    hipLaunchKernelGGL(k_nuts_uturn, dim3(1), dim3(256), 0, st, p, tm, tp, vm, vp, d, flag, want);
+    hipLaunchKernelGGL(k_nuts_uturn, dim3(1), dim3(256), 0, st, p.dev, tm, tp, vm, vp, d, flag, want);
     return hipGetLastError();
 }
 

@@ -24,10 +24,11 @@ typedef double apx_d4 __attribute__((ext_vector_type(4)));
 // pipelined two deep: the global loads of stages s+1 and s+2 are in flight while the
 // MFMAs consume s.  Each thread stages the same tile columns and pixel offsets in every
 // stage, so its column offsets into J are computed once.
-__global__ __launch_bounds__(256) void k_pair(Plan p, const DPair* __restrict__ pairs,
+__global__ __launch_bounds__(256) void k_pair(PlanPtr pp, const DPair* __restrict__ pairs,
                                               const PairItem* __restrict__ items,
                                               const float* __restrict__ weight,
                                               const apx_lm_state* lm) {
+    PlanRef p = *pp;
     constexpr int KC = PAIR_KC, TM = 64;
     constexpr int PER = TM * KC / 256;              // elements of A (and of B) per thread
     constexpr int NB = 2;                           // accumulators: NB x NB per wave
@@ -247,9 +248,10 @@ __device__ __forceinline__ void gram_emit(const double (&acc)[NQ], double* __res
 // each tile against [r 1 0 0] (the pixel's residual, a one), which gives the columns' J^T W r
 // and sum w J (the sky row of J^T W J) over the item in NT more blocks after the tile pairs.
 template <int NT, int NS>
-__global__ __launch_bounds__(256) void k_gram4(Plan p, const DPair* __restrict__ pairs,
+__global__ __launch_bounds__(256) void k_gram4(PlanPtr pp, const DPair* __restrict__ pairs,
                                                const PairItem* __restrict__ items, int n_items,
                                                const float* __restrict__ weight, const apx_lm_state* lm) {
+    PlanRef p = *pp;
     constexpr int NP = NT * (NT + 1) / 2;
     const PairItem it = items[xcd_chunk_item((int)blockIdx.x, n_items)];
     const DPair pr = pairs[it.pair];
@@ -336,9 +338,10 @@ __global__ __launch_bounds__(256) void k_gram4(Plan p, const DPair* __restrict__
 // (On 16 x 16 MFMA tiles two 7-column galaxies filled 49 of 256 entries: the overlaps of 60
 // galaxies on four 700 x 700 images took 562 us there, 273 us here.)
 template <int BA, int BB>
-__global__ __launch_bounds__(256) void k_cross4(Plan p, const DPair* __restrict__ pairs,
+__global__ __launch_bounds__(256) void k_cross4(PlanPtr pp, const DPair* __restrict__ pairs,
                                                 const PairItem* __restrict__ items, int n_items,
                                                 const float* __restrict__ weight, const apx_lm_state* lm) {
+    PlanRef p = *pp;
     constexpr int NS = BA + BB <= 4 ? 4 : 2;
     const PairItem it = items[xcd_chunk_item((int)blockIdx.x, n_items)];
     const DPair pr = pairs[it.pair];
@@ -431,7 +434,7 @@ hipError_t launch_gram4(const Plan& p, const PairLaunch& L, const float* weight,
     switch (L.tm) {
 #define APX_G4(T)                                                                                       \
     case T:                                                                                             \
-        hipLaunchKernelGGL((k_gram4<T, (T) <= 5 ? 4 : 2>), grid, block, 0, st, p, L.pairs, L.items, L.n_items, weight, lm); \
+        hipLaunchKernelGGL((k_gram4<T, (T) <= 5 ? 4 : 2>), grid, block, 0, st, p.dev, L.pairs, L.items, L.n_items, weight, lm); \
         break;
         APX_G4(1) APX_G4(2) APX_G4(3) APX_G4(4) APX_G4(5) APX_G4(6) APX_G4(7) APX_G4(8) APX_G4(9)
 #undef APX_G4
@@ -449,7 +452,7 @@ hipError_t launch_cross4(const Plan& p, const PairLaunch& L, const float* weight
     switch (L.tm) {
 #define APX_X4(K)                                                                                              \
     case K:                                                                                                    \
-        hipLaunchKernelGGL((k_cross4<cross_a(K), cross_b(K)>), grid, block, 0, st, p, L.pairs, L.items, L.n_items, \
+        hipLaunchKernelGGL((k_cross4<cross_a(K), cross_b(K)>), grid, block, 0, st, p.dev, L.pairs, L.items, L.n_items, \
                            weight, lm);                                                                        \
         break;
         APX_X4(0) APX_X4(1) APX_X4(2) APX_X4(3) APX_X4(4) APX_X4(5) APX_X4(6) APX_X4(7) APX_X4(8)
@@ -472,7 +475,7 @@ int pair_blocks_per_cu() {
 hipError_t launch_pairs(const Plan& p, const PairLaunch& L, const float* weight,
                         const apx_lm_state* lm, hipStream_t st) {
     if (L.n_items <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_pair, dim3(L.n_items), dim3(256), 0, st, p, L.pairs, L.items, weight, lm);
+    hipLaunchKernelGGL(k_pair, dim3(L.n_items), dim3(256), 0, st, p.dev, L.pairs, L.items, weight, lm);
     return hipGetLastError();
 }
 
@@ -496,8 +499,9 @@ __device__ __forceinline__ double butterfly(double v) {
 }
 
 // One wave per (column, component).
-__global__ __launch_bounds__(256) void k_col_sums(Plan p, const int* __restrict__ col_seg,
+__global__ __launch_bounds__(256) void k_col_sums(PlanPtr pp, const int* __restrict__ col_seg,
                                                   const int* __restrict__ col_idx) {
+    PlanRef p = *pp;
     const int sf = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (sf >= 2 * p.n_cols) return;
     const int c = sf >> 1, q = sf & 1;
@@ -507,7 +511,7 @@ __global__ __launch_bounds__(256) void k_col_sums(Plan p, const int* __restrict_
 
 hipError_t launch_col_sums(const Plan& p, const int* col_seg, const int* col_idx, hipStream_t st) {
     if (p.n_cols <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_col_sums, dim3((2 * p.n_cols + 3) / 4), dim3(256), 0, st, p, col_seg, col_idx);
+    hipLaunchKernelGGL(k_col_sums, dim3((2 * p.n_cols + 3) / 4), dim3(256), 0, st, p.dev, col_seg, col_idx);
     return hipGetLastError();
 }
 
@@ -515,7 +519,8 @@ hipError_t launch_col_sums(const Plan& p, const int* col_seg, const int* col_idx
 // 256, ... (all three components), then a fixed butterfly per wave and the four waves in order;
 // thread 0 adds the images' chi^2 in order.  One launch instead of four (image sums, chi^2,
 // check or accept): at 64 x 64 they were 1.8 us of work and 5 us of launch each.
-__global__ __launch_bounds__(256) void k_tail(Plan p, TailIO io) {
+__global__ __launch_bounds__(256) void k_tail(PlanPtr pp, TailIO io) {
+    PlanRef p = *pp;
     __shared__ double red[4][3];
     __shared__ int acc_flag;
     const int s = blockIdx.x, lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -568,7 +573,7 @@ __global__ __launch_bounds__(256) void k_tail(Plan p, TailIO io) {
 }
 
 hipError_t launch_tail(const Plan& p, const TailIO& io, hipStream_t st) {
-    hipLaunchKernelGGL(k_tail, dim3(p.n_sub), dim3(256), 0, st, p, io);
+    hipLaunchKernelGGL(k_tail, dim3(p.n_sub), dim3(256), 0, st, p.dev, io);
     return hipGetLastError();
 }
 
@@ -641,9 +646,10 @@ hipError_t launch_assemble(const AsmA& a, hipStream_t st) {
 // Dense Jacobian for callers that want it: J[k * ldJ + i] = sum of the stored blocks of
 // the columns tied to theta index k (in column order) + 1 on the pixels of images whose
 // sky is theta index k.
-__global__ void k_jscatter(Plan p, const int* __restrict__ par_off, const int* __restrict__ par_cols,
+__global__ void k_jscatter(PlanPtr pp, const int* __restrict__ par_off, const int* __restrict__ par_cols,
                            const int* __restrict__ par_sky_off, const int* __restrict__ par_sky,
                            float* __restrict__ Jd, long long ldJ) {
+    PlanRef p = *pp;
     const int k = blockIdx.y;
     const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= p.n_pix) return;
@@ -675,7 +681,7 @@ hipError_t launch_jscatter(const Plan& p, const int* par_off, const int* par_col
                            hipStream_t st) {
     if (p.n_par == 0 || p.n_pix == 0) return hipSuccess;
     dim3 grid((unsigned)((p.n_pix + 255) / 256), p.n_par);
-    hipLaunchKernelGGL(k_jscatter, grid, dim3(256), 0, st, p, par_off, par_cols, par_sky_off,
+    hipLaunchKernelGGL(k_jscatter, grid, dim3(256), 0, st, p.dev, par_off, par_cols, par_sky_off,
                        par_sky, Jd, ldJ);
     return hipGetLastError();
 }

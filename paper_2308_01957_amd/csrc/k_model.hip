@@ -77,7 +77,7 @@ __device__ void shift_taps(int method, int a, double delta, double* w, double* d
 struct PrepBlocks { int comps, psf, begin, trial; };
 
 // theta[k] of the evaluation: the caller's, or with a step theta + h where the solve succeeded
-__device__ __forceinline__ double prep_theta(const Plan& p, const PrepIO& io, int k) {
+__device__ __forceinline__ double prep_theta(PlanRef p, const PrepIO& io, int k) {
     double v = io.theta[k];
     if (io.step) {
         const int s = p.par_sub[k];
@@ -89,7 +89,7 @@ __device__ __forceinline__ double prep_theta(const Plan& p, const PrepIO& io, in
 // Start of an iteration: clear the per-iteration flags of both solve copies and decide
 // whether a large sub-problem takes the step solved ahead: the same A (its last trial was
 // rejected, so no new normal equations) and the lambda that solve started from.
-__device__ __forceinline__ int lm_begin_sub(const Plan& p, const apx_lm_state* lm, int s) {
+__device__ __forceinline__ int lm_begin_sub(PlanRef p, const apx_lm_state* lm, int s) {
     LMFlags f;
     f.chol_done = 0;
     f.chol_fail = 0;
@@ -109,7 +109,7 @@ __device__ __forceinline__ int lm_begin_sub(const Plan& p, const apx_lm_state* l
 // an adopting sub-problem takes the step, its predicted decrease, lambda and retry count from
 // the solve made ahead (exactly what solving now would give: same A, D, g and starting
 // lambda, same kernels), and the record is used up.
-__device__ __forceinline__ void lm_adopt_sub(const Plan& p, apx_lm_state* lm, int s) {
+__device__ __forceinline__ void lm_adopt_sub(PlanRef p, apx_lm_state* lm, int s) {
     if (threadIdx.x >= 64) return;
     int adopted = 0;
     if (threadIdx.x == 0) adopted = lm_begin_sub(p, lm, s);
@@ -127,7 +127,7 @@ __device__ __forceinline__ void lm_adopt_sub(const Plan& p, apx_lm_state* lm, in
     }
 }
 
-__device__ void prep_comp(const Plan& p, const PrepIO& io, int i) {
+__device__ void prep_comp(PlanRef p, const PrepIO& io, int i) {
     const int lm_trial = io.mark;
     if (i < p.n_images) {
         const DImage& im = p.images[i];
@@ -231,7 +231,7 @@ __device__ void prep_comp(const Plan& p, const PrepIO& io, int i) {
 // normalised, with d/dn and d/dR_d of the normalised stamp (quotient rule), in FP64 and
 // as FP32 copies for the FP32 kernels; with io.flip, the flipped stamps of the adjoint.  One
 // workgroup per image; the sums are ordered.
-__device__ void prep_psf(const Plan& p, const PrepIO& io, int k) {
+__device__ void prep_psf(PlanRef p, const PrepIO& io, int k) {
     __shared__ double red[4][3];
     const int lm_trial = io.mark;
     const DImage& im = p.images[k];
@@ -306,7 +306,8 @@ __device__ void prep_psf(const Plan& p, const PrepIO& io, int k) {
     }
 }
 
-__global__ __launch_bounds__(256) void k_prep(Plan p, PrepIO io, PrepBlocks nb) {
+__global__ __launch_bounds__(256) void k_prep(PlanPtr pp, PrepIO io, PrepBlocks nb) {
+    PlanRef p = *pp;
     int b = (int)blockIdx.x;
     if (b < nb.comps) {
         prep_comp(p, io, b * 256 + (int)threadIdx.x);
@@ -339,7 +340,7 @@ hipError_t launch_prep(const Plan& p, const PrepIO& io, hipStream_t st) {
     nb.psf = p.n_images;
     nb.begin = !io.lm ? 0 : io.adopt ? p.n_sub : (p.n_sub + 255) / 256;
     nb.trial = io.step ? (p.n_par + 255) / 256 : 0;
-    hipLaunchKernelGGL(k_prep, dim3(nb.comps + nb.psf + nb.begin + nb.trial), dim3(256), 0, st, p, io, nb);
+    hipLaunchKernelGGL(k_prep, dim3(nb.comps + nb.psf + nb.begin + nb.trial), dim3(256), 0, st, p.dev, io, nb);
     return hipGetLastError();
 }
 
@@ -408,7 +409,7 @@ __device__ __forceinline__ bool within_kre(const CompConst& c, double ucx, doubl
 }
 
 // Pixel value (before the area factor) of a Sersic component.
-__device__ __forceinline__ float sersic_pixel(const Plan& p, const CompConst& c, const DImage& im,
+__device__ __forceinline__ float sersic_pixel(PlanRef p, const CompConst& c, const DImage& im,
                                               double ucx, double ucy) {
     const float dxc = (float)(ucx - c.x0), dyc = (float)(ucy - c.y0);
     if (p.mode == APX_MODE_WITHIN_K_RE && !within_kre(c, ucx, ucy)) return sersic_I(c, dxc, dyc);
@@ -431,7 +432,7 @@ __device__ __forceinline__ long long adapt_index(const DComp& cp, int y, int x) 
     return cp.aoff + (long long)(y - cp.box[0]) * (cp.box[3] - cp.box[1]) + (x - cp.box[1]);
 }
 
-__device__ __forceinline__ void sersic_pixel_grad(const Plan& p, const CompConst& c, const DImage& im,
+__device__ __forceinline__ void sersic_pixel_grad(PlanRef p, const CompConst& c, const DImage& im,
                                                   const DComp& cp, int y, int x, double ucx, double ucy,
                                                   float acc[7]) {
     for (int k = 0; k < 7; ++k) acc[k] = 0.f;
@@ -500,7 +501,7 @@ constexpr double bin_rho(int deg) { return deg == BIN_DEG ? 0.07 : 0.015; }
 constexpr int BIN_DEG_FAR = 7;
 
 template <int DEG, int S>
-__device__ __forceinline__ double pixel64_series(const Plan& p, const CompConst& c, double iv, double gx, double gy,
+__device__ __forceinline__ double pixel64_series(PlanRef p, const CompConst& c, double iv, double gx, double gy,
                                                  double B0, double X0, const double* __restrict__ tab) {
     const double ux = gx * iv, uy = gy * iv, wxx = c.qxx * iv, wxy = c.qxy * iv, wyy = c.qyy * iv;
     const double nB = -64.0 * B0, X64 = 64.0 * X0;   // exponents in units of 1/64
@@ -535,7 +536,7 @@ __device__ __forceinline__ double pixel64_series(const Plan& p, const CompConst&
 }
 
 template <int S>
-__device__ __forceinline__ double pixel64_nodes(const Plan& p, const CompConst& c, double xp0, double yq0,
+__device__ __forceinline__ double pixel64_nodes(PlanRef p, const CompConst& c, double xp0, double yq0,
                                                 const double* __restrict__ tab) {
     const Poly64Regs rg = poly64_regs(c);
     const double v0 = xp0 * xp0 + yq0 * yq0;
@@ -578,7 +579,7 @@ __device__ __forceinline__ double pixel64_nodes(const Plan& p, const CompConst& 
     return sum;
 }
 
-__device__ __forceinline__ double sersic_pixel64(const Plan& p, const CompConst& c, double ucx, double ucy,
+__device__ __forceinline__ double sersic_pixel64(PlanRef p, const CompConst& c, double ucx, double ucy,
                                                  const double* __restrict__ tab) {
     const double dxc = ucx - c.x0, dyc = ucy - c.y0;
     if (p.mode == APX_MODE_WITHIN_K_RE && !within_kre(c, ucx, ucy)) return sersic_I64_t(c, dxc, dyc, tab);
@@ -594,7 +595,7 @@ __device__ __forceinline__ double sersic_pixel64(const Plan& p, const CompConst&
 }
 
 // Stage the 2^x / log2 table into LDS (the caller synchronises before use).
-__device__ __forceinline__ void stage_ptab(const Plan& p, double* sh) {
+__device__ __forceinline__ void stage_ptab(PlanRef p, double* sh) {
     for (int k = (int)threadIdx.x; k < PTAB_N; k += (int)blockDim.x) sh[k] = p.ptab[k];
 }
 
@@ -610,7 +611,7 @@ constexpr int SH_H = RT_Y + 2 * APX_SHIFT_MAX_A, SH_W = RT_X + 2 * APX_SHIFT_MAX
 // and the component's taps into tw (wx, wy, dwx, dwy; SHIFT_NT each).  The caller
 // synchronises before reading them.
 template <int NPL, typename T, typename F>
-__device__ __forceinline__ void stage_halo(const Plan& p, int ci, const DComp& cp, int y0, int x0,
+__device__ __forceinline__ void stage_halo(PlanRef p, int ci, const DComp& cp, int y0, int x0,
                                            T (*sh)[SH_H * SH_W], T* tw, F&& f) {
     const int a = p.shift_a, HW = RT_X + 2 * a, n = (RT_Y + 2 * a) * HW;
     if (threadIdx.x < STAP_STRIDE) tw[threadIdx.x] = (T)p.stap[(long long)ci * STAP_STRIDE + threadIdx.x];
@@ -658,7 +659,7 @@ __device__ __forceinline__ T tap_sum(const T* plane, int a, int ly, int lx, cons
 // d/d(q, PA, n, Re, log Ie) are T * dS'/dtheta; x0 and y0 move only delta, so
 // d/d x0 = inv1 (dT/d delta_x * S') + inv4 (dT/d delta_y * S') (inv2, inv5 for y0), with
 // S' = (d/d log Ie plane) / ln 10.  Every thread of the block calls it.
-__device__ void shifted_derivs(const Plan& p, int ci, const CompConst& c, const DComp& cp, const DImage& im,
+__device__ void shifted_derivs(PlanRef p, int ci, const CompConst& c, const DComp& cp, const DImage& im,
                                int y0, int x0, int ly, int lx, bool want, float (*sh)[SH_H * SH_W],
                                float* tw, float out[7]) {
     stage_halo<5, float>(p, ci, cp, y0, x0, sh, tw, [&](int ry, int rx, float* v) {
@@ -687,7 +688,7 @@ __device__ void shifted_derivs(const Plan& p, int ci, const CompConst& c, const 
 // Pixel value T * S' (area included) of a re-centred Sersic at pixel (ly, lx) of the render
 // tile with origin (y0, x0); 0 where !want.  Every thread of the block calls it.
 template <typename T>
-__device__ T shifted_pixel(const Plan& p, int ci, const CompConst& c, const DComp& cp, const DImage& im, int y0,
+__device__ T shifted_pixel(PlanRef p, int ci, const CompConst& c, const DComp& cp, const DImage& im, int y0,
                            int x0, int ly, int lx, bool want, T (*sh)[SH_H * SH_W], T* tw,
                            const double* __restrict__ tab = nullptr) {
     stage_halo<1, T>(p, ci, cp, y0, x0, sh, tw, [&](int ry, int rx, T* v) {
@@ -707,7 +708,8 @@ __device__ T shifted_pixel(const Plan& p, int ci, const CompConst& c, const DCom
 // SHIFT: the problem re-centres its Sersics (a separate instantiation keeps the plain
 // kernels' register and LDS budgets)
 template <bool SHIFT>
-__global__ __launch_bounds__(256) void k_render(Plan p, int skip_mode, const apx_lm_state* lm) {
+__global__ __launch_bounds__(256) void k_render(PlanPtr pp, int skip_mode, const apx_lm_state* lm) {
+    PlanRef p = *pp;
     __shared__ float sh[1][SHIFT ? SH_H * SH_W : 1];
     __shared__ float tw[SHIFT ? STAP_STRIDE : 1];
     const RTile t = p.rtiles[blockIdx.x];
@@ -745,16 +747,17 @@ __global__ __launch_bounds__(256) void k_render(Plan p, int skip_mode, const apx
 hipError_t launch_render_mode(const Plan& p, int skip_mode, const apx_lm_state* lm, hipStream_t st) {
     if (p.n_rtiles == 0) return hipSuccess;
     if (p.shift != APX_SHIFT_NONE)
-        hipLaunchKernelGGL(k_render<true>, dim3(p.n_rtiles), dim3(256), 0, st, p, skip_mode, lm);
+        hipLaunchKernelGGL(k_render<true>, dim3(p.n_rtiles), dim3(256), 0, st, p.dev, skip_mode, lm);
     else
-        hipLaunchKernelGGL(k_render<false>, dim3(p.n_rtiles), dim3(256), 0, st, p, skip_mode, lm);
+        hipLaunchKernelGGL(k_render<false>, dim3(p.n_rtiles), dim3(256), 0, st, p.dev, skip_mode, lm);
     return hipGetLastError();
 }
 
 // ------------------------------------------------------------- FP64 render
 // S64 (extended grid, FP64): the objective path's render.
 template <bool SHIFT>
-__global__ __launch_bounds__(256) void k_render64(Plan p, int skip_mode, const apx_lm_state* lm) {
+__global__ __launch_bounds__(256, SHIFT ? 4 : 6) void k_render64(PlanPtr pp, int skip_mode, const apx_lm_state* lm) {
+    PlanRef p = *pp;
     __shared__ double sh[1][SHIFT ? SH_H * SH_W : 1];
     __shared__ double tw[SHIFT ? STAP_STRIDE : 1];
     __shared__ double ptab[PTAB_N];
@@ -795,9 +798,9 @@ __global__ __launch_bounds__(256) void k_render64(Plan p, int skip_mode, const a
 hipError_t launch_render64(const Plan& p, int skip_mode, const apx_lm_state* lm, hipStream_t st) {
     if (p.n_rtiles == 0) return hipSuccess;
     if (p.shift != APX_SHIFT_NONE)
-        hipLaunchKernelGGL(k_render64<true>, dim3(p.n_rtiles), dim3(256), 0, st, p, skip_mode, lm);
+        hipLaunchKernelGGL(k_render64<true>, dim3(p.n_rtiles), dim3(256), 0, st, p.dev, skip_mode, lm);
     else
-        hipLaunchKernelGGL(k_render64<false>, dim3(p.n_rtiles), dim3(256), 0, st, p, skip_mode, lm);
+        hipLaunchKernelGGL(k_render64<false>, dim3(p.n_rtiles), dim3(256), 0, st, p.dev, skip_mode, lm);
     return hipGetLastError();
 }
 
@@ -805,7 +808,8 @@ hipError_t launch_render64(const Plan& p, int skip_mode, const apx_lm_state* lm,
 // D[col] over the group's input box: the pixel-integrated derivative of each free
 // parameter of each component of the group (pre-convolution).
 template <bool SHIFT>
-__global__ __launch_bounds__(256) void k_deriv(Plan p, const apx_lm_state* lm) {
+__global__ __launch_bounds__(256) void k_deriv(PlanPtr pp, const apx_lm_state* lm) {
+    PlanRef p = *pp;
     __shared__ float sh[5][SHIFT ? SH_H * SH_W : 1];
     __shared__ float tw[SHIFT ? STAP_STRIDE : 1];
     const RTile t = p.gtiles[blockIdx.x];
@@ -849,9 +853,9 @@ __global__ __launch_bounds__(256) void k_deriv(Plan p, const apx_lm_state* lm) {
 hipError_t launch_deriv(const Plan& p, const apx_lm_state* lm, hipStream_t st) {
     if (p.n_gtiles == 0) return hipSuccess;
     if (p.shift != APX_SHIFT_NONE)
-        hipLaunchKernelGGL(k_deriv<true>, dim3(p.n_gtiles), dim3(256), 0, st, p, lm);
+        hipLaunchKernelGGL(k_deriv<true>, dim3(p.n_gtiles), dim3(256), 0, st, p.dev, lm);
     else
-        hipLaunchKernelGGL(k_deriv<false>, dim3(p.n_gtiles), dim3(256), 0, st, p, lm);
+        hipLaunchKernelGGL(k_deriv<false>, dim3(p.n_gtiles), dim3(256), 0, st, p.dev, lm);
     return hipGetLastError();
 }
 
@@ -863,7 +867,8 @@ __device__ __forceinline__ double wave_sum(double v) {
 
 // grad_part[col][tile] = sum over the tile of Abar * dS/dtheta_col (recomputed).
 template <bool SHIFT>
-__global__ __launch_bounds__(256) void k_grad_tiles(Plan p) {
+__global__ __launch_bounds__(256) void k_grad_tiles(PlanPtr pp) {
+    PlanRef p = *pp;
     __shared__ double red[4][7];
     __shared__ float sh[5][SHIFT ? SH_H * SH_W : 1];
     __shared__ float tw[SHIFT ? STAP_STRIDE : 1];
@@ -918,9 +923,9 @@ __global__ __launch_bounds__(256) void k_grad_tiles(Plan p) {
 hipError_t launch_grad_tiles(const Plan& p, hipStream_t st) {
     if (p.n_gtiles == 0) return hipSuccess;
     if (p.shift != APX_SHIFT_NONE)
-        hipLaunchKernelGGL(k_grad_tiles<true>, dim3(p.n_gtiles), dim3(256), 0, st, p);
+        hipLaunchKernelGGL(k_grad_tiles<true>, dim3(p.n_gtiles), dim3(256), 0, st, p.dev);
     else
-        hipLaunchKernelGGL(k_grad_tiles<false>, dim3(p.n_gtiles), dim3(256), 0, st, p);
+        hipLaunchKernelGGL(k_grad_tiles<false>, dim3(p.n_gtiles), dim3(256), 0, st, p.dev);
     return hipGetLastError();
 }
 
@@ -928,7 +933,8 @@ hipError_t launch_grad_tiles(const Plan& p, hipStream_t st) {
 // Block c of image k sums pixels c*256 + t + SEED_BLOCKS*256*m in FP64 (fixed order per
 // thread, then waves in order); one wave per image folds the SEED_BLOCKS partials.
 constexpr int SEED_BLOCKS = 64;
-__global__ __launch_bounds__(256) void k_seed_part(Plan p, const float* __restrict__ seed, double* part) {
+__global__ __launch_bounds__(256) void k_seed_part(PlanPtr pp, const float* __restrict__ seed, double* part) {
+    PlanRef p = *pp;
     __shared__ double red[4];
     const int k = blockIdx.y, c = blockIdx.x;
     const DImage& im = p.images[k];
@@ -942,7 +948,8 @@ __global__ __launch_bounds__(256) void k_seed_part(Plan p, const float* __restri
     if (threadIdx.x == 0) part[k * SEED_BLOCKS + c] = ((red[0] + red[1]) + red[2]) + red[3];
 }
 
-__global__ void k_seed_fold(Plan p, const double* __restrict__ part) {
+__global__ void k_seed_fold(PlanPtr pp, const double* __restrict__ part) {
+    PlanRef p = *pp;
     const int k = blockIdx.x;
     double v = part[k * SEED_BLOCKS + threadIdx.x];
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
@@ -952,8 +959,8 @@ __global__ void k_seed_fold(Plan p, const double* __restrict__ part) {
 hipError_t launch_seed_sums(const Plan& p, const float* seed, double* part, hipStream_t st) {
     static_assert(SEED_BLOCKS == 64, "one lane per partial in the fold");
     if (p.n_images == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_seed_part, dim3(SEED_BLOCKS, p.n_images), dim3(256), 0, st, p, seed, part);
-    hipLaunchKernelGGL(k_seed_fold, dim3(p.n_images), dim3(64), 0, st, p, part);
+    hipLaunchKernelGGL(k_seed_part, dim3(SEED_BLOCKS, p.n_images), dim3(256), 0, st, p.dev, seed, part);
+    hipLaunchKernelGGL(k_seed_fold, dim3(p.n_images), dim3(64), 0, st, p.dev, part);
     return hipGetLastError();
 }
 

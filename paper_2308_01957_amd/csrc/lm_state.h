@@ -5,7 +5,7 @@
 
 namespace apx {
 
-__device__ __forceinline__ void lm_init_state(const Plan& p, int s, double chi2, apx_lm_state* lm) {
+__device__ __forceinline__ void lm_init_state(PlanRef p, int s, double chi2, apx_lm_state* lm) {
     apx_lm_state st;
     st.lambda = APX_LM_LAMBDA0;
     st.chi2 = chi2;
@@ -23,7 +23,7 @@ __device__ __forceinline__ void lm_init_state(const Plan& p, int s, double chi2,
 }
 
 // Gain ratio, accept or reject, lambda; returns whether the trial parameters are accepted.
-__device__ __forceinline__ int lm_accept_state(const Plan& p, int s, double c2t, apx_lm_state* lm) {
+__device__ __forceinline__ int lm_accept_state(PlanRef p, int s, double c2t, apx_lm_state* lm) {
     apx_lm_state st = lm[s];
     const LMFlags f = p.lmf[s];
     int accept = 0;
