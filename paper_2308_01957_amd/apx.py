@@ -10,8 +10,10 @@ backward pass is the library's adjoint gradient.
 """
 from __future__ import annotations
 
+import contextlib
 import ctypes
 import os
+import threading
 from typing import Dict, List, Optional, Sequence
 
 import numpy as np
@@ -240,6 +242,7 @@ class Problem:
         self.spec = spec
         self.device = torch.device("cuda", device)
         self.stream = torch.cuda.Stream(device=self.device)
+        self._events = threading.local()
         self.n_par = int(spec["n_par"])
         self.n_sub = len(spec["subs"])
         self.objective = int(objective)
@@ -307,12 +310,32 @@ class Problem:
             msg = self.lib.apx_last_error(self._ctx).decode() if ctx and self._ctx else ""
             raise ApxError(status, msg or self.lib.apx_status_string(status).decode())
 
+    # The library's stream waits for the caller's before a call and the caller's for the
+    # library's after it, through one event per thread for each direction (Stream.wait_stream
+    # makes and destroys an event each time: 12.7 us against 4.8; an lm_run call without iterations
+    # takes 37 us of host time instead of 51).  Outputs are allocated on the
+    # caller's stream before the call, so they live in its memory pool like any of its tensors;
+    # inputs may belong to any stream and are marked as used by the library's.
+    def _order(self, first, then, name):
+        ev = getattr(self._events, name, None)
+        if ev is None:
+            ev = self.torch.cuda.Event()
+            setattr(self._events, name, ev)
+        ev.record(first)
+        then.wait_event(ev)
+
     def _enter(self, *tensors):
         cur = self.torch.cuda.current_stream(self.device)
-        self.stream.wait_stream(cur)
+        if cur != self.stream:
+            self._order(cur, self.stream, "enter")
         for t in tensors:
             if t is not None:
                 t.record_stream(self.stream)
+
+    def _on_device(self):
+        """The problem's device as the current one for the launches of a call."""
+        c = self.torch.cuda
+        return contextlib.nullcontext() if c.current_device() == self.device.index else c.device(self.device)
 
     def _pix(self, data, weight):
         t = self.torch
@@ -325,7 +348,9 @@ class Problem:
         check_buffer(state, self.device, t.uint8, self.n_sub * LM_STATE_BYTES, "state")
 
     def _leave(self):
-        self.torch.cuda.current_stream(self.device).wait_stream(self.stream)
+        cur = self.torch.cuda.current_stream(self.device)
+        if cur != self.stream:
+            self._order(self.stream, cur, "leave")
 
     def _dev(self, x, dtype):
         t = self.torch
@@ -366,11 +391,13 @@ class Problem:
     # ----------------------------------------------------------------- hot path
     def render(self, theta, out=None):
         th = self._theta(theta)
-        self._enter(th)
-        with self.torch.cuda.stream(self.stream):
-            if out is None:
-                out = self.torch.empty(self.n_pix, dtype=self.torch.float32, device=self.device)
+        if out is None:
+            out = self.torch.empty(self.n_pix, dtype=self.torch.float32, device=self.device)
+            self._enter(th)
+        else:
             check_buffer(out, self.device, self.torch.float32, self.n_pix, "out")
+            self._enter(th, out)
+        with self._on_device():
             self._check(self.lib.apx_render(self._prob, th.data_ptr(), out.data_ptr()))
         self._leave()
         return out
@@ -378,11 +405,13 @@ class Problem:
     def chi2(self, theta, data, weight, out=None):
         th = self._theta(theta)
         self._pix(data, weight)
-        self._enter(th, data, weight)
-        with self.torch.cuda.stream(self.stream):
-            if out is None:
-                out = self.torch.empty(self.n_sub, dtype=self.torch.float64, device=self.device)
+        if out is None:
+            out = self.torch.empty(self.n_sub, dtype=self.torch.float64, device=self.device)
+            self._enter(th, data, weight)
+        else:
             check_buffer(out, self.device, self.torch.float64, self.n_sub, "out")
+            self._enter(th, data, weight, out)
+        with self._on_device():
             self._check(self.lib.apx_chi2(self._prob, th.data_ptr(), data.data_ptr(), weight.data_ptr(),
                                           out.data_ptr()))
         self._leave()
@@ -391,9 +420,9 @@ class Problem:
     def jacobian(self, theta):
         """Dense J as a (n_par, n_pix) FP32 tensor (row k = d model / d theta_k)."""
         th = self._theta(theta)
+        J = self.torch.empty((self.n_par, self.n_pix), dtype=self.torch.float32, device=self.device)
         self._enter(th)
-        with self.torch.cuda.stream(self.stream):
-            J = self.torch.empty((self.n_par, self.n_pix), dtype=self.torch.float32, device=self.device)
+        with self._on_device():
             self._check(self.lib.apx_jacobian(self._prob, th.data_ptr(), J.data_ptr(), self.n_pix))
         self._leave()
         return J
@@ -402,12 +431,12 @@ class Problem:
         """(JtWJ flat per-sub blocks, JtWr [n_par], chi2 [n_sub]), FP64 device tensors."""
         th = self._theta(theta)
         self._pix(data, weight)
-        self._enter(th, data, weight)
         t = self.torch
-        with t.cuda.stream(self.stream):
-            A = t.empty(int(self.a_offsets[-1]), dtype=t.float64, device=self.device)
-            g = t.empty(self.n_par, dtype=t.float64, device=self.device)
-            c2 = t.empty(self.n_sub, dtype=t.float64, device=self.device)
+        A = t.empty(int(self.a_offsets[-1]), dtype=t.float64, device=self.device)
+        g = t.empty(self.n_par, dtype=t.float64, device=self.device)
+        c2 = t.empty(self.n_sub, dtype=t.float64, device=self.device)
+        self._enter(th, data, weight)
+        with self._on_device():
             self._check(self.lib.apx_jtwj(self._prob, th.data_ptr(), data.data_ptr(), weight.data_ptr(),
                                           A.data_ptr(), g.data_ptr(), c2.data_ptr()))
         self._leave()
@@ -421,11 +450,11 @@ class Problem:
         """((J^T W J)^{-1} flat per-sub blocks, chi2 [n_sub]), FP64 device tensors."""
         th = self._theta(theta)
         self._pix(data, weight)
-        self._enter(th, data, weight)
         t = self.torch
-        with t.cuda.stream(self.stream):
-            C = t.empty(max(1, int(self.a_offsets[-1])), dtype=t.float64, device=self.device)
-            c2 = t.empty(self.n_sub, dtype=t.float64, device=self.device)
+        C = t.empty(max(1, int(self.a_offsets[-1])), dtype=t.float64, device=self.device)
+        c2 = t.empty(self.n_sub, dtype=t.float64, device=self.device)
+        self._enter(th, data, weight)
+        with self._on_device():
             self._check(self.lib.apx_covariance(self._prob, th.data_ptr(), data.data_ptr(), weight.data_ptr(),
                                                 C.data_ptr(), c2.data_ptr()))
         self._leave()
@@ -435,11 +464,11 @@ class Problem:
         """(F flat per-sub blocks with F F^T = (J^T W J)^{-1}, chi2 [n_sub]), FP64 device tensors."""
         th = self._theta(theta)
         self._pix(data, weight)
-        self._enter(th, data, weight)
         t = self.torch
-        with t.cuda.stream(self.stream):
-            F = t.empty(max(1, int(self.a_offsets[-1])), dtype=t.float64, device=self.device)
-            c2 = t.empty(self.n_sub, dtype=t.float64, device=self.device)
+        F = t.empty(max(1, int(self.a_offsets[-1])), dtype=t.float64, device=self.device)
+        c2 = t.empty(self.n_sub, dtype=t.float64, device=self.device)
+        self._enter(th, data, weight)
+        with self._on_device():
             self._check(self.lib.apx_covariance_factor(self._prob, th.data_ptr(), data.data_ptr(),
                                                        weight.data_ptr(), F.data_ptr(), c2.data_ptr()))
         self._leave()
@@ -461,10 +490,10 @@ class Problem:
             raise ValueError("F must hold the per-sub blocks (sum of n_s^2 entries)")
         self._pix(data, weight)
         check_buffer(theta, self.device, t.float64, self.n_par, "theta")
+        samples = t.empty((n_samples, self.n_par), dtype=t.float64, device=self.device)
+        stats = t.empty((n_samples, self.n_sub, 3), dtype=t.float64, device=self.device)
         self._enter(theta, data, weight, F, z, u)
-        with t.cuda.stream(self.stream):
-            samples = t.empty((n_samples, self.n_par), dtype=t.float64, device=self.device)
-            stats = t.empty((n_samples, self.n_sub, 3), dtype=t.float64, device=self.device)
+        with self._on_device():
             self._check(self.lib.apx_hmc_run(self._prob, data.data_ptr(), weight.data_ptr(), theta.data_ptr(),
                                              F.data_ptr(), float(step), int(n_leapfrog), n_samples,
                                              z.data_ptr(), u.data_ptr(), samples.data_ptr(), stats.data_ptr()))
@@ -489,10 +518,10 @@ class Problem:
             raise ValueError("F must hold the per-sub blocks (sum of n_s^2 entries)")
         self._pix(data, weight)
         check_buffer(theta, self.device, t.float64, self.n_par, "theta")
+        samples = t.empty((n_samples, self.n_par), dtype=t.float64, device=self.device)
+        stats = t.empty((n_samples, 4), dtype=t.float64, device=self.device)
         self._enter(theta, data, weight, F, z, u)
-        with t.cuda.stream(self.stream):
-            samples = t.empty((n_samples, self.n_par), dtype=t.float64, device=self.device)
-            stats = t.empty((n_samples, 4), dtype=t.float64, device=self.device)
+        with self._on_device():
             self._check(self.lib.apx_nuts_run(self._prob, data.data_ptr(), weight.data_ptr(), theta.data_ptr(),
                                               F.data_ptr(), float(step), int(max_depth), n_samples,
                                               z.data_ptr(), u.data_ptr(), samples.data_ptr(), stats.data_ptr()))
@@ -514,7 +543,7 @@ class Problem:
         self._pix(data, weight)
         check_buffer(theta, self.device, t.float64, self.n_par, "theta")
         self._enter(theta, data, weight, F, z, u)
-        with t.cuda.stream(self.stream):
+        with self._on_device():
             self._check(self.lib.apx_nuts_warmup(self._prob, data.data_ptr(), weight.data_ptr(), theta.data_ptr(),
                                                  F.data_ptr(), ctypes.byref(step), int(max_depth), n,
                                                  float(target), z.data_ptr(), u.data_ptr()))
@@ -527,11 +556,12 @@ class Problem:
         gm = self._dev(grad_model, self.torch.float32)
         if gm.numel() != self.n_pix:
             raise ValueError(f"grad_model has {gm.numel()} entries, the render has {self.n_pix} pixels")
-        self._enter(th, gm)
         t = self.torch
-        with t.cuda.stream(self.stream):
-            if out is None:
-                out = t.empty(self.n_par, dtype=t.float64, device=self.device)
+        given = out
+        if out is None:
+            out = t.empty(self.n_par, dtype=t.float64, device=self.device)
+        self._enter(th, gm, given)
+        with self._on_device():
             self._check(self.lib.apx_render_vjp(self._prob, th.data_ptr(), gm.data_ptr(), out.data_ptr()))
         self._leave()
         return out
@@ -539,11 +569,11 @@ class Problem:
     def chi2_grad(self, theta, data, weight):
         th = self._theta(theta)
         self._pix(data, weight)
-        self._enter(th, data, weight)
         t = self.torch
-        with t.cuda.stream(self.stream):
-            g = t.empty(self.n_par, dtype=t.float64, device=self.device)
-            c2 = t.empty(self.n_sub, dtype=t.float64, device=self.device)
+        g = t.empty(self.n_par, dtype=t.float64, device=self.device)
+        c2 = t.empty(self.n_sub, dtype=t.float64, device=self.device)
+        self._enter(th, data, weight)
+        with self._on_device():
             self._check(self.lib.apx_chi2_grad(self._prob, th.data_ptr(), data.data_ptr(), weight.data_ptr(),
                                                g.data_ptr(), c2.data_ptr()))
         self._leave()
@@ -559,15 +589,15 @@ class Problem:
             check_buffer(theta_out, self.device, t.float64, self.n_par, "theta_out")
         if state_out is not None:
             check_buffer(state_out, self.device, t.uint8, self.n_sub * LM_STATE_BYTES, "state_out")
-        self._enter(src, data, weight)
-        with t.cuda.stream(self.stream):
-            if theta_out is None:
-                th = src.clone()
-            else:
-                th = theta_out
-                th.copy_(src)
-            state = state_out if state_out is not None else \
-                t.zeros(self.n_sub * LM_STATE_BYTES, dtype=t.uint8, device=self.device)
+        if theta_out is None:
+            th = src.clone()
+        else:
+            th = theta_out
+            th.copy_(src)
+        state = state_out if state_out is not None else \
+            t.zeros(self.n_sub * LM_STATE_BYTES, dtype=t.uint8, device=self.device)
+        self._enter(src, data, weight, theta_out, state_out)
+        with self._on_device():
             self._check(self.lib.apx_lm_init(self._prob, th.data_ptr(), data.data_ptr(), weight.data_ptr(),
                                              state.data_ptr()))
         self._leave()
@@ -577,7 +607,7 @@ class Problem:
         self._pix(data, weight)
         self._lm_bufs(theta, state)
         self._enter(data, weight, theta, state)
-        with self.torch.cuda.stream(self.stream):
+        with self._on_device():
             self._check(self.lib.apx_lm_step(self._prob, data.data_ptr(), weight.data_ptr(), theta.data_ptr(),
                                              state.data_ptr()))
         self._leave()
@@ -586,7 +616,7 @@ class Problem:
         self._pix(data, weight)
         self._lm_bufs(theta, state)
         self._enter(data, weight, theta, state)
-        with self.torch.cuda.stream(self.stream):
+        with self._on_device():
             self._check(self.lib.apx_lm_run(self._prob, int(n_iter), data.data_ptr(), weight.data_ptr(),
                                             theta.data_ptr(), state.data_ptr(), 1 if use_graph else 0))
         self._leave()
