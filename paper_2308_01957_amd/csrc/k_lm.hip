@@ -4,7 +4,7 @@
 // next evaluation (k_prep); the gain ratio, accept or reject and the lambda update end it
 // (k_tail, lm_state.h).  All control stays on the device so an iteration can be captured in
 // a HIP graph; every sub-problem carries its own state.
-#include "apx_internal.h"
+#include "chol_rows.h"
 
 namespace apx {
 
@@ -17,24 +17,6 @@ __device__ __forceinline__ double lm_wave_max(double v) {
     return v;
 }
 
-// 1/sqrt(x) for positive normal x: the hardware estimate refined by two Newton steps
-// y <- y (3 - x y^2) / 2 (each roughly doubles the correct bits), a short dependent chain
-// on the factorisation's critical path.
-__device__ __forceinline__ double rsqrt_f64(double x) {
-    double y = __builtin_amdgcn_rsq(x);
-    const double hx = 0.5 * x;
-    y = y * fma(-hx * y, y, 1.5);
-    y = y * fma(-hx * y, y, 1.5);
-    return y;
-}
-
-// Value of v in lane `src` (a compile-time constant after unrolling), to every lane.
-__device__ __forceinline__ double lane_bcast(double v, int src) {
-    const int lo = __builtin_amdgcn_readlane(__double2loint(v), src);
-    const int hi = __builtin_amdgcn_readlane(__double2hiint(v), src);
-    return __hiloint2double(hi, lo);
-}
-
 // -------------------------------------------------------------- small sub-problems
 // One wave64 per sub-problem (n <= 64), one row of the damped matrix per lane in registers (N
 // columns, N the next of a few sizes >= n, padded with identity rows): a right-looking Cholesky
@@ -43,31 +25,6 @@ __device__ __forceinline__ double lane_bcast(double v, int src) {
 // of its serial chain bounds it: with the rows in LDS and each step behind three barriers the
 // largest of 768 cutouts (36 parameters) took 64 us and one 8-parameter system 10 us.  The
 // retries happen inside the kernel.
-template <int N>
-__device__ __forceinline__ bool chol_rows(const double* __restrict__ A, int n, double lamD, double (&a)[N], double& rinv) {
-    const int i = threadIdx.x;
-#pragma unroll
-    for (int j = 0; j < N; ++j) a[j] = (i < n && j < n) ? A[(long long)i * n + j] : (i == j ? 1.0 : 0.0);
-#pragma unroll
-    for (int j = 0; j < N; ++j)
-        if (i == j && j < n) a[j] += lamD;
-    bool ok = true;
-    rinv = 1.0;
-#pragma unroll
-    for (int k = 0; k < N; ++k) {
-        double piv = lane_bcast(a[k], k);
-        // a failed pivot is recorded and replaced by 1 so the (discarded) factor stays finite
-        if (!(piv > 0.0) || !isfinite(piv)) { ok = false; piv = 1.0; }
-        const double r = rsqrt_f64(piv);
-        const double l = i > k ? a[k] * r : 0.0;
-        a[k] = i > k ? l : (i == k ? piv * r : a[k]);
-        if (i == k) rinv = r;
-#pragma unroll
-        for (int j = k + 1; j < N; ++j) a[j] = fma(-l, lane_bcast(l, j), a[j]);
-    }
-    return ok;
-}
-
 template <int N>
 __device__ __forceinline__ void chol_small_n(const Plan& p, int s, const DSub& sb, apx_lm_state* lm, double* sm) {
     const int n = sb.n, i = threadIdx.x;
