@@ -131,6 +131,27 @@ __device__ __forceinline__ bool conv_skipped(PlanRef p, const ConvIO& io, int su
     return false;
 }
 
+// The stamp into LDS (rows KP long), for the fine tiles: a launch of few tiles has one wave or
+// two per SIMD, too few to hide that each row's scalar loads of a stamp that another kernel has
+// just written go out to the last-level cache; one round of vector loads beside the input's
+// takes their place (a 128 x 128 gradient at P = 25: 17 -> 11 us per FP32 launch, 13.2 -> 12.6 in
+// FP64, where LDS reads bound the rest).
+template <int P, int KP, int NT, typename T>
+__device__ inline void stage_stamp(T* __restrict__ kt, const T* __restrict__ K) {
+    constexpr int NE = (P * P + NT - 1) / NT;
+    T v[NE];
+#pragma unroll
+    for (int q = 0; q < NE; ++q) {
+        const int e = (int)threadIdx.x + NT * q;
+        v[q] = e < P * P ? K[e] : T(0);
+    }
+#pragma unroll
+    for (int q = 0; q < NE; ++q) {
+        const int e = (int)threadIdx.x + NT * q;
+        if (e < P * P) kt[(e / P) * KP + e % P] = v[q];
+    }
+}
+
 // The FP32 kinds.
 template <int P, int KIND, int TH, int TW, int R>
 __global__ __launch_bounds__(TH * TW / R) void k_conv(PlanPtr pp, const ConvJob* __restrict__ jobs,
@@ -148,6 +169,9 @@ __global__ __launch_bounds__(TH * TW / R) void k_conv(PlanPtr pp, const ConvJob*
     constexpr int LW = (LW0 + 3) & ~3;
     __shared__ __attribute__((aligned(16))) T tile[LH * LW];
     __shared__ double red[NW][3];
+    constexpr bool KLDS = R != CV_R;
+    constexpr int KP = (P + 3) & ~3;
+    __shared__ __attribute__((aligned(16))) T kt[KLDS ? P * KP : 1];
 
     const int item_idx = item_begin + xcd_chunk_item((int)blockIdx.x, (int)gridDim.x);
     const ConvItem it = items[item_idx];
@@ -157,6 +181,13 @@ __global__ __launch_bounds__(TH * TW / R) void k_conv(PlanPtr pp, const ConvJob*
     const int oy0 = jb.out_y0 + it.ty * TH;
     const int ox0 = jb.out_x0 + it.tx * TW;
     const int iy_base = oy0 - c, ix_base = ox0 - c;
+    // the stamp: the flipped stamp for the adjoint; on a live-PSF image the rendered stamp, or
+    // for its PSF columns a derivative stamp
+    const float* __restrict__ K;
+    if constexpr (KIND == CONV_ADJ) K = p.psf_flip + im.psf_off;
+    else K = im.live ? p.psf_live + im.live_off + (long long)jb.kslot[it.ch < 1 ? 0 : 1] * P * P
+                     : p.psf + im.psf_off;
+    if constexpr (KLDS) stage_stamp<P, KP, NT>(kt, K);
 
     // ---- stage the input tile (zero outside the input rectangle); every load of a thread
     // is issued before its LDS stores so the latencies overlap
@@ -202,12 +233,6 @@ __global__ __launch_bounds__(TH * TW / R) void k_conv(PlanPtr pp, const ConvJob*
 
     // ---- register-window convolution
     const int ty = (int)threadIdx.x / LPR, tx = (int)threadIdx.x % LPR;
-    // the stamp: the flipped stamp for the adjoint; on a live-PSF image the rendered stamp, or
-    // for its PSF columns a derivative stamp
-    const float* __restrict__ K;
-    if constexpr (KIND == CONV_ADJ) K = p.psf_flip + im.psf_off;
-    else K = im.live ? p.psf_live + im.live_off + (long long)jb.kslot[it.ch < 1 ? 0 : 1] * P * P
-                     : p.psf + im.psf_off;
     T acc[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) acc[r] = 0;
@@ -225,7 +250,8 @@ __global__ __launch_bounds__(TH * TW / R) void k_conv(PlanPtr pp, const ConvJob*
             // gfx950 issues FMAs of VGPR operands from two waves at once, FMAs that read an
             // SGPR one at a time (measured 124 vs 76 TFLOP/s)
             T kv;
-            asm("v_mov_b32 %0, %1" : "=v"(kv) : "s"(K[U * P + V]));
+            if constexpr (KLDS) kv = kt[U * KP + V];
+            else asm("v_mov_b32 %0, %1" : "=v"(kv) : "s"(K[U * P + V]));
 #pragma unroll
             for (int r = 0; r < R; ++r) part[r] = fma(kv, s[r + P - 1 - V], part[r]);
         }
@@ -348,6 +374,9 @@ __global__ __launch_bounds__(TH * TW / R) void k_conv64(PlanPtr pp, const ConvJo
     constexpr int LW = pitch64(LW0);
     __shared__ __attribute__((aligned(16))) double tile[LH * LW];
     __shared__ double red[NW][3];
+    constexpr bool KLDS = R != CV_R;
+    constexpr int KP = (P + 1) & ~1;
+    __shared__ __attribute__((aligned(16))) double kt[KLDS ? P * KP : 1];
 
     const int item_idx = item_begin + xcd_chunk_item((int)blockIdx.x, (int)gridDim.x);
     const ConvItem it = items[item_idx];
@@ -357,6 +386,12 @@ __global__ __launch_bounds__(TH * TW / R) void k_conv64(PlanPtr pp, const ConvJo
     const int oy0 = jb.out_y0 + it.ty * TH;
     const int ox0 = jb.out_x0 + it.tx * TW;
     const int iy_base = oy0 - c, ix_base = ox0 - c;
+
+    // the stamp does not change during the launch: scalar loads, which the barriers would
+    // otherwise turn into vector loads
+    using Const = const __attribute__((address_space(4))) double*;
+    const Const K = (Const)(p.psf64 + im.psf_off);
+    if constexpr (KLDS) stage_stamp<P, KP, NT>(kt, p.psf64 + im.psf_off);
 
     // ---- stage the input tile (zero outside the input rectangle), NB loads of a thread at a
     // time before their LDS stores
@@ -389,22 +424,18 @@ __global__ __launch_bounds__(TH * TW / R) void k_conv64(PlanPtr pp, const ConvJo
 
     // ---- register-window convolution
     const int ty = (int)threadIdx.x / LPR, tx = (int)threadIdx.x % LPR;
-    // the stamp does not change during the launch: scalar loads, which the barriers below would
-    // otherwise turn into vector loads
-    using Const = const __attribute__((address_space(4))) double*;
-    const Const K = (Const)(p.psf64 + im.psf_off);
     double acc[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) acc[r] = 0.0;
     constexpr int N = R + P - 1, NC = (P + CH64 - 1) / CH64;
     constexpr bool PINNED = P > (R == CV_R ? 41 : 51);
-    // acc[r] += sum_j kk[P - 1 - j] s[r + j], s the window that starts at pair o1 of the tile
+    // acc[r] += sum_j K[U, P - 1 - j] s[r + j], s the window that starts at pair o1 of the tile
     // (with TWO: plus the one at pair o2), read as pairs (ds_read_b128).  pin() keeps the
     // pieces apart: a piece's FMAs come before it, the reads that follow (whose offsets pass
     // through it) after.
     static_assert(N % 2 == 0 && R % 2 == 0 && LW % 2 == 0 && CH64 % 2 == 0, "windows are whole pairs");
     const double2* tile2 = reinterpret_cast<const double2*>(tile);
-    auto row = [&](auto two, int o1, int o2, Const kk) {
+    auto row = [&](auto two, int o1, int o2, int U) {
         constexpr bool TWO = decltype(two)::value;
         double s[N], part[R];
         double2 a[CH64 / 2], b[CH64 / 2];
@@ -453,7 +484,9 @@ __global__ __launch_bounds__(TH * TW / R) void k_conv64(PlanPtr pp, const ConvJo
             for (int q = 0; q < CH64; ++q) {
                 const int j = ch * CH64 + q;
                 if (j < P) {
-                    const double kv = kk[P - 1 - j];
+                    double kv;
+                    if constexpr (KLDS) kv = kt[U * KP + P - 1 - j];
+                    else kv = K[U * P + P - 1 - j];
 #pragma unroll
                     for (int r = 0; r < R; ++r) part[r] = fma(kv, s[r + j], part[r]);
                 }
@@ -465,8 +498,8 @@ __global__ __launch_bounds__(TH * TW / R) void k_conv64(PlanPtr pp, const ConvJo
     };
     const int o0 = (ty * LW + tx * R) / 2;
     const int npair = p.psf_sym[jb.image] ? c : 0;   // block-uniform
-    for (int U = 0; U < npair; ++U) row(std::true_type{}, o0 + (P - 1 - U) * (LW / 2), o0 + U * (LW / 2), K + U * P);
-    for (int U = npair; U < P - npair; ++U) row(std::false_type{}, o0 + (P - 1 - U) * (LW / 2), o0, K + U * P);
+    for (int U = 0; U < npair; ++U) row(std::true_type{}, o0 + (P - 1 - U) * (LW / 2), o0 + U * (LW / 2), U);
+    for (int U = npair; U < P - npair; ++U) row(std::false_type{}, o0 + (P - 1 - U) * (LW / 2), o0, U);
 
     // ---- epilogue
     const int y = oy0 + ty;
