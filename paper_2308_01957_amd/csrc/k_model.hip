@@ -865,11 +865,30 @@ __device__ __forceinline__ double wave_sum(double v) {
     return v;
 }
 
+// The sums of v[0..6] over the wave, v[q]'s in lanes 8 q .. 8 q + 7: lanes that differ in one
+// bit of the lane halve the values they hold between them, then each sum finishes in its eight
+// lanes.  10 exchanges of a double; a butterfly for each value takes 42.
+__device__ __forceinline__ double wave_sum7(const double (&v)[7], int lane) {
+    double a[4], b[2];
+    const bool h5 = lane & 32, h4 = lane & 16, h3 = lane & 8;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const double hi = k + 4 < 7 ? v[k + 4 < 7 ? k + 4 : 0] : 0.0;
+        a[k] = (h5 ? hi : v[k]) + __shfl_xor(h5 ? v[k] : hi, 32, 64);
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k) b[k] = (h4 ? a[k + 2] : a[k]) + __shfl_xor(h4 ? a[k] : a[k + 2], 16, 64);
+    double s = (h3 ? b[1] : b[0]) + __shfl_xor(h3 ? b[0] : b[1], 8, 64);
+#pragma unroll
+    for (int o = 4; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+    return s;
+}
+
 // grad_part[col][tile] = sum over the tile of Abar * dS/dtheta_col (recomputed).
 template <bool SHIFT>
 __global__ __launch_bounds__(256) void k_grad_tiles(PlanPtr pp) {
     PlanRef p = *pp;
-    __shared__ double red[4][7];
+    __shared__ double red[2][4][8];                // by turns: one barrier per component
     __shared__ float sh[5][SHIFT ? SH_H * SH_W : 1];
     __shared__ float tw[SHIFT ? STAP_STRIDE : 1];
     const RTile t = p.gtiles[blockIdx.x];
@@ -889,34 +908,32 @@ __global__ __launch_bounds__(256) void k_grad_tiles(PlanPtr pp) {
         const int ci = p.group_comps[k];
         const DComp& cp = p.comps[ci];
         const CompConst& c = p.cc[ci];
-        double v[7];
-        if (SHIFT && cp.type == APX_SERSIC) {      // block-uniform
+        double(&rd)[4][8] = red[(k - gr.comp_begin) & 1];
+        if (cp.type == APX_SERSIC) {               // block-uniform
+            double v[7];
             float acc[7] = {};
-            if constexpr (SHIFT)
+            if constexpr (SHIFT) {
                 shifted_derivs(p, ci, c, cp, im, gr.iy0 + t.y0, gr.ix0 + t.x0, ly - t.y0, lx - t.x0, inside, sh, tw,
                                acc);
-            for (int q = 0; q < 7; ++q) v[q] = (double)acc[q] * (double)abar;
-        } else if (cp.type == APX_SERSIC) {
-            float acc[7];
-            if (inside) sersic_pixel_grad(p, c, im, cp, y, x, ucx, ucy, acc);
-            else for (int q = 0; q < 7; ++q) acc[q] = 0.f;
-            for (int q = 0; q < 7; ++q) v[q] = (double)acc[q] * im.area * (double)abar;
-        } else {
-            for (int q = 0; q < 7; ++q) v[q] = 0.0;
-            if (inside) v[2] = (double)c.F * point_weight(c, y, x) * 2.302585092994046 * (double)abar;
-        }
-        for (int q = 0; q < 7; ++q) {
-            if (cp.col[q] < 0) continue;            // uniform across the block
-            const double s = wave_sum(v[q]);
-            if (lane == 0) red[wv][q] = s;
+                for (int q = 0; q < 7; ++q) v[q] = (double)acc[q] * (double)abar;
+            } else {
+                if (inside) sersic_pixel_grad(p, c, im, cp, y, x, ucx, ucy, acc);
+                for (int q = 0; q < 7; ++q) v[q] = (double)acc[q] * im.area * (double)abar;
+            }
+            const double s = wave_sum7(v, lane);
+            if ((lane & 7) == 0) rd[wv][lane >> 3] = s;
+        } else if (cp.col[2] >= 0) {
+            double v = 0.0;
+            if (inside) v = (double)c.F * point_weight(c, y, x) * 2.302585092994046 * (double)abar;
+            v = wave_sum(v);
+            if (lane == 0) rd[wv][2] = v;
         }
         __syncthreads();
         if (threadIdx.x < 7 && cp.col[threadIdx.x] >= 0) {
             const int q = threadIdx.x;
-            const double s = ((red[0][q] + red[1][q]) + red[2][q]) + red[3][q];
+            const double s = ((rd[0][q] + rd[1][q]) + rd[2][q]) + rd[3][q];
             p.grad_part[gr.gp_off + (long long)cp.col[q] * gr.ntiles + tile_local] = s;
         }
-        __syncthreads();
     }
 }
 
