@@ -438,6 +438,9 @@ static int choose_group_shape(apx_ctx* C, int key, int P, const std::vector<int>
     return best;
 }
 
+// Derivative and gradient launches of fewer group tiles than this split the groups' components.
+static constexpr int G_SPLIT_WG = 1024;
+
 // Convolution launches of fewer tiles than this (half the compute units) go fine.
 static constexpr int FINE_TILES = 128;
 
@@ -1905,6 +1908,13 @@ apx_status apx_problem_bind_workspace(apx_problem* P, void* dev, uint64_t bytes)
     p.rtile_comps = wsp<int>(P, "rtile_comps");
     p.gtiles = wsp<RTile>(P, "gtiles");
     p.n_gtiles = (int)P->gtiles.size();
+    // Few group tiles: the components of a group are dealt to several workgroups, up to one per
+    // component, until there are G_SPLIT_WG (4 per compute unit; GSPLIT_FIGS).
+    {
+        int most = 1;
+        for (const DGroup& g : P->groups) most = std::max(most, g.comp_end - g.comp_begin);
+        p.g_split = std::max(1, std::min(most, G_SPLIT_WG / std::max(1, p.n_gtiles)));
+    }
     p.cc = wsp<CompConst>(P, "cc");
     p.stap = wsp<double>(P, "stap");
     p.S = wsp<float>(P, "S");

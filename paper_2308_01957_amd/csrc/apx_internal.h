@@ -256,6 +256,7 @@ struct Plan {
     const int* rtile_off; const int* rtile_comps;
     // deriv/grad tiles
     const RTile* gtiles; int n_gtiles;
+    int g_split;              // workgroups that share a group tile's components (k_deriv, k_grad_tiles)
 
     // buffers
     CompConst* cc;

@@ -824,7 +824,7 @@ __global__ __launch_bounds__(256) void k_deriv(PlanPtr pp, const apx_lm_state* l
     const double ucy = im.aff[3] + im.aff[4] * x + im.aff[5] * y;
     const long long plane = (long long)gr.ih * gr.iw;
     float* Dg = p.D + gr.d_off + (long long)ly * gr.iw + lx;
-    for (int k = gr.comp_begin; k < gr.comp_end; ++k) {
+    for (int k = gr.comp_begin + (int)blockIdx.y; k < gr.comp_end; k += (int)gridDim.y) {
         const int ci = p.group_comps[k];
         const DComp& cp = p.comps[ci];
         const CompConst& c = p.cc[ci];
@@ -853,9 +853,9 @@ __global__ __launch_bounds__(256) void k_deriv(PlanPtr pp, const apx_lm_state* l
 hipError_t launch_deriv(const Plan& p, const apx_lm_state* lm, hipStream_t st) {
     if (p.n_gtiles == 0) return hipSuccess;
     if (p.shift != APX_SHIFT_NONE)
-        hipLaunchKernelGGL(k_deriv<true>, dim3(p.n_gtiles), dim3(256), 0, st, p.dev, lm);
+        hipLaunchKernelGGL(k_deriv<true>, dim3(p.n_gtiles, p.g_split), dim3(256), 0, st, p.dev, lm);
     else
-        hipLaunchKernelGGL(k_deriv<false>, dim3(p.n_gtiles), dim3(256), 0, st, p.dev, lm);
+        hipLaunchKernelGGL(k_deriv<false>, dim3(p.n_gtiles, p.g_split), dim3(256), 0, st, p.dev, lm);
     return hipGetLastError();
 }
 
@@ -904,11 +904,13 @@ __global__ __launch_bounds__(256) void k_grad_tiles(PlanPtr pp) {
     float abar = 0.f;
     if (inside) abar = p.Abar[im.ext_off + (long long)(y + im.c) * im.EW + (x + im.c)];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    for (int k = gr.comp_begin; k < gr.comp_end; ++k) {
+    int turn = 0;
+    for (int k = gr.comp_begin + (int)blockIdx.y; k < gr.comp_end; k += (int)gridDim.y) {
         const int ci = p.group_comps[k];
         const DComp& cp = p.comps[ci];
         const CompConst& c = p.cc[ci];
-        double(&rd)[4][8] = red[(k - gr.comp_begin) & 1];
+        double(&rd)[4][8] = red[turn];
+        turn ^= 1;
         if (cp.type == APX_SERSIC) {               // block-uniform
             double v[7];
             float acc[7] = {};
@@ -940,9 +942,9 @@ __global__ __launch_bounds__(256) void k_grad_tiles(PlanPtr pp) {
 hipError_t launch_grad_tiles(const Plan& p, hipStream_t st) {
     if (p.n_gtiles == 0) return hipSuccess;
     if (p.shift != APX_SHIFT_NONE)
-        hipLaunchKernelGGL(k_grad_tiles<true>, dim3(p.n_gtiles), dim3(256), 0, st, p.dev);
+        hipLaunchKernelGGL(k_grad_tiles<true>, dim3(p.n_gtiles, p.g_split), dim3(256), 0, st, p.dev);
     else
-        hipLaunchKernelGGL(k_grad_tiles<false>, dim3(p.n_gtiles), dim3(256), 0, st, p.dev);
+        hipLaunchKernelGGL(k_grad_tiles<false>, dim3(p.n_gtiles, p.g_split), dim3(256), 0, st, p.dev);
     return hipGetLastError();
 }
 
