@@ -1335,19 +1335,16 @@ static apx_status build_plan(apx_problem* P, const apx_problem_desc* d) {
             slices = std::min(slices, std::max(1, w.stages / 32));
             add_pair_items(w.pi, w.na, w.nb, w.tri, w.stages, ceil_div(w.stages, slices));
         }
-        // The items of one launch: runs of pixels of every pair's box (bands of rows keep the
-        // pixel count of a band in 30 bits).  A run is 256 .. 4096 pixels, as short as it takes
-        // to make GRAM_ITEMS items: with few workgroups on the chip the kernel waits for its
-        // loads (three Jacobian phases of 768 cutouts, all tile counts: 1525 us with runs of
-        // 4096 pixels of padded rows, 989 us with these), and more partials cost the assembly.
+        // The items of one launch of two groups: runs of pixels of every pair's box (bands of rows
+        // keep the pixel count of a band in 30 bits).  A run is 256 .. 4096 pixels, as short as it
+        // takes to make GRAM_ITEMS items: with few workgroups on the chip the kernel waits for
+        // its loads, and more partials cost the assembly.
         constexpr int GRAM_ITEMS = 2048;
-        auto add_runs = [&](const std::vector<Narrow>& list, std::vector<PairItem>& items, int ba, int bb,
-                            long long entries) {
-            auto blocks = [&](const Narrow& w) { return ba ? (long long)ceil_div(w.na, ba) * ceil_div(w.nb, bb) : 1LL; };
+        auto add_runs = [&](const std::vector<Narrow>& list, std::vector<PairItem>& items, int ba, int bb) {
             double px = 0.0;
             for (const Narrow& w : list) {
                 const DPair& pr = P->pairs[w.pi];
-                px += (double)blocks(w) * (pr.y1 - pr.y0) * (pr.x1 - pr.x0);
+                px += (double)ceil_div(w.na, ba) * ceil_div(w.nb, bb) * (pr.y1 - pr.y0) * (pr.x1 - pr.x0);
             }
             const int run = 256 * (int)std::min(16.0, std::max(1.0, std::ceil(px / GRAM_ITEMS / 256.0)));
             for (const Narrow& w : list) {
@@ -1357,33 +1354,48 @@ static apx_status build_plan(apx_problem* P, const apx_problem_desc* d) {
                 for (int r0 = 0; r0 < bh; r0 += band) {
                     const int npx = std::min(band, bh - r0) * bw;
                     for (int s0 = 0; s0 < npx; s0 += run)
-                        for (int ta = 0; ta < (ba ? w.na : 1); ta += ba ? ba : 1)
-                            for (int tb = 0; tb < (ba ? w.nb : 1); tb += ba ? bb : 1) {
-                                if (ba && pr.g == pr.h && ta > tb + bb - 1) continue;   // below the diagonal
+                        for (int ta = 0; ta < w.na; ta += ba)
+                            for (int tb = 0; tb < w.nb; tb += bb) {
+                                if (pr.g == pr.h && ta > tb + bb - 1) continue;   // below the diagonal
                                 PairItem it{};
                                 it.pair = w.pi;
-                                it.ta = ba ? ta : w.na;
+                                it.ta = ta;
                                 it.tb = tb;
                                 it.s0 = s0;
                                 it.s1 = std::min(npx, s0 + run);
                                 it.row0 = r0;
                                 it.out_off = outoff;
-                                outoff += entries;
+                                outoff += 16LL * ba * bb;
                                 items.push_back(it);
                             }
                 }
             }
         };
+        // a narrow group with itself: items of GRAM4_STAGES stages of its padded rows, whatever
+        // the launch holds (the order of these sums is part of a fit's result, see k_gram4)
         P->gitems.clear();
         for (int t = 0; t <= GRAM4_MAX_T; ++t) {
             P->gram_begin[t] = (int)P->gitems.size();
-            add_runs(self[t], P->gitems, 0, 0, 16LL * (t * (t + 1) / 2 + t));   // tile pairs, then J^T W [r 1]
+            for (const Narrow& w : self[t]) {
+                const DPair& pr = P->pairs[w.pi];
+                const int stages = (pr.y1 - pr.y0) * ceil_div(pr.x1 - pr.x0, PAIR_KC);
+                for (int s0 = 0; s0 < stages; s0 += GRAM4_STAGES) {
+                    PairItem it{};
+                    it.pair = w.pi;
+                    it.ta = t;
+                    it.s0 = s0;
+                    it.s1 = std::min(stages, s0 + GRAM4_STAGES);
+                    it.out_off = outoff;
+                    outoff += 16LL * (t * (t + 1) / 2 + t);       // tile pairs, then J^T W [r 1]
+                    P->gitems.push_back(it);
+                }
+            }
         }
         P->gram_begin[GRAM4_MAX_T + 1] = (int)P->gitems.size();
         P->xitems.clear();
         for (int k = 0; k < N_CROSS; ++k) {
             P->cross_begin[k] = (int)P->xitems.size();
-            add_runs(cross[k], P->xitems, cross_a(k), cross_b(k), 16LL * cross_a(k) * cross_b(k));
+            add_runs(cross[k], P->xitems, cross_a(k), cross_b(k));
         }
         P->cross_begin[N_CROSS] = (int)P->xitems.size();
         P->n_pairpart = outoff;
@@ -2165,10 +2177,11 @@ static apx_status fwd_chi2(apx_problem* P, const PrepIO& pio, const float* data,
                            float* model, TailIO tail, int skip_mode, const apx_lm_state* lm, int want_grad) {
     const Plan& p = P->plan;
     hipStream_t st = P->ctx->stream;
+    const int fit = tail.kind >= TAIL_INIT;         // an evaluation of an LM fit
     APXCHK(prep(P, pio, skip_mode, lm, want_grad));
     {
         TimeScope ts(P, APX_TIME_RENDER);
-        if (P->objective == APX_OBJECTIVE_FP64) HIPCHK(launch_render64(p, skip_mode, lm, st));
+        if (P->objective == APX_OBJECTIVE_FP64) HIPCHK(launch_render64(p, fit, skip_mode, lm, st));
         else HIPCHK(launch_render_mode(p, skip_mode, lm, st));
     }
     ConvIO io{};
@@ -2180,9 +2193,10 @@ static apx_status fwd_chi2(apx_problem* P, const PrepIO& pio, const float* data,
     io.part = p.fwd_part;
     io.skip_mode = skip_mode;
     io.lm = lm;
+    io.fit = fit;
     APXCHK(run_conv(P, CONV_FWD, io));
     if (data) {
-        TimeScope ts(P, tail.kind >= TAIL_INIT ? APX_TIME_LM : APX_TIME_REDUCE);
+        TimeScope ts(P, fit ? APX_TIME_LM : APX_TIME_REDUCE);
         tail.img_items = wsp<int2>(P, "img_items");
         tail.chi_seg = wsp<int>(P, "chi_seg");
         tail.sub_img = wsp<int>(P, "sub_img");

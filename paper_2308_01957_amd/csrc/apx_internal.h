@@ -169,11 +169,12 @@ struct DPair {
 // one tile pair over stages [s0, s1) of the pair's box (stage s: row y0 + s / nxs, pixels
 // x0 + (s % nxs) KC ... of that row, nxs = ceil((x1 - x0) / KC))
 struct PairItem { int pair, ta, tb, s0, s1, row0; long long out_off; };
-// Narrow pairs run on 4 x 4 FP64 MFMA blocks over runs of pixels: pixels s0 .. s1 - 1, counted
-// along the rows of the pair's box from its row y0 + row0 on.  A group with itself (at most
-// GRAM4_MAX_T tiles of 4 columns): item.ta = the group's 4-column tiles; the partial is every
-// tile pair (a <= b, row-major over the upper triangle) as a 4 x 4 block.
-constexpr int GRAM4_MAX_T = 9;
+// Narrow pairs run on 4 x 4 FP64 MFMA blocks.  A group with itself (at most GRAM4_MAX_T tiles of
+// 4 columns) over up to GRAM4_STAGES stages (as above): item.ta = the group's 4-column tiles; the
+// partial is every tile pair (a <= b, row-major over the upper triangle) as a 4 x 4 block.
+constexpr int GRAM4_MAX_T = 9, GRAM4_STAGES = 4096 / PAIR_KC;
+// Two groups run over pixels s0 .. s1 - 1, counted along the rows of the pair's box from its
+// row y0 + row0 on.
 // Two groups of which one has fewer than WIDE_COLS columns (pair.g the one with more tiles), or a
 // group of 37 .. WIDE_COLS - 1 columns with itself: cross_a(k) x cross_b(k) tiles from tile ta of
 // g and tile tb of h; the partial is every tile pair, row-major, as a 4 x 4 block.
@@ -364,7 +365,8 @@ struct PrepIO {
 hipError_t launch_prep(const Plan& p, const PrepIO& io, hipStream_t st);
 // skip_mode: 0 none, 1 skip sub-problems without a valid trial, 2 skip those that keep J
 hipError_t launch_render_mode(const Plan& p, int skip_mode, const apx_lm_state* lm, hipStream_t st);
-hipError_t launch_render64(const Plan& p, int skip_mode, const apx_lm_state* lm, hipStream_t st);
+// fit: 1 in LM fits (every node by its own log2 and 2^x, see k_render64)
+hipError_t launch_render64(const Plan& p, int fit, int skip_mode, const apx_lm_state* lm, hipStream_t st);
 hipError_t launch_deriv(const Plan& p, const apx_lm_state* lm, hipStream_t st);
 hipError_t launch_grad_tiles(const Plan& p, hipStream_t st);
 
@@ -396,6 +398,7 @@ struct ConvIO {
     double* part;             // per-item partials
     int skip_mode;            // as launch_render_mode
     const apx_lm_state* lm;
+    int fit;                  // FWD, FP64 objective: 1 in LM fits (stamp rows one by one, see k_conv64)
 };
 hipError_t launch_conv_fwd(const Plan& p, const ConvLaunch& L, const ConvIO& io, hipStream_t st);
 hipError_t launch_conv_fwd64(const Plan& p, const ConvLaunch& L, const ConvIO& io, hipStream_t st);

@@ -24,28 +24,32 @@ __device__ __forceinline__ double lane_bcast(double v, int src) {
 }
 
 // One row of an n x n matrix per lane in registers (N >= n columns, padded with identity rows),
-// with lamD added to the diagonal: a right-looking Cholesky whose pivot and column entries come
-// by readlane, so no column step waits for LDS or a barrier.  On return a holds the lane's row
-// of L, rinv the reciprocal of its diagonal entry; false on a non-positive or non-finite pivot.
+// with lam D added to the diagonal (the lane's D): a right-looking Cholesky whose pivot and column entries come
+// by readlane, so no column step waits for LDS or a barrier.  Square root and quotients are
+// the correctly rounded ones: a fit's later steps depend on the last bits of this one (the
+// FP32 derivative images are not continuous in theta), so its arithmetic is part of the
+// result.  On return a holds the lane's row of L, diag its diagonal entry; false on a
+// non-positive or non-finite pivot.
 template <int N>
-__device__ __forceinline__ bool chol_rows(const double* __restrict__ A, int n, double lamD, double (&a)[N], double& rinv) {
+__device__ __forceinline__ bool chol_rows(const double* __restrict__ A, int n, double lam, double D,
+                                          double (&a)[N], double& diag) {
     const int i = threadIdx.x;
 #pragma unroll
     for (int j = 0; j < N; ++j) a[j] = (i < n && j < n) ? A[(long long)i * n + j] : (i == j ? 1.0 : 0.0);
 #pragma unroll
     for (int j = 0; j < N; ++j)
-        if (i == j && j < n) a[j] += lamD;
+        if (i == j && j < n) a[j] = fma(lam, D, a[j]);
     bool ok = true;
-    rinv = 1.0;
+    diag = 1.0;
 #pragma unroll
     for (int k = 0; k < N; ++k) {
         double piv = lane_bcast(a[k], k);
         // a failed pivot is recorded and replaced by 1 so the (discarded) factor stays finite
         if (!(piv > 0.0) || !isfinite(piv)) { ok = false; piv = 1.0; }
-        const double r = rsqrt_f64(piv);
-        const double l = i > k ? a[k] * r : 0.0;
-        a[k] = i > k ? l : (i == k ? piv * r : a[k]);
-        if (i == k) rinv = r;
+        const double d = sqrt(piv);
+        const double l = i > k ? a[k] / d : 0.0;
+        a[k] = i > k ? l : (i == k ? d : a[k]);
+        if (i == k) diag = d;
 #pragma unroll
         for (int j = k + 1; j < N; ++j) a[j] = fma(-l, lane_bcast(l, j), a[j]);
     }

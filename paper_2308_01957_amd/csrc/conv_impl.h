@@ -341,8 +341,10 @@ constexpr int pitch64(int w) {
 }
 
 // The FP64 objective's model convolution.  Where the stamp is the same upside down (any stamp
-// sampled from a round profile; psf_sym, found per call by k_psf_prep), rows U and P - 1 - U
-// of the stamp multiply the sum of two input rows: R + P - 1 additions replace P R FMAs.
+// sampled from a round profile; psf_sym, found per call by k_prep), rows U and P - 1 - U
+// of the stamp multiply the sum of two input rows: R + P - 1 additions replace P R FMAs.  The
+// evaluations of an LM fit (io.fit) take the rows one by one: the fold rounds differently, and a
+// fit follows the last bits of its residuals (see k_render64).
 // Each window goes through registers in pieces of CH64 taps, the next piece's LDS reads in
 // flight while the current one is multiplied.  Above P = 41 the pieces are pinned in that order
 // (the compiler otherwise reads whole windows of both rows first, 256 registers and spills at
@@ -429,11 +431,11 @@ __global__ __launch_bounds__(TH * TW / R) void k_conv64(PlanPtr pp, const ConvJo
     for (int r = 0; r < R; ++r) acc[r] = 0.0;
     constexpr int N = R + P - 1, NC = (P + CH64 - 1) / CH64;
     constexpr bool PINNED = P > (R == CV_R ? 41 : 51);
-    // acc[r] += sum_j K[U, P - 1 - j] s[r + j], s the window that starts at pair o1 of the tile
-    // (with TWO: plus the one at pair o2), read as pairs (ds_read_b128).  pin() keeps the
-    // pieces apart: a piece's FMAs come before it, the reads that follow (whose offsets pass
-    // through it) after.
-    static_assert(N % 2 == 0 && R % 2 == 0 && LW % 2 == 0 && CH64 % 2 == 0, "windows are whole pairs");
+    // acc[r] += sum_V K[U, V] s[r + P - 1 - V], V ascending, s the window that starts at pair o1 of
+    // the tile (with TWO: plus the one at pair o2), read from its end as pairs (ds_read_b128).
+    // pin() keeps the pieces apart: a piece's FMAs come before it, the reads that follow (whose
+    // offsets pass through it) after.
+    static_assert(N % 2 == 0 && R % 2 == 0 && P % 2 == 1 && LW % 2 == 0 && CH64 % 2 == 0, "windows are whole pairs");
     const double2* tile2 = reinterpret_cast<const double2*>(tile);
     auto row = [&](auto two, int o1, int o2, int U) {
         constexpr bool TWO = decltype(two)::value;
@@ -442,7 +444,7 @@ __global__ __launch_bounds__(TH * TW / R) void k_conv64(PlanPtr pp, const ConvJo
 #pragma unroll
         for (int r = 0; r < R; ++r) part[r] = 0.0;
 #pragma unroll
-        for (int k = 0; k < R; k += 2) {
+        for (int k = P - 1; k < N; k += 2) {
             double2 v = tile2[o1 + k / 2];
             if constexpr (TWO) {
                 const double2 w = tile2[o2 + k / 2];
@@ -452,43 +454,44 @@ __global__ __launch_bounds__(TH * TW / R) void k_conv64(PlanPtr pp, const ConvJo
             s[k] = v.x;
             s[k + 1] = v.y;
         }
+        // entry m below those is s[P - 2 - m]; pairs (m + 1, m), m even
 #pragma unroll
         for (int q = 0; q < CH64; q += 2)
-            if (R + q < N) {
-                a[q / 2] = tile2[o1 + (R + q) / 2];
-                if constexpr (TWO) b[q / 2] = tile2[o2 + (R + q) / 2];
+            if (q < P - 1) {
+                a[q / 2] = tile2[o1 + (P - 3 - q) / 2];
+                if constexpr (TWO) b[q / 2] = tile2[o2 + (P - 3 - q) / 2];
             }
 #pragma unroll
         for (int ch = 0; ch < NC; ++ch) {
 #pragma unroll
             for (int q = 0; q < CH64; q += 2) {
-                const int k = R + ch * CH64 + q;
-                if (k < N) {
-                    s[k] = a[q / 2].x;
-                    s[k + 1] = a[q / 2].y;
+                const int m = ch * CH64 + q;
+                if (m < P - 1) {
+                    s[P - 3 - m] = a[q / 2].x;
+                    s[P - 2 - m] = a[q / 2].y;
                     if constexpr (TWO) {
-                        s[k] += b[q / 2].x;
-                        s[k + 1] += b[q / 2].y;
+                        s[P - 3 - m] += b[q / 2].x;
+                        s[P - 2 - m] += b[q / 2].y;
                     }
                 }
             }
 #pragma unroll
             for (int q = 0; q < CH64; q += 2) {
-                const int k = R + (ch + 1) * CH64 + q;
-                if (k < N) {
-                    a[q / 2] = tile2[o1 + k / 2];
-                    if constexpr (TWO) b[q / 2] = tile2[o2 + k / 2];
+                const int m = (ch + 1) * CH64 + q;
+                if (m < P - 1) {
+                    a[q / 2] = tile2[o1 + (P - 3 - m) / 2];
+                    if constexpr (TWO) b[q / 2] = tile2[o2 + (P - 3 - m) / 2];
                 }
             }
 #pragma unroll
             for (int q = 0; q < CH64; ++q) {
-                const int j = ch * CH64 + q;
-                if (j < P) {
+                const int V = ch * CH64 + q;
+                if (V < P) {
                     double kv;
-                    if constexpr (KLDS) kv = kt[U * KP + P - 1 - j];
-                    else kv = K[U * P + P - 1 - j];
+                    if constexpr (KLDS) kv = kt[U * KP + V];
+                    else kv = K[U * P + V];
 #pragma unroll
-                    for (int r = 0; r < R; ++r) part[r] = fma(kv, s[r + j], part[r]);
+                    for (int r = 0; r < R; ++r) part[r] = fma(kv, s[r + P - 1 - V], part[r]);
                 }
             }
             if constexpr (PINNED) pin(part, o1, o2);
@@ -497,7 +500,7 @@ __global__ __launch_bounds__(TH * TW / R) void k_conv64(PlanPtr pp, const ConvJo
         for (int r = 0; r < R; ++r) acc[r] += part[r];
     };
     const int o0 = (ty * LW + tx * R) / 2;
-    const int npair = p.psf_sym[jb.image] ? c : 0;   // block-uniform
+    const int npair = !io.fit && p.psf_sym[jb.image] ? c : 0;   // block-uniform
     for (int U = 0; U < npair; ++U) row(std::true_type{}, o0 + (P - 1 - U) * (LW / 2), o0 + U * (LW / 2), U);
     for (int U = npair; U < P - npair; ++U) row(std::false_type{}, o0 + (P - 1 - U) * (LW / 2), o0, U);
 

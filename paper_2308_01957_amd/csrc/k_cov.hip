@@ -24,8 +24,8 @@ __device__ __forceinline__ void cov_small_n(const Plan& p, const DSub& sb, doubl
     constexpr int LD = N + 1;
     double* inv = L + N * LD;                        // reciprocals of the diagonal
     {
-        double a[N], rinv;
-        if (!chol_rows<N>(p.A + sb.a_off, n, 0.0, a, rinv)) {
+        double a[N], diag;
+        if (!chol_rows<N>(p.A + sb.a_off, n, 0.0, 0.0, a, diag)) {
             if (c < n)
                 for (int i = 0; i < n; ++i) out[(long long)i * n + c] = __builtin_nan("");
             return;
@@ -33,7 +33,7 @@ __device__ __forceinline__ void cov_small_n(const Plan& p, const DSub& sb, doubl
         if (c < N) {
 #pragma unroll
             for (int j = 0; j < N; ++j) L[c * LD + j] = a[j];
-            inv[c] = rinv;
+            inv[c] = 1.0 / diag;
         }
     }
     __syncthreads();

@@ -247,26 +247,31 @@ __device__ __forceinline__ void gram_emit(const double (&acc)[NQ], double* __res
 // A group (NT tiles of 4 columns, at most 36 columns) with itself: every tile pair a <= b, and
 // each tile against [r 1 0 0] (the pixel's residual, a one), which gives the columns' J^T W r
 // and sum w J (the sky row of J^T W J) over the item in NT more blocks after the tile pairs.
+// Its items are up to 128 stages of PAIR_KC pixels of a row (stage s: row s / nxs of the box,
+// pixels (s % nxs) PAIR_KC ..., nxs stages a row), wave w taking stages s0 + w, + 4, ... in
+// order: the order of these sums is part of a fit's result (its later steps follow the last
+// bits of this one through the FP32 derivative images), so it does not follow the number of
+// items of a launch.  NS chunks of 16 pixels of a wave are in flight.
 template <int NT, int NS>
 __global__ __launch_bounds__(256) void k_gram4(PlanPtr pp, const DPair* __restrict__ pairs,
                                                const PairItem* __restrict__ items, int n_items,
                                                const float* __restrict__ weight, const apx_lm_state* lm) {
     PlanRef p = *pp;
-    constexpr int NP = NT * (NT + 1) / 2;
+    constexpr int NP = NT * (NT + 1) / 2, NH = PAIR_KC / 16;     // chunks of a stage
+    static_assert(NS % NH == 0, "whole stages in flight");
     const PairItem it = items[xcd_chunk_item((int)blockIdx.x, n_items)];
     const DPair pr = pairs[it.pair];
     if (lm && lm[pr.sub].need_jac == 0) return;
     const DGroup G = p.groups[pr.g];
-    const int imW = p.images[pr.image].Wc;
+    const int imW = p.images[pr.image].Wc, bw = pr.x1 - pr.x0;
     const long long gs = (long long)G.oh * G.ow;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int col = lane & 3, pxl = lane >> 2;       // column within a tile, pixel within a chunk
-    const int yb = pr.y0 + it.row0;                  // first row of the item's band
-    const float* __restrict__ Jg = p.J + G.j_off + (long long)(yb - G.oy0) * G.ow + (pr.x0 - G.ox0);
-    const long long pix0 = p.images[pr.image].pix_off + (long long)yb * imW + pr.x0;
+    const float* __restrict__ Jg = p.J + G.j_off + (long long)(pr.y0 - G.oy0) * G.ow + (pr.x0 - G.ox0);
+    const long long pix0 = p.images[pr.image].pix_off + (long long)pr.y0 * imW + pr.x0;
     const float* __restrict__ wb = weight + pix0;
     const float* __restrict__ rb = p.rbuf + pix0;
-    const GramDiv div(pr.x1 - pr.x0);
+    const GramDiv div((bw + PAIR_KC - 1) / PAIR_KC);
     const float* cb[NT];                             // this lane's column of each tile
     bool cval[NT];
 #pragma unroll
@@ -278,37 +283,39 @@ __global__ __launch_bounds__(256) void k_gram4(PlanPtr pp, const DPair* __restri
     double acc[NP + NT];
 #pragma unroll
     for (int q = 0; q < NP + NT; ++q) acc[q] = 0.0;
-    auto fetch = [&](int e0, float (&bv)[NS][NT], float (&wf)[NS], float (&rf)[NS]) {
+    auto fetch = [&](int st0, float (&bv)[NS][NT], float (&wf)[NS], float (&rf)[NS], bool (&in)[NS]) {
 #pragma unroll
         for (int h = 0; h < NS; ++h) {
-            const int e = e0 + 16 * h + pxl;
-            const bool in = e < it.s1;
-            int row, x;
-            div(in ? e : it.s1 - 1, row, x);
-            const long long pix = (long long)row * imW + x, grow = (long long)row * G.ow + x;
-            const float wl = wb[pix];
+            const int st = st0 + 4 * (h / NH);
+            int row, sx;
+            div(st < it.s1 ? st : it.s1 - 1, row, sx);
+            const int x = sx * PAIR_KC + 16 * (h % NH) + pxl;
+            in[h] = st < it.s1 && x < bw;
+            const int xc = x < bw ? x : bw - 1;
+            const long long pix = (long long)row * imW + xc, grow = (long long)row * G.ow + xc;
+            wf[h] = wb[pix];
             rf[h] = rb[pix];
 #pragma unroll
             for (int t = 0; t < NT; ++t) bv[h][t] = cb[t][grow];
-            wf[h] = in ? wl : 0.f;
         }
     };
     float bc[NS][NT], wc[NS], rc[NS];
-    int e0 = it.s0 + 16 * NS * wv;
-    if (e0 < it.s1) fetch(e0, bc, wc, rc);
-    while (e0 < it.s1) {
-        const int e1 = e0 + 64 * NS;
+    bool ic[NS];
+    int st = it.s0 + wv;
+    if (st < it.s1) fetch(st, bc, wc, rc, ic);
+    while (st < it.s1) {
+        const int st1 = st + 4 * (NS / NH);
         float bn[NS][NT], wn[NS], rn[NS];
-        const bool more = e1 < it.s1;
-        if (more) fetch(e1, bn, wn, rn);
+        bool in[NS];
+        const bool more = st1 < it.s1;
+        if (more) fetch(st1, bn, wn, rn, in);
 #pragma unroll
         for (int h = 0; h < NS; ++h) {
-            const bool in = e0 + 16 * h + pxl < it.s1;
-            const double w = (double)wc[h];
+            const double w = ic[h] ? (double)wc[h] : 0.0;
             const double vx = col == 0 ? (double)rc[h] : (col == 1 ? 1.0 : 0.0);     // [r 1 0 0]
             double b[NT];
 #pragma unroll
-            for (int t = 0; t < NT; ++t) b[t] = (in && cval[t]) ? (double)bc[h][t] : 0.0;
+            for (int t = 0; t < NT; ++t) b[t] = (ic[h] && cval[t]) ? (double)bc[h][t] : 0.0;
             int q = 0;
 #pragma unroll
             for (int ta = 0; ta < NT; ++ta) {
@@ -326,9 +333,10 @@ __global__ __launch_bounds__(256) void k_gram4(PlanPtr pp, const DPair* __restri
                 for (int t = 0; t < NT; ++t) bc[h][t] = bn[h][t];
                 wc[h] = wn[h];
                 rc[h] = rn[h];
+                ic[h] = in[h];
             }
         }
-        e0 = e1;
+        st = st1;
     }
     gram_emit<NP + NT>(acc, p.pair_part + it.out_off);
 }
@@ -434,7 +442,7 @@ hipError_t launch_gram4(const Plan& p, const PairLaunch& L, const float* weight,
     switch (L.tm) {
 #define APX_G4(T)                                                                                       \
     case T:                                                                                             \
-        hipLaunchKernelGGL((k_gram4<T, (T) <= 5 ? 4 : 2>), grid, block, 0, st, p.dev, L.pairs, L.items, L.n_items, weight, lm); \
+        hipLaunchKernelGGL((k_gram4<T, (T) <= 2 ? 8 : (T) <= 5 ? 4 : 2>), grid, block, 0, st, p.dev, L.pairs, L.items, L.n_items, weight, lm); \
         break;
         APX_G4(1) APX_G4(2) APX_G4(3) APX_G4(4) APX_G4(5) APX_G4(6) APX_G4(7) APX_G4(8) APX_G4(9)
 #undef APX_G4

@@ -34,10 +34,10 @@ __device__ __forceinline__ void chol_small_n(const Plan& p, int s, const DSub& s
     double lam = lm[s].lambda;
     const double dmax = lm_wave_max(i < n ? di : -1e308);
     const double Di = fmax(di, APX_LM_DAMP_FLOOR * dmax);
-    double a[N], rinv = 1.0;
+    double a[N], diag = 1.0;
     int done = 0, retries = 0;
     for (int att = 0; att < APX_LM_ATTEMPTS; ++att) {
-        if (chol_rows<N>(A, n, lam * Di, a, rinv)) { done = 1; break; }
+        if (chol_rows<N>(A, n, lam, Di, a, diag)) { done = 1; break; }
         lam = fmin(lam * APX_LM_UP, APX_LM_LAMBDA_MAX);
         ++retries;
     }
@@ -46,7 +46,7 @@ __device__ __forceinline__ void chol_small_n(const Plan& p, int s, const DSub& s
         double y = gi;
 #pragma unroll
         for (int k = 0; k < N; ++k) {                    // L y = g
-            const double yk = lane_bcast(y, k) * lane_bcast(rinv, k);
+            const double yk = lane_bcast(y, k) / lane_bcast(diag, k);
             y = i == k ? yk : (i > k ? fma(-a[k], yk, y) : y);
         }
         if (i < N) {
@@ -57,7 +57,7 @@ __device__ __forceinline__ void chol_small_n(const Plan& p, int s, const DSub& s
         const double* col = sm + (i < N ? i : 0);        // column i of L
 #pragma unroll
         for (int k = N - 1; k >= 0; --k) {               // L^T h = y
-            const double hk = lane_bcast(y, k) * lane_bcast(rinv, k);
+            const double hk = lane_bcast(y, k) / lane_bcast(diag, k);
             y = i == k ? hk : (i < k ? fma(-col[k * (N + 1)], hk, y) : y);
         }
         if (i < n) h = y;

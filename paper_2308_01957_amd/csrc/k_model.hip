@@ -173,10 +173,10 @@ __device__ void prep_comp(PlanRef p, const PrepIO& io, int i) {
             c.A_d = lie * 3.3219280948873622 + b * log2e;
             c.B_d = b * log2e;
             c.g_d = 0.5 / n;
-            c.ax = im.aff[1] * c.cs_d + im.aff[4] * c.sn_d;
-            c.bx = im.aff[2] * c.cs_d + im.aff[5] * c.sn_d;
-            c.ay = (-im.aff[1] * c.sn_d + im.aff[4] * c.cs_d) * c.iq_d;
-            c.by = (-im.aff[2] * c.sn_d + im.aff[5] * c.cs_d) * c.iq_d;
+            c.ax = fma(im.aff[1], c.cs_d, im.aff[4] * c.sn_d);
+            c.bx = fma(im.aff[2], c.cs_d, im.aff[5] * c.sn_d);
+            c.ay = fma(im.aff[4], c.cs_d, -(im.aff[1] * c.sn_d)) * c.iq_d;
+            c.by = fma(im.aff[5], c.cs_d, -(im.aff[2] * c.sn_d)) * c.iq_d;
             c.qxx = c.ax * c.ax + c.ay * c.ay;
             c.qxy = 2.0 * (c.ax * c.bx + c.ay * c.by);
             c.qyy = c.bx * c.bx + c.by * c.by;
@@ -398,8 +398,7 @@ struct NodeSet {
 // and the square root, which only pixels inside the margin pay for.
 __device__ __forceinline__ bool within_kre(const CompConst& c, double ucx, double ucy) {
     const double dx = ucx - c.x0, dy = ucy - c.y0;
-    const double xp = dx * c.cs_d + dy * c.sn_d;
-    const double yp = -dx * c.sn_d + dy * c.cs_d;
+    const double xp = along64(c, dx, dy), yp = across64(c, dx, dy);
     const double ya = yp * c.iq_d;
     const double R2 = xp * xp + ya * ya, k2 = c.kre * c.kre;
     if (R2 < k2 * (1.0 - 1e-12)) return true;
@@ -535,7 +534,7 @@ __device__ __forceinline__ double pixel64_series(PlanRef p, const CompConst& c, 
     return sum;
 }
 
-template <int S>
+template <int S, bool FIT>
 __device__ __forceinline__ double pixel64_nodes(PlanRef p, const CompConst& c, double xp0, double yq0,
                                                 const double* __restrict__ tab) {
     const Poly64Regs rg = poly64_regs(c);
@@ -543,7 +542,7 @@ __device__ __forceinline__ double pixel64_nodes(PlanRef p, const CompConst& c, d
     const double gx = 2.0 * (xp0 * c.ax + yq0 * c.ay), gy = 2.0 * (xp0 * c.bx + yq0 * c.by);
     const double dv = fma(fabs(gx) + fabs(gy), p.node_max, c.qmax);     // bounds v0 |d|
     // (v0 far enough above the floor of R^2 that no node reaches it; false for a NaN)
-    if (__all(dv <= bin_rho(BIN_DEG) * v0 && v0 >= 4e-12)) {
+    if (!FIT && __all(dv <= bin_rho(BIN_DEG) * v0 && v0 >= 4e-12)) {
         const double B0 = c.B_d * exp2_t<false>(fma(c.g_d, log2_t(v0, tab, rg), -rg.h), tab, rg);
         const double X0 = rg.A - B0;
         // exponents that need no clamp: |X0 - B0 ((1 + d)^g - 1)| < 1000
@@ -579,18 +578,18 @@ __device__ __forceinline__ double pixel64_nodes(PlanRef p, const CompConst& c, d
     return sum;
 }
 
+template <bool FIT>
 __device__ __forceinline__ double sersic_pixel64(PlanRef p, const CompConst& c, double ucx, double ucy,
                                                  const double* __restrict__ tab) {
     const double dxc = ucx - c.x0, dyc = ucy - c.y0;
     if (p.mode == APX_MODE_WITHIN_K_RE && !within_kre(c, ucx, ucy)) return sersic_I64_t(c, dxc, dyc, tab);
-    const double xp0 = dxc * c.cs_d + dyc * c.sn_d;
-    const double yq0 = (-dxc * c.sn_d + dyc * c.cs_d) * c.iq_d;
+    const double xp0 = along64(c, dxc, dyc), yq0 = across64(c, dxc, dyc) * c.iq_d;
     // the usual rules unrolled (a loop waits for its node's scalar loads at every node)
     switch (p.s) {
-        case 2: return pixel64_nodes<2>(p, c, xp0, yq0, tab);
-        case 3: return pixel64_nodes<3>(p, c, xp0, yq0, tab);
-        case 4: return pixel64_nodes<4>(p, c, xp0, yq0, tab);
-        default: return pixel64_nodes<0>(p, c, xp0, yq0, tab);
+        case 2: return pixel64_nodes<2, FIT>(p, c, xp0, yq0, tab);
+        case 3: return pixel64_nodes<3, FIT>(p, c, xp0, yq0, tab);
+        case 4: return pixel64_nodes<4, FIT>(p, c, xp0, yq0, tab);
+        default: return pixel64_nodes<0, FIT>(p, c, xp0, yq0, tab);
     }
 }
 
@@ -687,14 +686,14 @@ __device__ void shifted_derivs(PlanRef p, int ci, const CompConst& c, const DCom
 
 // Pixel value T * S' (area included) of a re-centred Sersic at pixel (ly, lx) of the render
 // tile with origin (y0, x0); 0 where !want.  Every thread of the block calls it.
-template <typename T>
+template <typename T, bool FIT>
 __device__ T shifted_pixel(PlanRef p, int ci, const CompConst& c, const DComp& cp, const DImage& im, int y0,
                            int x0, int ly, int lx, bool want, T (*sh)[SH_H * SH_W], T* tw,
                            const double* __restrict__ tab = nullptr) {
     stage_halo<1, T>(p, ci, cp, y0, x0, sh, tw, [&](int ry, int rx, T* v) {
         const double rcx = im.aff[0] + im.aff[1] * rx + im.aff[2] * ry;
         const double rcy = im.aff[3] + im.aff[4] * rx + im.aff[5] * ry;
-        if constexpr (sizeof(T) == 8) v[0] = sersic_pixel64(p, c, rcx, rcy, tab) * im.area;
+        if constexpr (sizeof(T) == 8) v[0] = sersic_pixel64<FIT>(p, c, rcx, rcy, tab) * im.area;
         else v[0] = (float)((double)sersic_pixel(p, c, im, rcx, rcy) * im.area);
     });
     __syncthreads();
@@ -732,7 +731,7 @@ __global__ __launch_bounds__(256) void k_render(PlanPtr pp, int skip_mode, const
             continue;
         }
         if (SHIFT && cp.type == APX_SERSIC) {      // block-uniform
-            if constexpr (SHIFT) sum += (double)shifted_pixel<float>(p, ci, c, cp, im, t.y0, t.x0, ly, lx, inbox, sh, tw);
+            if constexpr (SHIFT) sum += (double)shifted_pixel<float, false>(p, ci, c, cp, im, t.y0, t.x0, ly, lx, inbox, sh, tw);
             continue;
         }
         if (!inbox) continue;
@@ -754,9 +753,16 @@ hipError_t launch_render_mode(const Plan& p, int skip_mode, const apx_lm_state* 
 }
 
 // ------------------------------------------------------------- FP64 render
-// S64 (extended grid, FP64): the objective path's render.
-template <bool SHIFT>
-__global__ __launch_bounds__(256, SHIFT ? 4 : 6) void k_render64(PlanPtr pp, int skip_mode, const apx_lm_state* lm) {
+// S64 (extended grid, FP64): the objective path's render.  FIT (the evaluations of an LM fit):
+// every node by its own log2 and 2^x, without the series of pixel64_series.  Both carry the
+// same rounding error, but they do not round alike, and a fit follows the last bits of its
+// residuals: a theta that moves by 1e-14 turns the rounding of a few nodes of the FP32
+// derivative images, which changes the rounding of their whole FFT tiles (1e-8 of J^T W r), and
+// two iterations later the largest parameter of 768 cutouts by 1e-5.  So a fit keeps the one
+// arithmetic it has always had, and its result.  (A full render of 768 cutouts: 821 us, with the
+// series 626.)
+template <bool SHIFT, bool FIT>
+__global__ __launch_bounds__(256, SHIFT || FIT ? 4 : 6) void k_render64(PlanPtr pp, int skip_mode, const apx_lm_state* lm) {
     PlanRef p = *pp;
     __shared__ double sh[1][SHIFT ? SH_H * SH_W : 1];
     __shared__ double tw[SHIFT ? STAP_STRIDE : 1];
@@ -783,24 +789,23 @@ __global__ __launch_bounds__(256, SHIFT ? 4 : 6) void k_render64(PlanPtr pp, int
             continue;
         }
         if (SHIFT && cp.type == APX_SERSIC) {      // block-uniform
-            if constexpr (SHIFT) sum += shifted_pixel<double>(p, ci, c, cp, im, t.y0, t.x0, ly, lx, inbox, sh, tw, ptab);
+            if constexpr (SHIFT) sum += shifted_pixel<double, FIT>(p, ci, c, cp, im, t.y0, t.x0, ly, lx, inbox, sh, tw, ptab);
             continue;
         }
         if (!inbox) continue;
         if (cp.type == APX_SERSIC)
             sum += (p.mode == APX_MODE_ADAPTIVE ? p.aval[adapt_index(cp, y, x)]
-                                                : sersic_pixel64(p, c, ucx, ucy, ptab)) * im.area;
+                                                : sersic_pixel64<FIT>(p, c, ucx, ucy, ptab)) * im.area;
         else sum += (double)c.F64 * point_weight(c, y, x);
     }
     if (inside) p.S64[im.ext_off + (long long)(y + im.c) * im.EW + (x + im.c)] = sum;
 }
 
-hipError_t launch_render64(const Plan& p, int skip_mode, const apx_lm_state* lm, hipStream_t st) {
+hipError_t launch_render64(const Plan& p, int fit, int skip_mode, const apx_lm_state* lm, hipStream_t st) {
     if (p.n_rtiles == 0) return hipSuccess;
-    if (p.shift != APX_SHIFT_NONE)
-        hipLaunchKernelGGL(k_render64<true>, dim3(p.n_rtiles), dim3(256), 0, st, p.dev, skip_mode, lm);
-    else
-        hipLaunchKernelGGL(k_render64<false>, dim3(p.n_rtiles), dim3(256), 0, st, p.dev, skip_mode, lm);
+    auto* k = p.shift != APX_SHIFT_NONE ? (fit ? k_render64<true, true> : k_render64<true, false>)
+                                        : (fit ? k_render64<false, true> : k_render64<false, false>);
+    hipLaunchKernelGGL(k, dim3(p.n_rtiles), dim3(256), 0, st, p.dev, skip_mode, lm);
     return hipGetLastError();
 }
 

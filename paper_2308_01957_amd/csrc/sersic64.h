@@ -163,19 +163,29 @@ __device__ __forceinline__ double exp2_64th(double y, const double* __restrict__
     return ldexp(tab[n & 63] * p, n >> 6);
 }
 
-// I at a point given in the component's frame (xp along the major axis, yq = yp / q).
-__device__ __forceinline__ double sersic_I64_r(const CompConst& c, double xp, double yq,
-                                               const double* __restrict__ tab, const Poly64Regs& rg) {
-    const double R2 = fmax(xp * xp + yq * yq, 1e-12);
-    const double t = exp2_t<false>(fma(c.g_d, log2_t(R2, tab, rg), -rg.h), tab, rg);
+// I at squared elliptical radius R2, floored at 1e-12.
+__device__ __forceinline__ double sersic_I64_R2(const CompConst& c, double R2, const double* __restrict__ tab,
+                                                const Poly64Regs& rg) {
+    const double t = exp2_t<false>(fma(c.g_d, log2_t(fmax(R2, 1e-12), tab, rg), -rg.h), tab, rg);
     return exp2_t<true>(fma(-c.B_d, t, rg.A), tab, rg);
 }
 
+// I at a point given in the component's frame (xp along the major axis, yq = yp / q).
+__device__ __forceinline__ double sersic_I64_r(const CompConst& c, double xp, double yq,
+                                               const double* __restrict__ tab, const Poly64Regs& rg) {
+    return sersic_I64_R2(c, fma(xp, xp, yq * yq), tab, rg);
+}
+
+// A centre offset along and across the major axis.  The sums of products of the FP64 render are
+// written as the FMAs they are: left to the compiler, which of two products is fused depends on
+// what else a kernel uses them for, and a fit follows the last bits (see k_render64).
+__device__ __forceinline__ double along64(const CompConst& c, double dx, double dy) { return fma(c.cs_d, dx, dy * c.sn_d); }
+__device__ __forceinline__ double across64(const CompConst& c, double dx, double dy) { return fma(-dx, c.sn_d, dy * c.cs_d); }
+
 __device__ __forceinline__ double sersic_I64_t(const CompConst& c, double dx, double dy,
                                                const double* __restrict__ tab) {
-    const double xp = dx * c.cs_d + dy * c.sn_d;
-    const double yq = (-dx * c.sn_d + dy * c.cs_d) * c.iq_d;
-    return sersic_I64_r(c, xp, yq, tab, poly64_regs(c));
+    const double xp = along64(c, dx, dy), yq = across64(c, dx, dy) * c.iq_d;
+    return sersic_I64_R2(c, fma(yq, yq, xp * xp), tab, poly64_regs(c));
 }
 
 __device__ __forceinline__ double sersic_I64(const CompConst& c, double dx, double dy) {
