@@ -267,17 +267,22 @@ apx_status apx_ctx_set_stream(apx_ctx* ctx, void* hip_stream);
  * or the Jacobian columns of one window) is cut into workgroup tiles of one of four shapes:
  * 0 = 32 x 64, 1 = 16 x 64, 2 = 32 x 32, 3 = 16 x 32 output pixels; the direct jobs of one
  * kind at one PSF size take the one shape of least estimated cost (tiles needed x cost of
- * one tile, summed over those jobs), so that each PSF size is one launch.  The policy
- * holds for problems created after the call:
+ * one tile, summed over those jobs), so that each PSF size is one launch.  A launch of fewer
+ * 32 x 64 tiles than half the device's compute units takes shape 3 with two outputs per lane
+ * instead of eight (not under a fixed policy, nor with psf_up > 1).  The policy holds for
+ * problems created after the call:
  *   APX_TILES_AUTOTUNE (default): on a device context, the first problem that needs a
  *     convolution kernel at a PSF size times all four shapes of it on a synthetic
  *     256 x 256 job of 32 channels (a few ms, synchronous on the context stream, in scratch
  *     memory the context allocates once and frees in apx_ctx_destroy) and the context keeps
- *     the table; host-only contexts use the model;
+ *     the table; host-only contexts use the model.  The launches that add FP64 sums over their
+ *     tiles (the model, and Jacobian columns of groups of more than 36 columns or of a live
+ *     PSF) take costs fixed in the library instead of the timings, so that two problems of
+ *     one description give the same bits; costs set by apx_ctx_set_tile_cost hold for all;
  *   APX_TILES_MODEL: an operation-count model, no timing;
  *   APX_TILES_FIXED + s (s = 0..3): shape s for every job.
- * The shape changes nothing but the order in which the FP64 per-tile partial sums of chi^2,
- * J^T W r and the gradient are added.  APX_E_INVALID for an unknown policy. */
+ * The shape changes nothing but the order in which the FP64 per-tile partial sums of chi^2 and
+ * J^T W r are added.  APX_E_INVALID for an unknown policy. */
 #define APX_TILES_AUTOTUNE  0
 #define APX_TILES_MODEL     1
 #define APX_TILES_FIXED     2

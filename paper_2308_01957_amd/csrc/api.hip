@@ -23,9 +23,11 @@ struct apx_ctx {
     std::string err;
     int tiles = APX_TILES_AUTOTUNE;                     // tile-shape policy for new problems
     std::map<int, std::array<double, 4>> tile_us;       // (kernel, P) -> measured us per tile
+    std::set<int> tile_given;                           // entries of it that the caller set
+    int n_cu = 0;                                       // compute units (0: not asked yet)
     void* tune_mem = nullptr;                           // autotuner scratch (allocated once)
     size_t tune_bytes = 0;
-    int pair_slots = 0;                                 // resident k_pair<64> workgroups
+    int pair_slots = 0;                                 // resident k_pair workgroups
 };
 
 // ------------------------------------------------------------ library scratch
@@ -376,6 +378,39 @@ static std::array<double, 4> tile_costs(apx_ctx* C, int key, int P) {
     return cost;
 }
 
+// Relative cost of one output in tiles of each shape, measured once on MI355X (as the autotuner
+// measures it, us per tile over th tw): for the launches whose results hold FP64 sums over a
+// tile, under the autotuner's policy.  Near-equal shapes change places in the timings from one
+// problem to the next, and another tile adds the sums of chi^2 and J^T W r in another order; from
+// this table two problems of one description have the same tiles, and their results the same
+// bits.  (ns per output, shapes 0 .. 3.  FP64 model: P = 11 .010 each; 15 .016 .016 .016 .019; 17
+// .018 .022 .018 .024; 25 .030 .038 .035 .039; 41 .066 .092 .089 .111; folded 25 .019 .027 .025
+// .026.  FP32: 11 .010 each; 27 .022 .023 .022 .024; 31 .026 .028 .028 .043; 41 .041 .062 .053 .057;
+// 51 .060 .086 .083 .095; 63 .109 .093 .136 .186.)
+static std::array<double, 4> tile_fixed(int key, int P) {
+    struct Row { int max_P; double f[4]; };
+    static constexpr Row fp64[] = {{15, {1, 1.05, 1, 1.15}}, {17, {1, 1.2, 1, 1.3}}, {63, {1, 1.25, 1.17, 1.3}}};
+    static constexpr Row fp32[] = {{27, {1, 1, 1, 1.04}}, {31, {1, 1.05, 1.05, 1.5}}, {51, {1, 1.45, 1.35, 1.5}},
+                                   {63, {1.15, 1, 1.4, 1.9}}};
+    const Row* r = key == TUNE_FWD64 ? fp64 : fp32;
+    while (r->max_P < P) ++r;
+    std::array<double, 4> cost;
+    for (int s = 0; s < N_TILE_SHAPES; ++s) cost[s] = r->f[s] * tile_th(s) * tile_tw(s);
+    return cost;
+}
+
+// Compute units of the context's device; gfx950's 256 for a plan-only context.
+static int compute_units(apx_ctx* C) {
+    if (C->n_cu > 0) return C->n_cu;
+    C->n_cu = 256;
+    if (C->device >= 0) {
+        int v = 0;
+        if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, C->device) == hipSuccess && v > 0) C->n_cu = v;
+        else (void)hipGetLastError();
+    }
+    return C->n_cu;
+}
+
 // Automatic mode: a job of nch channels with an out_h x out_w output takes FFT tiles when
 // its pairs of 128 x 128 transforms (ceil(nch * blocks / 2), blocks of (129 - P)^2 outputs)
 // cost less than its direct tiles of the cheapest shape, both by the operation-count model
@@ -400,17 +435,12 @@ static bool auto_fft(int P, int out_h, int out_w, int nch) {
 // registers per lane).
 static int pair_slots(apx_ctx* C) {
     if (C->pair_slots > 0) return C->pair_slots;
-    int per_cu = 3, n_cu = 256;
+    int per_cu = 3;
     if (C->device >= 0) {
-        int v = 0;
-        if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, C->device) == hipSuccess && v > 0)
-            n_cu = v;
-        else
-            (void)hipGetLastError();
         const int b = pair_blocks_per_cu();
         if (b > 0) per_cu = b;
     }
-    C->pair_slots = per_cu * n_cu;
+    C->pair_slots = per_cu * compute_units(C);
     return C->pair_slots;
 }
 
@@ -418,14 +448,16 @@ static int pair_slots(apx_ctx* C) {
 // summed over a group of jobs at one PSF size (outputs h[j] x w[j] with nch[j] channels
 // each).  A shape must beat the best lower-indexed (larger) one by more than 3 % to be
 // taken: measured costs of near-equal shapes wobble from run to run, and the larger tile
-// re-reads less halo.  Every direct job of one kind and PSF size takes this one shape, so a
+// re-reads less halo.  summed: the launch adds FP64 sums over its tiles; under the autotuner's
+// policy its costs are then the caller's or fixed (tile_fixed), not timed.  Every direct job of one kind and PSF size takes this one shape, so a
 // phase launches once per PSF size: per-job shapes split a batch of small images into four
 // launches per size, each ending in a partly filled round (on 4096 cutouts the FP64 model
 // convolutions took 2.34 ms per iteration in 36 launches, 1.82 ms in 9).
 static int choose_group_shape(apx_ctx* C, int key, int P, const std::vector<int>& h,
-                              const std::vector<int>& w, const std::vector<int>& nch) {
+                              const std::vector<int>& w, const std::vector<int>& nch, bool summed) {
     if (C->tiles >= APX_TILES_FIXED && C->tiles < APX_TILES_FIXED + N_TILE_SHAPES) return C->tiles - APX_TILES_FIXED;
-    const std::array<double, 4> cost = tile_costs(C, key, P);
+    std::array<double, 4> cost = tile_costs(C, key, P);
+    if (summed && C->tiles == APX_TILES_AUTOTUNE && !C->tile_given.count(key * 64 + P)) cost = tile_fixed(key, P);
     int best = 0;
     double bc = 1e300;
     for (int s = 0; s < N_TILE_SHAPES; ++s) {
@@ -441,8 +473,6 @@ static int choose_group_shape(apx_ctx* C, int key, int P, const std::vector<int>
 // Derivative and gradient launches of fewer group tiles than this split the groups' components.
 static constexpr int G_SPLIT_WG = 1024;
 
-// Convolution launches of fewer tiles than this (half the compute units) go fine.
-static constexpr int FINE_TILES = 128;
 
 // Regularised lower incomplete gamma P(a, x) by its power series (x < a + 1 here).
 static double gammainc_lower_series_host(double a, double x) {
@@ -1099,23 +1129,27 @@ static apx_status build_plan(apx_problem* P, const apx_problem_desc* d) {
                 if (jobs[j].shape < N_TILE_SHAPES) byP[jobP[j]].push_back((int)j);
             for (const auto& kv : byP) {
                 std::vector<int> h, w, nc;
+                bool summed = kind == CONV_FWD;
                 for (int j : kv.second) {
                     h.push_back(jobs[j].out_h);
                     w.push_back(jobs[j].out_w);
                     nc.push_back(nch[j]);
+                    summed = summed || (kind == CONV_JCOL && nch[j] > 0 && !jobs[j].gram_part);
                 }
-                int s = choose_group_shape(C, key, kv.first, h, w, nc);
-                // Too few tiles to give half the compute units one: 16 x 32 tiles with
-                // CV_R_FINE outputs per lane (a 128 x 128 image at P = 25: 8 workgroups and
-                // 18 us, against 32 and 12).  Not under a fixed policy, nor with sub-pixel
-                // grids, whose epilogue needs all CV_R outputs in a lane.
+                int s = choose_group_shape(C, key, kv.first, h, w, nc, summed);
+                // Too few 32 x 64 tiles to give half the compute units one: 16 x 32 tiles with
+                // CV_R_FINE outputs per lane, by the sizes alone (one image at P = 25, FP64 model
+                // and adjoint with events: 6 tiles 26 -> 14 and 34 -> 15 us, 91 tiles 28 -> 20 and 29
+                // -> 18, 200 tiles 28 -> 33 and 30 -> 26; at P = 41 200 tiles 46 -> 72).  Not under a
+                // fixed policy, nor with sub-pixel grids, whose epilogue needs all CV_R outputs
+                // in a lane.
                 long long tiles = 0;
                 bool plain = C->tiles < APX_TILES_FIXED;
                 for (size_t q = 0; q < h.size(); ++q) {
-                    tiles += (long long)nc[q] * ceil_div(h[q], tile_th(s)) * ceil_div(w[q], tile_tw(s));
+                    tiles += (long long)nc[q] * ceil_div(h[q], tile_th(0)) * ceil_div(w[q], tile_tw(0));
                     plain = plain && P->images[jobs[kv.second[q]].image].up == 1;
                 }
-                if (plain && tiles < FINE_TILES) {
+                if (plain && tiles < compute_units(C) / 2) {
                     s = FINE_SHAPE;
                     fineP.insert(kv.first);
                 }
@@ -1778,6 +1812,7 @@ apx_status apx_ctx_set_tile_cost(apx_ctx* ctx, int32_t kernel, int32_t P, const 
         cost[s] = us[s];
     }
     ctx->tile_us[kernel * 64 + P] = cost;
+    ctx->tile_given.insert(kernel * 64 + P);
     return APX_OK;
 }
 
