@@ -3,7 +3,8 @@
 // parameter uncertainties and their full covariance).  FP64 throughout.
 //
 // Sub-problems of at most SMALL_N parameters: one wave factors the block, one row per lane in
-// registers, and every lane solves A x = e_c for its own column c in registers.  Larger ones:
+// registers, and every lane solves A x = e_c for its own column c, in registers up to 24
+// parameters, 8 rows at a time above.  Larger ones:
 // the blocked Cholesky of the LM (no damping), then the inverse block column by block column
 // -- workgroup j solves L Y = E_j and L^T X = Y for the CHOL_NB columns of block j, with the
 // off-diagonal products on FP64 MFMA and the triangular 64 x 64 solves 16 rows at a time, one
@@ -66,6 +67,85 @@ __device__ __forceinline__ void cov_small_n(const Plan& p, const DSub& sb, doubl
     }
 }
 
+// 25 .. SMALL_N parameters: the column lies in LDS and goes through registers in panels of 8 rows
+// (with all of it in registers the two solves unroll to thousands of FMAs, over 2000 spilled SGPRs
+// and ten minutes to compile: 34 us for 40 parameters, 94 for 41, 96 for 64; now 38, 56, 77; with the
+// factor in LDS as well, a row per step, 100, 104, 208).
+template <int N>
+__device__ __forceinline__ void cov_panels_n(const Plan& p, const DSub& sb, double* __restrict__ out, int factor, double* L) {
+    const int n = sb.n, c = threadIdx.x;
+    constexpr int LD = N + 2, LY = 65, W = 8;        // LD: rows of whole 16-byte chunks, an odd number of them
+    static_assert(N % W == 0, "whole panels");
+    double* inv = L + N * LD;                        // reciprocals of the diagonal
+    double* Y = inv + N + c;                         // this lane's column, pitch LY
+    {
+        double a[N], diag;
+        if (!chol_rows<N>(p.A + sb.a_off, n, 0.0, 0.0, a, diag)) {
+            if (c < n)
+                for (int i = 0; i < n; ++i) out[(long long)i * n + c] = __builtin_nan("");
+            return;
+        }
+        if (c < N) {
+#pragma unroll
+            for (int j = 0; j < N; ++j) L[c * LD + j] = a[j];
+            inv[c] = 1.0 / diag;
+        }
+    }
+    const int np = (n + W - 1) / W;                  // rows n .. W np - 1 are identity rows of the factor
+    for (int i = 0; i < W * np; ++i) Y[i * LY] = i == c ? 1.0 : 0.0;
+    __syncthreads();
+    for (int pp = 0; pp < np; ++pp) {                // L y = e_c
+        const int r0 = W * pp;
+        double x[W];
+#pragma unroll
+        for (int q = 0; q < W; ++q) x[q] = Y[(r0 + q) * LY];
+#pragma unroll
+        for (int j = 0; j < W; ++j) {
+            x[j] *= inv[r0 + j];
+#pragma unroll
+            for (int q = j + 1; q < W; ++q) x[q] = fma(-L[(r0 + q) * LD + r0 + j], x[j], x[q]);
+        }
+#pragma unroll
+        for (int q = 0; q < W; ++q) Y[(r0 + q) * LY] = x[q];
+#pragma unroll 4
+        for (int i = r0 + W; i < n; ++i) {
+            double t = Y[i * LY];
+#pragma unroll
+            for (int q = 0; q < W; ++q) t = fma(-L[i * LD + r0 + q], x[q], t);
+            Y[i * LY] = t;
+        }
+    }
+    for (int pp = factor ? -1 : np - 1; pp >= 0; --pp) {     // L^T x = y
+        const int r0 = W * pp;
+        double x[W];
+#pragma unroll
+        for (int q = 0; q < W; ++q) x[q] = Y[(r0 + q) * LY];
+#pragma unroll
+        for (int j = W - 1; j >= 0; --j) {
+            x[j] *= inv[r0 + j];
+#pragma unroll
+            for (int q = 0; q < j; ++q) x[q] = fma(-L[(r0 + j) * LD + r0 + q], x[j], x[q]);
+        }
+#pragma unroll
+        for (int q = 0; q < W; ++q) Y[(r0 + q) * LY] = x[q];
+#pragma unroll 4
+        for (int i = 0; i < r0; ++i) {
+            double t = Y[i * LY];
+#pragma unroll
+            for (int q = 0; q < W; ++q) t = fma(-L[(r0 + q) * LD + i], x[q], t);
+            Y[i * LY] = t;
+        }
+    }
+    if (c < n) {
+        // row c of F = L^{-T}, or column c of the inverse
+        const long long step = factor ? 1 : n, base = factor ? (long long)c * n : c;
+        for (int i = 0; i < n; ++i) out[base + i * step] = Y[i * LY];
+    }
+}
+
+// Doubles of LDS of a launch for sub-problems of up to N parameters.
+constexpr int cov_lds(int N) { return N <= 24 ? N * (N + 2) : N * (N + 2) + N + N * 65; }
+
 template <int NMAX>
 __global__ __launch_bounds__(64) void k_cov_small(Plan p, const int* __restrict__ small_subs,
                                                   double* __restrict__ cov, int factor) {
@@ -79,15 +159,15 @@ __global__ __launch_bounds__(64) void k_cov_small(Plan p, const int* __restrict_
     if constexpr (NMAX > 16)
         if (sb.n <= 24) return cov_small_n<24>(p, sb, out, factor, sm);
     if constexpr (NMAX > 24)
-        if (sb.n <= 40) return cov_small_n<40>(p, sb, out, factor, sm);
-    if constexpr (NMAX > 40) cov_small_n<64>(p, sb, out, factor, sm);
+        if (sb.n <= 40) return cov_panels_n<40>(p, sb, out, factor, sm);
+    if constexpr (NMAX > 40) cov_panels_n<64>(p, sb, out, factor, sm);
 }
 
 hipError_t launch_cov_small(const Plan& p, const int* small_subs, int n_small, int nmax, double* cov,
                             int factor, hipStream_t st) {
     if (n_small <= 0 || nmax <= 0) return hipSuccess;
 #define APX_CS(N)                                                                                              \
-    hipLaunchKernelGGL(k_cov_small<N>, dim3(n_small), dim3(64), (size_t)(N) * ((N) + 2) * sizeof(double), st, p, \
+    hipLaunchKernelGGL(k_cov_small<N>, dim3(n_small), dim3(64), cov_lds(N) * sizeof(double), st, p, \
                        small_subs, cov, factor)
     if (nmax <= 8) APX_CS(8);
     else if (nmax <= 16) APX_CS(16);

@@ -23,8 +23,9 @@ __device__ __forceinline__ double lm_wave_max(double v) {
 // whose pivot and column entries come by readlane, so no column step waits for LDS or a
 // barrier.  The factor goes through LDS once, for the back substitution's columns.  Latency
 // of its serial chain bounds it: with the rows in LDS and each step behind three barriers the
-// largest of 768 cutouts (36 parameters) took 64 us and one 8-parameter system 10 us.  The
-// retries happen inside the kernel.
+// solves of 512 sub-problems of 8, 24, 40, 41 and 64 parameters took 16, 40, 74, 78 and 145 us, now
+// 10, 19, 29, 57 and 60 (the 64-column rows spill 31 of 512 VGPRs).  The retries happen inside the
+// kernel.
 template <int N>
 __device__ __forceinline__ void chol_small_n(const Plan& p, int s, const DSub& sb, apx_lm_state* lm, double* sm) {
     const int n = sb.n, i = threadIdx.x;
