@@ -127,6 +127,7 @@ struct apx_problem {
     std::vector<double> g_w;
     std::vector<int> gr_seg, gr_idx;              // gradient sources per theta index
     std::vector<double> gr_w;
+    int max_sub_images = 0, max_par_cols = 0;     // images of one sub-problem, columns of one theta index
     std::vector<long long> a_off_csr, a_src;      // A assembly
     std::vector<int> a_sub, a_row, a_col;
     std::vector<int> par_sub, par_off, par_cols, par_sky_off, par_sky;
@@ -156,7 +157,7 @@ struct apx_problem {
     Layout L;
     std::map<std::string, size_t> off;
     Plan plan{};
-    double* asrc = nullptr;          // [pair_part | col_sum | (column numbers of the gradient) | img_sum]
+    double* asrc = nullptr;          // [pair_part | col_sum | gradient columns | img_sum]
     long long asrc_col = 0, asrc_gcol = 0, asrc_img = 0;
     double* chi2_sub = nullptr;      // [n_sub]
     double* chi2_trial = nullptr;    // [n_sub]
@@ -1581,6 +1582,7 @@ static apx_status build_plan(apx_problem* P, const apx_problem_desc* d) {
             }
             P->g_seg.push_back((int)P->g_idx.size());
             P->gr_seg.push_back((int)P->gr_idx.size());
+            P->max_par_cols = std::max(P->max_par_cols, (int)pc[p].size());
             P->par_off.push_back((int)P->par_cols.size());
             P->par_sky_off.push_back((int)P->par_sky.size());
             P->g_sub.push_back(std::max(0, P->par_sub[p]));
@@ -1588,7 +1590,10 @@ static apx_status build_plan(apx_problem* P, const apx_problem_desc* d) {
         P->chi_seg.assign(d->n_sub + 1, 0);
         P->sub_img.resize(d->n_images);
         for (const DImage& im : P->images) P->chi_seg[im.sub + 1]++;
-        for (int s = 0; s < d->n_sub; ++s) P->chi_seg[s + 1] += P->chi_seg[s];
+        for (int s = 0; s < d->n_sub; ++s) {
+            P->max_sub_images = std::max(P->max_sub_images, P->chi_seg[s + 1]);
+            P->chi_seg[s + 1] += P->chi_seg[s];
+        }
         std::vector<int> next(P->chi_seg.begin(), P->chi_seg.end() - 1);
         for (int k = 0; k < d->n_images; ++k) P->sub_img[next[P->images[k].sub]++] = k;
     }
@@ -2235,6 +2240,7 @@ static apx_status fwd_chi2(apx_problem* P, const PrepIO& pio, const float* data,
         tail.img_items = wsp<int2>(P, "img_items");
         tail.chi_seg = wsp<int>(P, "chi_seg");
         tail.sub_img = wsp<int>(P, "sub_img");
+        tail.summed = P->max_sub_images > TAIL_IMAGES;
         HIPCHK(launch_tail(p, tail, st));
     }
     return APX_OK;
@@ -2352,6 +2358,7 @@ static apx_status grad_sum(apx_problem* P, double* out) {
     a.n_cols = (int)P->cols.size();
     a.n_par = P->n_par;
     a.out = out;
+    a.summed = P->max_par_cols > GRAD_COLUMNS;
     HIPCHK(launch_grad_sum(a, P->ctx->stream));
     return APX_OK;
 }

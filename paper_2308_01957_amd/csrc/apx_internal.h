@@ -437,7 +437,9 @@ struct TailIO {
                               // ACCEPT: gain ratio, accept or reject, lambda, theta update
     apx_lm_state* lm;
     double* theta;
+    int summed;               // the image sums by a launch of their own
 };
+constexpr int TAIL_IMAGES = 8;
 hipError_t launch_tail(const Plan& p, const TailIO& io, hipStream_t st);
 // J^T W J and J^T W r from their partials: entry e of A sums src[ent_src[k]], k in
 // [ent_off[e], ent_off[e + 1]), in order; g[q] sums g_w[k] src[g_idx[k]] over g_seg.
@@ -457,11 +459,13 @@ hipError_t launch_assemble(const AsmA& a, hipStream_t st);
 // Gradient per theta index: the sources gr_idx of gr_seg, weighted; a source in [col0, col0 +
 // n_cols) stands for the sum of that column's tile partials (gcol_seg), others are entries of src.
 struct GradSum {
-    const double* src; const double* grad_part;
+    double* src; const double* grad_part;
     const int* gr_seg; const int* gr_idx; const double* gr_w; const int* gcol_seg;
     int col0, n_cols, n_par;
     double* out;
+    int summed;               // the columns' sums into src[col0 ..] by a launch of their own first
 };
+constexpr int GRAD_COLUMNS = 8;
 hipError_t launch_grad_sum(const GradSum& a, hipStream_t st);
 hipError_t launch_fill(double* x, long long n, double v, hipStream_t st);
 hipError_t launch_fill_f(float* x, long long n, float v, hipStream_t st);

@@ -523,17 +523,35 @@ hipError_t launch_col_sums(const Plan& p, const int* col_seg, const int* col_idx
     return hipGetLastError();
 }
 
+// One wave per image: its three sums.
+__global__ __launch_bounds__(256) void k_img_sums(PlanPtr pp, const int2* __restrict__ img_items) {
+    PlanRef p = *pp;
+    const int k = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (k >= p.n_images) return;
+    const int2 it = img_items[k];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        const double v = butterfly(lane_sum(it.x, it.y, [&](int i) { return p.fwd_part[3LL * i + c]; }));
+        if ((threadIdx.x & 63) == 0) p.img_sum[3 * k + c] = v;
+    }
+}
+
 // One workgroup per sub-problem: for each of its images, every thread takes items tid, tid +
 // 256, ... (all three components), then a fixed butterfly per wave and the four waves in order;
 // thread 0 adds the images' chi^2 in order.  One launch instead of four (image sums, chi^2,
-// check or accept): at 64 x 64 they were 1.8 us of work and 5 us of launch each.
+// check or accept): at 64 x 64 they were 1.8 us of work and 5 us of launch each.  An image costs
+// the workgroup 0.65 us, so where a sub-problem has more than TAIL_IMAGES of them (io.summed) the
+// image sums have a launch of their own, and one wave adds them (200 images in one sub-problem:
+// a chi^2 call 215 us with the images one after another, 77 so).
 __global__ __launch_bounds__(256) void k_tail(PlanPtr pp, TailIO io) {
     PlanRef p = *pp;
     __shared__ double red[4][3];
     __shared__ int acc_flag;
     const int s = blockIdx.x, lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     double chi = 0.0;                                    // thread 0's
-    for (int q = io.chi_seg[s]; q < io.chi_seg[s + 1]; ++q) {
+    if (io.summed && wv == 0)
+        chi = butterfly(lane_sum(io.chi_seg[s], io.chi_seg[s + 1], [&](int q) { return p.img_sum[3 * io.sub_img[q]]; }));
+    for (int q = io.summed ? io.chi_seg[s + 1] : io.chi_seg[s]; q < io.chi_seg[s + 1]; ++q) {
         const int k = io.sub_img[q];
         const int2 it = io.img_items[k];
         double v0 = 0.0, v1 = 0.0, v2 = 0.0;
@@ -581,17 +599,29 @@ __global__ __launch_bounds__(256) void k_tail(PlanPtr pp, TailIO io) {
 }
 
 hipError_t launch_tail(const Plan& p, const TailIO& io, hipStream_t st) {
+    if (io.summed) hipLaunchKernelGGL(k_img_sums, dim3((p.n_images + 3) / 4), dim3(256), 0, st, p.dev, io.img_items);
     hipLaunchKernelGGL(k_tail, dim3(p.n_sub), dim3(256), 0, st, p.dev, io);
     return hipGetLastError();
 }
 
-// One wave per theta index.
+// One wave per column: the sum of its tile partials.
+__global__ __launch_bounds__(256) void k_grad_cols(GradSum a) {
+    const int c = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (c >= a.n_cols) return;
+    const double v = butterfly(lane_sum(a.gcol_seg[c], a.gcol_seg[c + 1], [&](int i) { return a.grad_part[i]; }));
+    if ((threadIdx.x & 63) == 0) a.src[a.col0 + c] = v;
+}
+
+// One wave per theta index.  A column costs the wave 0.75 us, so where a parameter is tied over more
+// than GRAD_COLUMNS of them (a.summed) the columns have a launch of their own before it (200
+// components tied, in 200 images: a gradient call 391 us before both, 104 now).
 __global__ __launch_bounds__(256) void k_grad_sum(GradSum a) {
     const int k = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (k >= a.n_par) return;
     const int lane = threadIdx.x & 63;
     double acc = 0.0;
-    for (int q = a.gr_seg[k]; q < a.gr_seg[k + 1]; ++q) {
+    if (a.summed) acc = lane_sum(a.gr_seg[k], a.gr_seg[k + 1], [&](int q) { return a.gr_w[q] * a.src[a.gr_idx[q]]; });
+    for (int q = a.summed ? a.gr_seg[k + 1] : a.gr_seg[k]; q < a.gr_seg[k + 1]; ++q) {
         const int j = a.gr_idx[q], c = j - a.col0;
         const double w = a.gr_w[q];
         if (c >= 0 && c < a.n_cols) acc += w * lane_sum(a.gcol_seg[c], a.gcol_seg[c + 1], [&](int i) { return a.grad_part[i]; });
@@ -603,6 +633,7 @@ __global__ __launch_bounds__(256) void k_grad_sum(GradSum a) {
 
 hipError_t launch_grad_sum(const GradSum& a, hipStream_t st) {
     if (a.n_par <= 0) return hipSuccess;
+    if (a.summed && a.n_cols > 0) hipLaunchKernelGGL(k_grad_cols, dim3((a.n_cols + 3) / 4), dim3(256), 0, st, a);
     hipLaunchKernelGGL(k_grad_sum, dim3((a.n_par + 3) / 4), dim3(256), 0, st, a);
     return hipGetLastError();
 }
