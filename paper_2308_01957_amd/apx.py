@@ -337,6 +337,15 @@ class Problem:
         c = self.torch.cuda
         return contextlib.nullcontext() if c.current_device() == self.device.index else c.device(self.device)
 
+    def _run(self, call, *args):
+        """One library call.  The caller's stream waits for the library's also when it fails: part of it
+        may be enqueued, and its outputs go back to the caller's pool with the exception."""
+        try:
+            with self._on_device():
+                self._check(call(*args))
+        finally:
+            self._leave()
+
     def _pix(self, data, weight):
         t = self.torch
         check_buffer(data, self.device, t.float32, self.n_pix, "data")
@@ -397,9 +406,7 @@ class Problem:
         else:
             check_buffer(out, self.device, self.torch.float32, self.n_pix, "out")
             self._enter(th, out)
-        with self._on_device():
-            self._check(self.lib.apx_render(self._prob, th.data_ptr(), out.data_ptr()))
-        self._leave()
+        self._run(self.lib.apx_render, self._prob, th.data_ptr(), out.data_ptr())
         return out
 
     def chi2(self, theta, data, weight, out=None):
@@ -411,10 +418,7 @@ class Problem:
         else:
             check_buffer(out, self.device, self.torch.float64, self.n_sub, "out")
             self._enter(th, data, weight, out)
-        with self._on_device():
-            self._check(self.lib.apx_chi2(self._prob, th.data_ptr(), data.data_ptr(), weight.data_ptr(),
-                                          out.data_ptr()))
-        self._leave()
+        self._run(self.lib.apx_chi2, self._prob, th.data_ptr(), data.data_ptr(), weight.data_ptr(), out.data_ptr())
         return out
 
     def jacobian(self, theta):
@@ -422,9 +426,7 @@ class Problem:
         th = self._theta(theta)
         J = self.torch.empty((self.n_par, self.n_pix), dtype=self.torch.float32, device=self.device)
         self._enter(th)
-        with self._on_device():
-            self._check(self.lib.apx_jacobian(self._prob, th.data_ptr(), J.data_ptr(), self.n_pix))
-        self._leave()
+        self._run(self.lib.apx_jacobian, self._prob, th.data_ptr(), J.data_ptr(), self.n_pix)
         return J
 
     def jtwj(self, theta, data, weight):
@@ -436,10 +438,8 @@ class Problem:
         g = t.empty(self.n_par, dtype=t.float64, device=self.device)
         c2 = t.empty(self.n_sub, dtype=t.float64, device=self.device)
         self._enter(th, data, weight)
-        with self._on_device():
-            self._check(self.lib.apx_jtwj(self._prob, th.data_ptr(), data.data_ptr(), weight.data_ptr(),
-                                          A.data_ptr(), g.data_ptr(), c2.data_ptr()))
-        self._leave()
+        self._run(self.lib.apx_jtwj, self._prob, th.data_ptr(), data.data_ptr(), weight.data_ptr(), A.data_ptr(),
+                  g.data_ptr(), c2.data_ptr())
         return A, g, c2
 
     def block(self, A, s: int):
@@ -454,10 +454,8 @@ class Problem:
         C = t.empty(max(1, int(self.a_offsets[-1])), dtype=t.float64, device=self.device)
         c2 = t.empty(self.n_sub, dtype=t.float64, device=self.device)
         self._enter(th, data, weight)
-        with self._on_device():
-            self._check(self.lib.apx_covariance(self._prob, th.data_ptr(), data.data_ptr(), weight.data_ptr(),
-                                                C.data_ptr(), c2.data_ptr()))
-        self._leave()
+        self._run(self.lib.apx_covariance, self._prob, th.data_ptr(), data.data_ptr(), weight.data_ptr(),
+                  C.data_ptr(), c2.data_ptr())
         return C, c2
 
     def covariance_factor(self, theta, data, weight):
@@ -468,10 +466,8 @@ class Problem:
         F = t.empty(max(1, int(self.a_offsets[-1])), dtype=t.float64, device=self.device)
         c2 = t.empty(self.n_sub, dtype=t.float64, device=self.device)
         self._enter(th, data, weight)
-        with self._on_device():
-            self._check(self.lib.apx_covariance_factor(self._prob, th.data_ptr(), data.data_ptr(),
-                                                       weight.data_ptr(), F.data_ptr(), c2.data_ptr()))
-        self._leave()
+        self._run(self.lib.apx_covariance_factor, self._prob, th.data_ptr(), data.data_ptr(), weight.data_ptr(),
+                  F.data_ptr(), c2.data_ptr())
         return F, c2
 
     def hmc(self, theta, data, weight, F, step: float, n_leapfrog: int, z, u):
@@ -493,11 +489,9 @@ class Problem:
         samples = t.empty((n_samples, self.n_par), dtype=t.float64, device=self.device)
         stats = t.empty((n_samples, self.n_sub, 3), dtype=t.float64, device=self.device)
         self._enter(theta, data, weight, F, z, u)
-        with self._on_device():
-            self._check(self.lib.apx_hmc_run(self._prob, data.data_ptr(), weight.data_ptr(), theta.data_ptr(),
-                                             F.data_ptr(), float(step), int(n_leapfrog), n_samples,
-                                             z.data_ptr(), u.data_ptr(), samples.data_ptr(), stats.data_ptr()))
-        self._leave()
+        self._run(self.lib.apx_hmc_run, self._prob, data.data_ptr(), weight.data_ptr(), theta.data_ptr(),
+                  F.data_ptr(), float(step), int(n_leapfrog), n_samples, z.data_ptr(), u.data_ptr(),
+                  samples.data_ptr(), stats.data_ptr())
         return samples, stats
 
     def nuts(self, theta, data, weight, F, step: float, max_depth: int, z, u):
@@ -521,11 +515,9 @@ class Problem:
         samples = t.empty((n_samples, self.n_par), dtype=t.float64, device=self.device)
         stats = t.empty((n_samples, 4), dtype=t.float64, device=self.device)
         self._enter(theta, data, weight, F, z, u)
-        with self._on_device():
-            self._check(self.lib.apx_nuts_run(self._prob, data.data_ptr(), weight.data_ptr(), theta.data_ptr(),
-                                              F.data_ptr(), float(step), int(max_depth), n_samples,
-                                              z.data_ptr(), u.data_ptr(), samples.data_ptr(), stats.data_ptr()))
-        self._leave()
+        self._run(self.lib.apx_nuts_run, self._prob, data.data_ptr(), weight.data_ptr(), theta.data_ptr(),
+                  F.data_ptr(), float(step), int(max_depth), n_samples, z.data_ptr(), u.data_ptr(),
+                  samples.data_ptr(), stats.data_ptr())
         return samples, stats
 
     def nuts_warmup(self, theta, data, weight, F, step0: float, max_depth: int, target: float, z, u) -> float:
@@ -543,11 +535,8 @@ class Problem:
         self._pix(data, weight)
         check_buffer(theta, self.device, t.float64, self.n_par, "theta")
         self._enter(theta, data, weight, F, z, u)
-        with self._on_device():
-            self._check(self.lib.apx_nuts_warmup(self._prob, data.data_ptr(), weight.data_ptr(), theta.data_ptr(),
-                                                 F.data_ptr(), ctypes.byref(step), int(max_depth), n,
-                                                 float(target), z.data_ptr(), u.data_ptr()))
-        self._leave()
+        self._run(self.lib.apx_nuts_warmup, self._prob, data.data_ptr(), weight.data_ptr(), theta.data_ptr(),
+                  F.data_ptr(), ctypes.byref(step), int(max_depth), n, float(target), z.data_ptr(), u.data_ptr())
         return float(step.value)
 
     def render_vjp(self, theta, grad_model, out=None):
@@ -561,9 +550,7 @@ class Problem:
         if out is None:
             out = t.empty(self.n_par, dtype=t.float64, device=self.device)
         self._enter(th, gm, given)
-        with self._on_device():
-            self._check(self.lib.apx_render_vjp(self._prob, th.data_ptr(), gm.data_ptr(), out.data_ptr()))
-        self._leave()
+        self._run(self.lib.apx_render_vjp, self._prob, th.data_ptr(), gm.data_ptr(), out.data_ptr())
         return out
 
     def chi2_grad(self, theta, data, weight):
@@ -573,10 +560,8 @@ class Problem:
         g = t.empty(self.n_par, dtype=t.float64, device=self.device)
         c2 = t.empty(self.n_sub, dtype=t.float64, device=self.device)
         self._enter(th, data, weight)
-        with self._on_device():
-            self._check(self.lib.apx_chi2_grad(self._prob, th.data_ptr(), data.data_ptr(), weight.data_ptr(),
-                                               g.data_ptr(), c2.data_ptr()))
-        self._leave()
+        self._run(self.lib.apx_chi2_grad, self._prob, th.data_ptr(), data.data_ptr(), weight.data_ptr(),
+                  g.data_ptr(), c2.data_ptr())
         return g, c2
 
     def lm_init(self, theta, data, weight, theta_out=None, state_out=None):
@@ -597,29 +582,23 @@ class Problem:
         state = state_out if state_out is not None else \
             t.zeros(self.n_sub * LM_STATE_BYTES, dtype=t.uint8, device=self.device)
         self._enter(src, data, weight, theta_out, state_out)
-        with self._on_device():
-            self._check(self.lib.apx_lm_init(self._prob, th.data_ptr(), data.data_ptr(), weight.data_ptr(),
-                                             state.data_ptr()))
-        self._leave()
+        self._run(self.lib.apx_lm_init, self._prob, th.data_ptr(), data.data_ptr(), weight.data_ptr(),
+                  state.data_ptr())
         return th, state
 
     def lm_step(self, data, weight, theta, state):
         self._pix(data, weight)
         self._lm_bufs(theta, state)
         self._enter(data, weight, theta, state)
-        with self._on_device():
-            self._check(self.lib.apx_lm_step(self._prob, data.data_ptr(), weight.data_ptr(), theta.data_ptr(),
-                                             state.data_ptr()))
-        self._leave()
+        self._run(self.lib.apx_lm_step, self._prob, data.data_ptr(), weight.data_ptr(), theta.data_ptr(),
+                  state.data_ptr())
 
     def lm_run(self, n_iter: int, data, weight, theta, state, use_graph: bool = False):
         self._pix(data, weight)
         self._lm_bufs(theta, state)
         self._enter(data, weight, theta, state)
-        with self._on_device():
-            self._check(self.lib.apx_lm_run(self._prob, int(n_iter), data.data_ptr(), weight.data_ptr(),
-                                            theta.data_ptr(), state.data_ptr(), 1 if use_graph else 0))
-        self._leave()
+        self._run(self.lib.apx_lm_run, self._prob, int(n_iter), data.data_ptr(), weight.data_ptr(),
+                  theta.data_ptr(), state.data_ptr(), 1 if use_graph else 0)
 
     def set_timing(self, enabled: bool, classes=None):
         """Record kernel times (HIP events): every class, or only the named classes."""
