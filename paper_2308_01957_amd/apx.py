@@ -577,6 +577,7 @@ class Problem:
         if theta_out is None:
             th = src.clone()
         else:
+            self._leave()               # work of earlier calls on this buffer, from whichever stream
             th = theta_out
             th.copy_(src)
         state = state_out if state_out is not None else \

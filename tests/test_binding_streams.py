@@ -107,3 +107,11 @@ def test_the_caller_waits_for_every_call(problem, name, failing):
     at = LOG.index(name)
     assert LOG[at - 1] != name and "library waits for caller" in LOG[:at]
     assert LOG[at + 1:] == ["record library", "caller waits for library"], LOG
+
+
+def test_a_fit_is_started_again_behind_the_work_on_its_buffers(problem):
+    out = Tensor("theta_out", 4)
+    problem.lm_init(T["theta"], T["data"], T["weight"], theta_out=out, state_out=Tensor("state", 64))
+    copy = LOG.index("caller copies into theta_out")
+    assert LOG[:copy] == ["record library", "caller waits for library"], LOG
+    assert LOG.index("library waits for caller") > copy
