@@ -471,8 +471,9 @@ static int choose_group_shape(apx_ctx* C, int key, int P, const std::vector<int>
     return best;
 }
 
-// Derivative and gradient launches of fewer group tiles than this split the groups' components.
-static constexpr int G_SPLIT_WG = 1024;
+// Derivative and gradient launches split the groups' components until they have this many
+// workgroups per compute unit.
+static constexpr int G_SPLIT_WG = 8;
 
 
 // Regularised lower incomplete gamma P(a, x) by its power series (x < a + 1 here).
@@ -1961,11 +1962,16 @@ apx_status apx_problem_bind_workspace(apx_problem* P, void* dev, uint64_t bytes)
     p.gtiles = wsp<RTile>(P, "gtiles");
     p.n_gtiles = (int)P->gtiles.size();
     // Few group tiles: the components of a group are dealt to several workgroups, up to one per
-    // component, until there are G_SPLIT_WG (4 per compute unit; GSPLIT_FIGS).
+    // component of the largest group (the others' spare workgroups leave at once), until there
+    // are G_SPLIT_WG per compute unit.  Derivatives and gradient contraction, us, without the split
+    // and up to 4 and 8 per compute unit: 128 x 128 with 4 galaxies and 10 stars 16.5 and 17.1, 9.9
+    // and 10.0, 10.0 and 10.3; 187 x 301 with 8 galaxies and 12 stars 20.8 and 19.1, 14.5 and 13.7,
+    // 13.1 and 12.3; 300 x 300 with 20 galaxies and 300 stars 42.7 and 39.7, 42.2 and 39.3, 27.8 and
+    // 26.9; 16 per compute unit gain only where stars make most tiles (21.5 and 24.0 there).
     {
         int most = 1;
         for (const DGroup& g : P->groups) most = std::max(most, g.comp_end - g.comp_begin);
-        p.g_split = std::max(1, std::min(most, G_SPLIT_WG / std::max(1, p.n_gtiles)));
+        p.g_split = std::max(1, std::min(most, G_SPLIT_WG * compute_units(P->ctx) / std::max(1, p.n_gtiles)));
     }
     p.cc = wsp<CompConst>(P, "cc");
     p.stap = wsp<double>(P, "stap");

@@ -819,6 +819,7 @@ __global__ __launch_bounds__(256) void k_deriv(PlanPtr pp, const apx_lm_state* l
     __shared__ float tw[SHIFT ? STAP_STRIDE : 1];
     const RTile t = p.gtiles[blockIdx.x];
     const DGroup& gr = p.groups[t.a];
+    if (gr.comp_begin + (int)blockIdx.y >= gr.comp_end) return;
     if (lm && lm[gr.sub].need_jac == 0) return;
     const DImage& im = p.images[gr.image];
     const int ty = (int)threadIdx.x / RT_X, tx = (int)threadIdx.x % RT_X;
@@ -898,6 +899,7 @@ __global__ __launch_bounds__(256) void k_grad_tiles(PlanPtr pp) {
     __shared__ float tw[SHIFT ? STAP_STRIDE : 1];
     const RTile t = p.gtiles[blockIdx.x];
     const DGroup& gr = p.groups[t.a];
+    if (gr.comp_begin + (int)blockIdx.y >= gr.comp_end) return;
     const DImage& im = p.images[gr.image];
     const int tile_local = blockIdx.x - gr.tile_begin;
     const int ly = t.y0 + (int)threadIdx.x / RT_X;
