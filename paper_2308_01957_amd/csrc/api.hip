@@ -66,6 +66,9 @@ void scratch_lookup(int device) {
 
 namespace {
 
+// Runs of pixels of the J^T W J items of two groups, shortest and longest.
+constexpr int RUN_MIN = 256, RUN_MAX = 4096;
+
 struct PRange { int P, shape, begin, count, pair_begin, pair_count, fine; };
 
 template <class T>
@@ -118,6 +121,8 @@ struct apx_problem {
     int gram_begin[GRAM4_MAX_T + 2] = {};         // items of tile count t: [gram_begin[t], gram_begin[t + 1])
     std::vector<PairItem> xitems;                 // 4 x 4-block items of two groups, sorted by block shape
     int cross_begin[N_CROSS + 1] = {};            // items of block shape k: [cross_begin[k], cross_begin[k + 1])
+    int min_run = RUN_MIN;                        // their least run of pixels
+    size_t x_bytes = 0;                           // workspace of these items, partials and sources
     // reduction tables
     std::vector<int2> img_items;                  // FWD items of each image: first, end
     std::vector<int> col_seg, col_idx;            // JCOL items of each column
@@ -1382,7 +1387,8 @@ static apx_status build_plan(apx_problem* P, const apx_problem_desc* d) {
                 const DPair& pr = P->pairs[w.pi];
                 px += (double)ceil_div(w.na, ba) * ceil_div(w.nb, bb) * (pr.y1 - pr.y0) * (pr.x1 - pr.x0);
             }
-            const int run = 256 * (int)std::min(16.0, std::max(1.0, std::ceil(px / GRAM_ITEMS / 256.0)));
+            const int run = RUN_MIN * (int)std::min((double)RUN_MAX / RUN_MIN, std::max((double)P->min_run / RUN_MIN,
+                                                                                        std::ceil(px / GRAM_ITEMS / RUN_MIN)));
             for (const Narrow& w : list) {
                 const DPair& pr = P->pairs[w.pi];
                 const int bw = pr.x1 - pr.x0, bh = pr.y1 - pr.y0;
@@ -1402,6 +1408,7 @@ static apx_status build_plan(apx_problem* P, const apx_problem_desc* d) {
                                 it.row0 = r0;
                                 it.out_off = outoff;
                                 outoff += 16LL * ba * bb;
+                                P->x_bytes += 16 * sizeof(double) * ba * bb;
                                 items.push_back(it);
                             }
                 }
@@ -1489,6 +1496,7 @@ static apx_status build_plan(apx_problem* P, const apx_problem_desc* d) {
         };
         // keep item order: 64-wide tiles, 4 x 4 blocks of two groups, then of one with itself
         for (const PairItem& it : P->pitems64) add_block(P->pairs[it.pair], it.ta * 64, it.tb * 64, 64, 64, it.out_off, 64);
+        const size_t wide_src = contrib.size();
         for (int k = 0; k < N_CROSS; ++k)
             for (int i = P->cross_begin[k]; i < P->cross_begin[k + 1]; ++i) {
                 const PairItem& it = P->xitems[i];
@@ -1497,6 +1505,7 @@ static apx_status build_plan(apx_problem* P, const apx_problem_desc* d) {
                         add_block(P->pairs[it.pair], 4 * (it.ta + ta), 4 * (it.tb + tb), 4, 4,
                                   it.out_off + 16LL * (ta * cross_b(k) + tb), 4);
             }
+        P->x_bytes += P->xitems.size() * sizeof(PairItem) + (contrib.size() - wide_src) * sizeof(long long);
         for (const PairItem& it : P->gitems) {
             int q = 0;
             for (int ta = 0; ta < it.ta; ++ta)
@@ -1679,7 +1688,8 @@ static void layout(apx_problem* P) {
     // buffers
     ws_take<CompConst>(P, "cc", P->comps.size());
     ws_take<double>(P, "stap", P->shift != APX_SHIFT_NONE ? STAP_STRIDE * P->comps.size() : 0);
-    ws_take<float>(P, "S", P->n_ext);
+    // the FP32 render: the model of the FP32 objective, and what live-PSF columns convolve
+    ws_take<float>(P, "S", P->objective == APX_OBJECTIVE_FP32 || P->has_live_cols ? P->n_ext : 0);
     ws_take<double>(P, "S64", P->objective == APX_OBJECTIVE_FP64 ? P->n_ext : 0);
     ws_take<float>(P, "Abar", P->n_ext);
     ws_take<float>(P, "rbuf", P->n_pix);
@@ -1827,19 +1837,40 @@ const char* apx_last_error(const apx_ctx* ctx) { return ctx ? ctx->err.c_str() :
 apx_status apx_problem_create(apx_ctx* ctx, const apx_problem_desc* desc, apx_problem** out) {
     if (!ctx || !desc || !out) return APX_E_INVALID;
     *out = nullptr;
-    apx_problem* P = new apx_problem();
-    P->ctx = ctx;
-    apx_status st;
-    try {
-        st = build_plan(P, desc);
-    } catch (const std::exception& e) {
-        st = fail(ctx, APX_E_INVALID, std::string("plan construction failed: ") + e.what());
-    }
-    if (st != APX_OK) {
-        delete P;
+    auto plan = [&](int min_run, apx_problem*& P) {
+        P = new apx_problem();
+        P->ctx = ctx;
+        P->min_run = min_run;
+        apx_status st;
+        try {
+            st = build_plan(P, desc);
+        } catch (const std::exception& e) {
+            st = fail(ctx, APX_E_INVALID, std::string("plan construction failed: ") + e.what());
+        }
+        if (st != APX_OK) {
+            delete P;
+            P = nullptr;
+            return st;
+        }
+        layout(P);
         return st;
+    };
+    apx_problem* P = nullptr;
+    const apx_status st = plan(RUN_MIN, P);
+    if (st != APX_OK) return st;
+    // a problem whose short runs of J^T W J alone keep it out of the library's scratch takes
+    // longer ones, the longest at the last
+    for (int run = 4 * RUN_MIN; run <= RUN_MAX && P->L.total > APX_SCRATCH_BYTES &&
+                                P->L.total - P->x_bytes <= APX_SCRATCH_BYTES; run *= 4) {
+        apx_problem* Q = nullptr;
+        if (plan(run, Q) != APX_OK) break;
+        if (Q->L.total > APX_SCRATCH_BYTES) {
+            delete Q;
+            continue;
+        }
+        delete P;
+        P = Q;
     }
-    layout(P);
     *out = P;
     return APX_OK;
 }
