@@ -346,13 +346,14 @@ constexpr int pitch64(int w) {
 // evaluations of an LM fit (io.fit) take the rows one by one: the fold rounds differently, and a
 // fit follows the last bits of its residuals (see k_render64).
 // Each window goes through registers in pieces of CH64 taps, the next piece's LDS reads in
-// flight while the current one is multiplied.  Above P = 41 the pieces are pinned in that order
-// (the compiler otherwise reads whole windows of both rows first, 256 registers and spills at
-// P = 51: 411 us for 2048 x 2048 against 297 pinned); below, its own order is as fast on a
-// full chip and better with one workgroup per CU (P = 31: 35 against 43 us).
-// Bound by FP64 issue and LDS reads alike: by 2 P^2 per output, on one 2048 x 2048 image,
-// 34 -> 55 TFLOP/s at P = 15 without and with the fold, 44 -> 74 at P = 25, 49 -> 80 at P = 41,
-// 53 -> 78 at P = 51, 41 -> 63 at P = 63.
+// flight while the current one is multiplied.  Above P = 41 the pieces of folded rows are pinned
+// in that order (the compiler otherwise reads whole windows of both rows first, 256 registers and
+// spills at P = 51: 411 us for 2048 x 2048 against 297 pinned); below, its own order is as fast on
+// a full chip and better with one workgroup per CU (P = 31: 35 against 43 us).  Single rows keep
+// the compiler's order at every P (pinned 443 against 404 us at P = 51, 891 against 642 at 57).
+// Bound by FP64 issue and LDS reads alike: one 2048 x 2048 image, 2 P^2 per output, row by row
+// and folded: 36 and 46 TFLOP/s at P = 15, 48 and 67 at P = 25, 51 and 78 at P = 41, 54 and 78 at
+// P = 51, 37 and 59 at P = 63 (2-D windows held whole, without a fold: 31, 43, 50, 53, 33).
 constexpr int CH64 = 8;
 __device__ __forceinline__ void pin(double (&a)[CV_R], int& o1, int& o2) {
     asm volatile("" : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(a[4]), "+v"(a[5]), "+v"(a[6]), "+v"(a[7]),
@@ -430,10 +431,10 @@ __global__ __launch_bounds__(TH * TW / R) void k_conv64(PlanPtr pp, const ConvJo
 #pragma unroll
     for (int r = 0; r < R; ++r) acc[r] = 0.0;
     constexpr int N = R + P - 1, NC = (P + CH64 - 1) / CH64;
-    constexpr bool PINNED = P > (R == CV_R ? 41 : 51);
+    constexpr bool PINNED = P > (R == CV_R ? 41 : 51);           // folded rows
     // acc[r] += sum_V K[U, V] s[r + P - 1 - V], V ascending, s the window that starts at pair o1 of
     // the tile (with TWO: plus the one at pair o2), read from its end as pairs (ds_read_b128).
-    // pin() keeps the pieces apart: a piece's FMAs come before it, the reads that follow (whose
+    // pin() keeps the pieces apart (folded rows): a piece's FMAs come before it, the reads that follow (whose
     // offsets pass through it) after.
     static_assert(N % 2 == 0 && R % 2 == 0 && P % 2 == 1 && LW % 2 == 0 && CH64 % 2 == 0, "windows are whole pairs");
     const double2* tile2 = reinterpret_cast<const double2*>(tile);
@@ -494,7 +495,7 @@ __global__ __launch_bounds__(TH * TW / R) void k_conv64(PlanPtr pp, const ConvJo
                     for (int r = 0; r < R; ++r) part[r] = fma(kv, s[r + P - 1 - V], part[r]);
                 }
             }
-            if constexpr (PINNED) pin(part, o1, o2);
+            if constexpr (PINNED && TWO) pin(part, o1, o2);
         }
 #pragma unroll
         for (int r = 0; r < R; ++r) acc[r] += part[r];
