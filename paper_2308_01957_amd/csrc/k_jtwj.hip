@@ -203,16 +203,16 @@ __global__ __launch_bounds__(256) void k_pair(PlanPtr pp, const DPair* __restric
 // lane 16 k + 4 b + j, D[i][j] at lane 16 i + 4 b + j; measured on gfx950).  Lane L takes pixel
 // L / 4 of a 16-pixel chunk and column L % 4 of a tile of 4 columns, so one instruction
 // contracts 16 pixels of one 4 x 4 tile pair, and the tiles are loaded straight from J into
-// registers (each reused by every pair it is in).  An item is a run of pixels of the pair's
-// box counted along its rows (no padding at row ends; the row of a pixel comes from a
-// multiplication by the reciprocal of the box width, GramDiv).  Its four waves take every
-// fourth run of 16 NS pixels; all loads of a wave's next run are issued before the MFMAs of
-// the current one.  At the end each wave folds its four blocks (lanes xor 4, xor 8) and the
-// four waves are added in order.
-// What bounds it: latency of the loads while there are few waves, which is why the plan cuts
-// the boxes into enough items to fill the chip (add_runs in the plan), then for wide groups
-// the MFMAs (35 columns: 54 per 16 pixels, 98 us of MFMA issue in the 163 us that 3.9 M pixels
-// take) and for narrow ones the loads (8 columns against 8, 28 M pixels: 273 us).
+// registers (each reused by every pair it is in).  The items of a group with itself (k_gram4) are
+// stages of PAIR_KC pixels of a row, padded at row ends; those of two groups (k_cross4) are runs
+// of pixels counted along the rows of the pair's box (no padding).  The row of a stage or of a
+// pixel comes from a multiplication by the reciprocal of the row's length (GramDiv).  All loads
+// of a wave's next chunks are issued before the MFMAs of the current ones.  At the end each wave
+// folds its four blocks (lanes xor 4, xor 8) and the four waves are added in order.
+// What bounds them: latency of the loads while there are few waves (k_cross4's runs are cut
+// short enough to fill the chip, add_runs in the plan), then for wide groups the MFMAs (35
+// columns: 54 per 16 pixels, 98 us of MFMA issue in the 192 us that 3.9 M pixels take in
+// k_gram4) and for narrow ones the loads (8 columns against 8, 28 M pixels: 273 us).
 struct GramDiv {                                    // e / bw for 0 <= e < 2^31, bw >= 1
     unsigned m, bw;                                 // m = floor((2^32 - 1) / bw)
     __device__ __forceinline__ explicit GramDiv(int w) : m(0xffffffffu / (unsigned)w), bw((unsigned)w) {}

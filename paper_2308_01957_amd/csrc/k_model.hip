@@ -494,7 +494,7 @@ __device__ __forceinline__ double point_weight(const CompConst& c, int y, int x)
 // DEG terms are taken while |d| <= bin_rho(DEG), where the rest is below 1.4e-16
 // (|C(g, k)| < 0.016 at k = 8, < 0.0094 at k = 12 for g = 1/(2n), n in [0.36, 10]); the bound on
 // |d| over the nodes must hold on every active lane of the wave, so the branch is uniform.
-// Bound by FP64 issue; the full render of 768 cutouts (70 154 tiles of 8 x 32) went from 847
+// Bound by FP64 issue; the full render of 768 cutouts (70 154 tiles of 8 x 32) goes from 821
 // to 626 us, a 187 x 301 image with 4 x 4 Gauss-Legendre nodes from 49 to 32 us.
 constexpr double bin_rho(int deg) { return deg == BIN_DEG ? 0.07 : 0.015; }
 constexpr int BIN_DEG_FAR = 7;
