@@ -42,6 +42,9 @@ if ROOT not in sys.path:
 PEAK_FP32_VALU_TFLOPS = 256 * 4 * 32 * 2 * 2.4e9 / 1e12    # 157.3
 PEAK_FP64_TFLOPS = PEAK_FP32_VALU_TFLOPS / 2             # 78.6, vector and MFMA
 PEAK_HBM_GBS = 8000.0
+# Outside a fit the FP64 model convolution adds mirrored input rows under a stamp that is the
+# same upside down, so it runs about half of the 2 P^2 its rate is counted by.
+FOLD_NOTE = "; an algorithmic rate of 2 P^2 FLOP per pixel, of which mirrored stamp rows halve what runs"
 
 
 def cpu_baseline_blend(spec, data, weight):
@@ -239,18 +242,19 @@ def class_rooflines(spec, prob, kt, phases, per_call=(1, 1), n_obj=None):
     pair_bytes = float(pair_bytes_per_sub(spec).sum())
     n_fwd = kt.get("conv_fwd", (0.0, 0))[1] / per_call[0] if n_obj is None else n_obj
     n_adj = kt.get("conv_adj", (0.0, 0))[1] / per_call[1]
+    fwd_note = FOLD_NOTE if n_obj is None else ""     # a fit takes every stamp row by itself
     models = {}
     if conv_mode == 0:       # the direct-convolution counts do not price an FFT convolution
         models["conv_jcol"] = ((float(flop.sum()) + psf_cols) * phases, PEAK_FP32_VALU_TFLOPS,
                                "k_conv<P,JCOL> (2-D)")
         models["conv_fwd"] = (fwd * n_fwd, PEAK_FP64_TFLOPS if fp64 else PEAK_FP32_VALU_TFLOPS,
-                              "k_conv<P,FWD,%s>" % ("double" if fp64 else "float"))
+                              "k_conv64<P> (FP64)" + fwd_note if fp64 else "k_conv<P,FWD,float>")
         models["conv_adj"] = (fwd * n_adj, PEAK_FP32_VALU_TFLOPS, "k_conv<P,ADJ>")
     out = {}
     ms_p = kt.get("pairs", (0.0, 0))[0]
     if ms_p > 0 and pair_flop > 0:
-        out["pairs"] = dict(pair_roof(pair_flop * phases, pair_bytes * phases, ms_p, "k_pair / k_gram4 (FP64 MFMA)"),
-                            ms_total=ms_p, traffic=None)
+        out["pairs"] = dict(pair_roof(pair_flop * phases, pair_bytes * phases, ms_p,
+                                      "k_pair / k_gram4 / k_cross4 (FP64 MFMA)"), ms_total=ms_p, traffic=None)
     for cls, (fl, peak, name) in models.items():
         ms = kt.get(cls, (0.0, 0))[0]
         if ms <= 0 or fl <= 0:
@@ -630,14 +634,16 @@ def run_cutouts(args, torch, apx, synth):
                               "of a phase, cutouts whose stamp is not rank one and whose job stays on direct "
                               "tiles)", timed="conv_jcol" in jclasses or mode == 1),
         "render": cls_roof(flop_ren, kt["render"][0], PEAK_FP64_TFLOPS,
-                           "k_render64 (FP64 trial render; %g FLOP per Sersic node)" % RENDER64_FLOP_PER_NODE,
+                           "k_render64 (FP64 trial render; %g FLOP per Sersic node, each node by its own log2 "
+                           "and 2^x as a fit runs them)" % RENDER64_FLOP_PER_NODE,
                            timed=True),
         "conv_fft": cls_roof(pairs_fft * FFT_PAIR_FLOP, fft_ms, PEAK_FP32_VALU_TFLOPS,
                              "k_conv_fft<JCOL> (FFT-tile Jacobian convolutions; 5 N log2 N per 128^2 "
                              "transform, two transforms and the spectrum product per item pair)",
                              timed="conv_fft" in jclasses),
-        "conv_fwd": cls_roof(flop_fwd, ko["conv_fwd"][0], PEAK_FP64_TFLOPS, "k_conv<P,FWD,double> (FP64 objective)"),
-        "pairs": dict(pair_roof(flop_pair, byte_pair, ko["pairs"][0], "k_gram4 / k_pair (FP64 MFMA)"),
+        "conv_fwd": cls_roof(flop_fwd, ko["conv_fwd"][0], PEAK_FP64_TFLOPS, "k_conv64<P> (FP64 objective; a fit takes every stamp row by itself: 2 P^2 FLOP per pixel "
+                             "as run)"),
+        "pairs": dict(pair_roof(flop_pair, byte_pair, ko["pairs"][0], "k_gram4 / k_cross4 / k_pair (FP64 MFMA)"),
                       ms_per_step=ko["pairs"][0] / max(1, args.steps), traffic=None, timed_region=False),
     }
     per_class["conv_jcol"].update({"ms_per_phase": jcol_ms / max(1, args.steps),
@@ -827,7 +833,7 @@ def run_field(args, torch, apx, synth):
     rf_adj = {"bound": "alu", "kernel": adj_name, "achieved": achieved,
               "peak": PEAK_FP32_VALU_TFLOPS, "unit": "TFLOP/s", "frac": achieved / PEAK_FP32_VALU_TFLOPS,
               "ms_per_eval": adj_ms / reps}
-    rf_fwd = {"bound": "alu", "kernel": f"k_conv<{P_psf},FWD,double> (FP64)", "achieved": ach_fwd,
+    rf_fwd = {"bound": "alu", "kernel": f"k_conv64<{P_psf}> (FP64){FOLD_NOTE}", "achieved": ach_fwd,
               "peak": PEAK_FP64_TFLOPS, "unit": "TFLOP/s", "frac": ach_fwd / PEAK_FP64_TFLOPS,
               "ms_per_eval": fwd_ms / reps}
     dominant, other = (rf_fwd, rf_adj) if fwd_ms >= adj_ms else (rf_adj, rf_fwd)
