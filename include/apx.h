@@ -511,7 +511,9 @@ apx_status apx_render_vjp(apx_problem* p, const double* theta, const float* grad
  * normal equations, counters zeroed.  theta: device FP64 [n_par], read only (copy it into
  * the buffer the iterations update); data, weight: device FP32 [n_pix]; state: device,
  * [n_sub] apx_lm_state, overwritten.  Out-of-domain theta raises the sticky APX_E_DOMAIN
- * flag (apx_problem_check).  Asynchronous on the context stream. */
+ * flag (apx_problem_check).  The chi2 of a fit's states and apx_chi2 at the same theta agree
+ * to FP64 rounding, not to the bit (a fit evaluates its model node by node and stamp row by
+ * stamp row).  Asynchronous on the context stream. */
 apx_status apx_lm_init(apx_problem* p, const double* theta, const float* data,
                        const float* weight, apx_lm_state* state);
 
